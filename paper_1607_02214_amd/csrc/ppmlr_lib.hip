@@ -25,9 +25,11 @@ using ppmlr::kStatSlots;
 
 struct AxisTables {
     // FP64 and FP32 copies: extended widths [M], centres [M], faces [M+1];
-    // interior widths and centres [n]
+    // interior widths, centres, 1 / width and 1 / (x_{i+1} - x_{i-1}) [n]
     double *dx64 = nullptr, *xc64 = nullptr, *xf64 = nullptr, *dxi64 = nullptr, *xci64 = nullptr;
-    float *dx32 = nullptr, *xc32 = nullptr, *xf32 = nullptr, *dxi32 = nullptr, *xci32 = nullptr;
+    double *rdx64 = nullptr, *rdc64 = nullptr;
+    float *dx32 = nullptr, *xc32 = nullptr, *xf32 = nullptr, *xci32 = nullptr;
+    float *rdx32 = nullptr, *rdc32 = nullptr;
 };
 
 struct ppmlr_ctx {
@@ -149,7 +151,8 @@ void free_tables(ppmlr_ctx *c)
 {
     for (int a = 0; a < 3; ++a) {
         AxisTables &t = c->tab[a];
-        void *ptrs[] = {t.dx64, t.xc64, t.xf64, t.dxi64, t.xci64, t.dx32, t.xc32, t.xf32, t.dxi32, t.xci32};
+        void *ptrs[] = {t.dx64, t.xc64, t.xf64, t.dxi64, t.xci64, t.rdx64, t.rdc64,
+                        t.dx32, t.xc32, t.xf32, t.xci32, t.rdx32, t.rdc32};
         for (void *p : ptrs)
             if (p) (void)hipFree(p);
         t = AxisTables();
@@ -225,8 +228,9 @@ int stride_for(int threads, int elem)
 {
     if (threads > 1024) return -1;
     const int sm = threads <= 256 ? 256 : (threads + 127) / 128 * 128;
-    if (ppmlr::lds_bytes(kSlotsA + kSlotsB, sm, elem) <= 160 * 1024) return sm;
-    if (ppmlr::lds_bytes(kSlotsA + kSlotsB, threads, elem) <= 160 * 1024 && elem == 8) return 0;
+    const int P = threads / (2 * kG + 1) + 1;   // at most: a tile's pencils have 15 zones or more
+    if (ppmlr::lds_bytes(kSlotsA + kSlotsB, sm, elem, P) <= 160 * 1024) return sm;
+    if (ppmlr::lds_bytes(kSlotsA + kSlotsB, threads, elem, P) <= 160 * 1024 && elem == 8) return 0;
     return -1;
 }
 
@@ -263,16 +267,7 @@ void fill_args(const ppmlr_ctx *c, ppmlr::SweepArgs<T> &a, const T *in, T *u, in
     const int nx = c->n[0], ny = c->n[1], nz = c->n[2];
     const int N = c->n[axis], L = seg_len(N, nseg), M = L + 2 * kG;
     const bool f64 = sizeof(T) == 8;
-    auto tabs = [&](int ax, const T *&dx, const T *&xc, const T *&xf, const T *&dxi, const T *&xci) {
-        const AxisTables &t = c->tab[ax];
-        if (f64) {
-            dx = (const T *)t.dx64; xc = (const T *)t.xc64; xf = (const T *)t.xf64;
-            dxi = (const T *)t.dxi64; xci = (const T *)t.xci64;
-        } else {
-            dx = (const T *)t.dx32; xc = (const T *)t.xc32; xf = (const T *)t.xf32;
-            dxi = (const T *)t.dxi32; xci = (const T *)t.xci32;
-        }
-    };
+    auto pick = [&](const double *p64, const float *p32) { return f64 ? (const T *)p64 : (const T *)p32; };
     std::memset(&a, 0, sizeof(a));
     a.u = u;
     a.vol = (long long)nx * ny * nz;
@@ -297,11 +292,16 @@ void fill_args(const ppmlr_ctx *c, ppmlr::SweepArgs<T> &a, const T *in, T *u, in
     a.tiles_q = (a.nq + P - 1) / P;
     a.inv_div = 1.0f / (float)(axis == 0 ? M : P);
     a.ntiles = a.tiles_q * a.nr;
-    const T *dummy;
-    tabs(axis, a.dx, a.xc, a.xf, dummy, dummy);
-    const T *t0, *t1, *t2;
-    tabs(qax, t0, t1, t2, a.dx_q, a.xc_q);
-    tabs(rax, t0, t1, t2, a.dx_r, a.xc_r);
+    const AxisTables &tn = c->tab[axis], &tq = c->tab[qax], &tr = c->tab[rax];
+    a.dx = pick(tn.dx64, tn.dx32);
+    a.xc = pick(tn.xc64, tn.xc32);
+    a.xf = pick(tn.xf64, tn.xf32);
+    a.rdx = pick(tn.rdx64, tn.rdx32);
+    a.rdc = pick(tn.rdc64, tn.rdc32);
+    a.xc_q = pick(tq.xci64, tq.xci32);
+    a.xc_r = pick(tr.xci64, tr.xci32);
+    a.rdx_q = pick(tq.rdx64, tq.rdx32);
+    a.rdx_r = pick(tr.rdx64, tr.rdx32);
     a.bc_lo = c->bc_lo[axis];
     a.bc_hi = c->bc_hi[axis];
     a.gamma = (T)c->gamma;
@@ -331,11 +331,6 @@ void fill_args(const ppmlr_ctx *c, ppmlr::SweepArgs<T> &a, const T *in, T *u, in
     a.p_floor = (T)c->opt.p_floor;
     a.stats = c->opt.collect_stats ? c->d_stats : nullptr;
     a.cfl_max = c->d_cflmax;
-    if (f64) {
-        a.dxw_x = (const T *)c->tab[0].dxi64; a.dxw_y = (const T *)c->tab[1].dxi64; a.dxw_z = (const T *)c->tab[2].dxi64;
-    } else {
-        a.dxw_x = (const T *)c->tab[0].dxi32; a.dxw_y = (const T *)c->tab[1].dxi32; a.dxw_z = (const T *)c->tab[2].dxi32;
-    }
     // plain tile order along q then r (grouping q tiles that share cache
     // lines before stepping r was measured on the z sweep and raised its
     // fetched bytes)
@@ -355,7 +350,7 @@ ppmlr_status launch_one(ppmlr_ctx *c, const ppmlr::SweepArgs<T> &a, hipStream_t 
 {
     const int threads = block_threads(a.P, a.M);
     const int slots = (GUESS == ppmlr::kGuessPlain ? kSlotsA : ppmlr::kSlotsAGuess) + kSlotsB;
-    const size_t lds = ppmlr::lds_bytes(slots, SM > 0 ? SM : a.S, (int)sizeof(T));
+    const size_t lds = ppmlr::lds_bytes(slots, SM > 0 ? SM : threads, (int)sizeof(T), a.P);
     const int blocks = 8 * a.tiles_per_xcd;
     auto kern = ppmlr::sweep_kernel<AX, T, STATS, FUSE, SM, GUESS, TRACE>;
     if (lds > 64 * 1024) {
@@ -426,7 +421,7 @@ ppmlr_status sweep_typed(ppmlr_ctx *c, const T *in, T *u, hipStream_t st, double
 {
     const int P = pick_tile(c, axis, (int)sizeof(T));
     const int M = tile_M(c, axis, (int)sizeof(T));
-    if (block_threads(P, M) > 1024 || ppmlr::lds_bytes(kSlotsA + kSlotsB, P * M, (int)sizeof(T)) > 160 * 1024)
+    if (block_threads(P, M) > 1024 || ppmlr::lds_bytes(kSlotsA + kSlotsB, P * M, (int)sizeof(T), P) > 160 * 1024)
         return fail(c, PPMLR_EINVAL, "tile does not fit one workgroup");
     ppmlr::SweepArgs<T> a;
     fill_args(c, a, in, u, axis, dt, dt_dev, P, seg_count(c, axis, (int)sizeof(T)));
@@ -841,10 +836,12 @@ ppmlr_status ppmlr_create(const ppmlr_grid *grid, double gamma, const ppmlr_coor
     for (int a = 0; a < 3 && !s; ++a) {
         extend_axis(c, a);
         AxisTables &t = c->tab[a];
-        std::vector<double> dxi(c->n[a]), xci(c->n[a]);
+        std::vector<double> dxi(c->n[a]), xci(c->n[a]), rdx(c->n[a]), rdc(c->n[a]);
         for (int i = 0; i < c->n[a]; ++i) {
             dxi[i] = c->faces[a][i + 1] - c->faces[a][i];
             xci[i] = 0.5 * (c->faces[a][i] + c->faces[a][i + 1]);
+            rdx[i] = 1.0 / dxi[i];
+            rdc[i] = 1.0 / (c->ext_xc[a][i + kG + 1] - c->ext_xc[a][i + kG - 1]);
         }
         if (!s) s = upload(c, &t.dx64, c->ext_dx[a]);
         if (!s) s = upload(c, &t.xc64, c->ext_xc[a]);
@@ -854,8 +851,11 @@ ppmlr_status ppmlr_create(const ppmlr_grid *grid, double gamma, const ppmlr_coor
         if (!s) s = upload(c, &t.dx32, c->ext_dx[a]);
         if (!s) s = upload(c, &t.xc32, c->ext_xc[a]);
         if (!s) s = upload(c, &t.xf32, c->ext_xf[a]);
-        if (!s) s = upload(c, &t.dxi32, dxi);
         if (!s) s = upload(c, &t.xci32, xci);
+        if (!s) s = upload(c, &t.rdx64, rdx);
+        if (!s) s = upload(c, &t.rdc64, rdc);
+        if (!s) s = upload(c, &t.rdx32, rdx);
+        if (!s) s = upload(c, &t.rdc32, rdc);
     }
     c->partial_blocks = kTotBlocks;
     if (!s) s = hip_check(c, hipMalloc((void **)&c->d_stats, sizeof(unsigned long long) * kStatWords * kStatSlots),
@@ -1337,7 +1337,7 @@ ppmlr_status ppmlr_set_tile(ppmlr_ctx *c, int axis, int pencils)
     if (pencils > 0) {
         int M = tile_M(c, axis, 4);
         if (block_threads(pencils, M) > 1024) return fail(c, PPMLR_EINVAL, "tile exceeds 1024 threads");
-        if (ppmlr::lds_bytes(kSlotsA + kSlotsB, pencils * M, 4) > 160 * 1024)
+        if (ppmlr::lds_bytes(kSlotsA + kSlotsB, pencils * M, 4, pencils) > 160 * 1024)
             return fail(c, PPMLR_EINVAL, "tile exceeds the LDS budget");
     }
     c->tile[axis] = pencils;
@@ -1584,12 +1584,11 @@ struct PersistArgs {
 template <typename T, bool STATS, int SM>
 __global__ void __launch_bounds__(SM) ensemble_persistent_kernel(const PersistArgs<T> p)
 {
-    // all LDS is the dynamic allocation (tile buffers at address 0, then the
-    // workgroup's scalars: per-wave maxima, counters, the barrier flag)
+    // all LDS is the dynamic allocation (the workgroup's scalars: per-wave
+    // maxima, counters, the barrier flag; then the tile buffers)
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    unsigned char *tail = smem_raw + ppmlr::lds_tile_bytes(kSlotsA + kSlotsB, SM, (int)sizeof(T));
-    double *s_red = reinterpret_cast<double *>(tail);
-    unsigned int *s_stat = reinterpret_cast<unsigned int *>(tail + 16 * sizeof(double));
+    double *s_red = reinterpret_cast<double *>(smem_raw);
+    unsigned int *s_stat = reinterpret_cast<unsigned int *>(smem_raw + 16 * sizeof(double));
     unsigned int *s_ok = s_stat + ppmlr::kStatWords;
     double *cred = s_red;
     const int b = blockIdx.x;
@@ -1799,7 +1798,8 @@ ppmlr_status ensemble_typed(ppmlr_ctx *const *ctxs, const ppmlr_state *const *st
         // the host tables must stay alive until the copies have been made
         if (!err) err = hip_check(c0, hipStreamSynchronize(st), "hipStreamSynchronize");
     }
-    const size_t lds = ppmlr::lds_bytes(kSlotsA + kSlotsB, block, (int)sizeof(T));
+    // (members differ in pencils per workgroup: at most block / 15)
+    const size_t lds = ppmlr::lds_bytes(kSlotsA + kSlotsB, block, (int)sizeof(T), block / (2 * kG + 1));
     long long j = 0;                                       // sweeps enqueued by this call
     if (persistent && !err) {
         // one cooperative launch of as many workgroups as the device holds at

@@ -43,21 +43,26 @@ constexpr int kStatWords = 37;  // iteration histogram [32], floors, nonconverge
                                 // learned-guess faces, learned-guess fallbacks
 constexpr int kStatSlots = 64;  // copies of the counters (workgroup b adds to copy b % 64)
 
-// Dynamic LDS of a sweep workgroup: the tile buffers A and B (slots values
-// per zone, stride S) from address 0, then the workgroup's scalars: 16
-// doubles of per-wave signal-speed maxima, the kStatWords counters, the
-// learned guess's face count (or a persistent launch's barrier flag) and a
-// persistent launch's tile claim.  With the buffers at address 0 a zone's LDS
-// address is its lane offset, with the slot in the instruction's offset
-// field; behind static shared arrays every address needed their size added.
-constexpr int kLdsTail = 16 * 8 + (kStatWords + 2) * 4;
-__host__ __device__ constexpr size_t lds_tile_bytes(int slots, int S, int elem)
+// Dynamic LDS of a sweep workgroup: the workgroup's scalars (16 doubles of
+// per-wave signal-speed maxima, the kStatWords counters, the learned guess's
+// face count or a persistent launch's barrier flag, and a persistent launch's
+// tile claim), then the tile buffers A and B (slots values per zone, stride
+// S).  A zone reads its neighbours' slots up to two zones away without a
+// bounds test: what a zone at the end of a tile reads beyond it (another
+// value's slot, the scalars in front, the guard of two zones behind) reaches
+// ghost zones only, as the tile's 7 ghost zones are the radius of the whole
+// sweep.  P: pencils per workgroup (the zones of y and z tiles are P slots
+// apart).
+constexpr int kLdsScalars = 16 * 8 + (kStatWords + 2) * 4;
+__host__ __device__ constexpr size_t lds_guard(int P, int elem) { return ((size_t)2 * P * elem + 15) / 16 * 16; }
+__host__ __device__ constexpr size_t lds_front(int P, int elem)
 {
-    return ((size_t)slots * (size_t)S * (size_t)elem + 15) / 16 * 16;
+    constexpr size_t head = (kLdsScalars + 15) / 16 * 16;
+    return lds_guard(P, elem) > head ? lds_guard(P, elem) : head;
 }
-__host__ __device__ constexpr size_t lds_bytes(int slots, int S, int elem)
+__host__ __device__ constexpr size_t lds_bytes(int slots, int S, int elem, int P)
 {
-    return lds_tile_bytes(slots, S, elem) + kLdsTail;
+    return lds_front(P, elem) + ((size_t)slots * (size_t)S * (size_t)elem + 15) / 16 * 16 + lds_guard(P, elem);
 }
 
 enum { kPeriodic = 0, kOutflow = 1, kInflow = 2 };
@@ -91,12 +96,19 @@ template <> struct Ar<double> {
     __device__ static inline double rcp(double x) { return rcp64(x); }
     __device__ static inline double div(double a, double b) { return a * rcp64(b); }
     __device__ static inline double sqrt_(double x) { return __builtin_sqrt(x); }
+    // square root of a positive, finite value: x rsqrt(x) with one correction
+    __device__ static inline double sqrtp(double x)
+    {
+        const double y = rsqrt64(x), r = x * y;
+        return __builtin_fma(__builtin_fma(-r, r, x), 0.5 * y, r);
+    }
     __device__ static inline double rsqrt(double x) { return rsqrt64(x); }
 };
 template <> struct Ar<float> {
     __device__ static inline float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
     __device__ static inline float div(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
     __device__ static inline float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
+    __device__ static inline float sqrtp(float x) { return __builtin_amdgcn_sqrtf(x); }
     __device__ static inline float rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
 };
 
@@ -145,7 +157,8 @@ struct SweepArgs {
     int seg_fast;               // 1: consecutive tiles are the segments of one pencil group; 0: bands in turn
     const T *dx, *xc, *xf;      // sweep axis: extended widths [Mext], centres [Mext], faces [Mext+1]
     const T *xc_q, *xc_r;       // transverse centres (interior zones)
-    const T *dx_q, *dx_r;       // transverse widths (interior zones)
+    const T *rdx, *rdc;         // sweep axis, interior zones: 1 / dx, 1 / (x_{i+1} - x_{i-1})
+    const T *rdx_q, *rdx_r;     // transverse 1 / dx (interior zones)
     int bc_lo, bc_hi;
     T gamma;
     T dt;                       // used when dt_dev == nullptr
@@ -162,7 +175,6 @@ struct SweepArgs {
     T tol, p_floor;
     unsigned long long *stats;  // kStatSlots x kStatWords counters or nullptr
     unsigned long long *cfl_max;// fused signal-speed max (double bits, kCflSlots slots) or nullptr
-    const T *dxw_x, *dxw_y, *dxw_z;       // interior widths of all axes (fused CFL)
     // learned Riemann guess (FP32 single-run sweeps)
     const unsigned short *mlp_frag;       // packed BF16 weight fragments
     const float *mlp_theta;               // FP32 parameters (biases)
@@ -175,29 +187,40 @@ struct SweepArgs {
 // Riemann initial-guess modes of the sweep body
 enum { kGuessPlain = 0, kGuessLearned = 1, kGuessHarvest = 2 };
 
-// Background field B_d = M [3 (m.r) r / r^5 - m / r^3] + b_ext at (x, y, z).
-template <typename T>
-__device__ inline void background(const SweepArgs<T> &a, T x, T y, T z, T &bx, T &by, T &bz)
-{
-    bx = a.bext_x;
-    by = a.bext_y;
-    bz = a.bext_z;
-    if (a.dip_m != T(0)) {
-        T r2 = x * x + y * y + z * z;
-        T ir = Ar<T>::rsqrt(r2);
-        T ir2 = ir * ir;
-        T ir3 = ir2 * ir;
-        T ir5 = ir3 * ir2;
-        T mr = a.dir_x * x + a.dir_y * y + a.dir_z * z;
-        T c = T(3) * mr * ir5;
-        bx += a.dip_m * (c * x - a.dir_x * ir3);
-        by += a.dip_m * (c * y - a.dir_y * ir3);
-        bz += a.dip_m * (c * z - a.dir_z * ir3);
+// Background field B_d = M [3 (m.r) r / r^5 - m / r^3] + b_ext along a
+// pencil, in the pencil frame (n, t1, t2): t1, t2 are the cyclic successors of
+// the sweep axis.  What depends on the pencil alone is set up once for the
+// zone's two evaluations (centre and right face).
+template <int AX, typename T>
+struct PencilField {
+    T c1, c2, ct2, mt3;            // transverse position, its square, 3 (m.r) of the transverse part
+    T en, e1, e2, mn, m1, m2;      // uniform field, dipole direction
+    __device__ inline PencilField(const SweepArgs<T> &a, T c1_, T c2_) : c1(c1_), c2(c2_)
+    {
+        const T e[3] = {a.bext_x, a.bext_y, a.bext_z}, m[3] = {a.dir_x, a.dir_y, a.dir_z};
+        en = e[AX]; e1 = e[(AX + 1) % 3]; e2 = e[(AX + 2) % 3];
+        mn = m[AX]; m1 = m[(AX + 1) % 3]; m2 = m[(AX + 2) % 3];
+        ct2 = c1 * c1 + c2 * c2;
+        mt3 = T(3) * (m1 * c1 + m2 * c2);
     }
-}
+    __device__ inline void at(const SweepArgs<T> &a, T n, T &bn, T &b1, T &b2) const
+    {
+        bn = en;
+        b1 = e1;
+        b2 = e2;
+        if (a.dip_m != T(0)) {
+            const T ir = Ar<T>::rsqrt(n * n + ct2);
+            const T ir2 = ir * ir;
+            const T g = a.dip_m * (ir2 * ir);                       // M / r^3
+            const T c = ((T(3) * mn) * n + mt3) * ir2 * g;          // 3 M (m.r) / r^5
+            bn = c * n + (bn - g * mn);
+            b1 = c * c1 + (b1 - g * m1);
+            b2 = c * c2 + (b2 - g * m2);
+        }
+    }
+};
 
-// Map pencil-frame coordinates (n, t1, t2) of axis AX to (x, y, z) and the
-// field back; t1, t2 are the cyclic successors of the sweep axis.
+// Pencil-frame coordinates (n, t1, t2) of axis AX as (x, y, z).
 template <int AX, typename T>
 __device__ inline void to_xyz(T n, T t1, T t2, T &x, T &y, T &z)
 {
@@ -212,38 +235,6 @@ __device__ inline void to_pencil(T bx, T by, T bz, T &bn, T &b1, T &b2)
     else if (AX == 1) { bn = by; b1 = bz; b2 = bx; }
     else { bn = bz; b1 = bx; b2 = by; }
 }
-template <int AX, typename T>
-__device__ inline void field_at(const SweepArgs<T> &a, T n, T c1, T c2, T &bn, T &b1, T &b2)
-{
-    T x, y, z, bx, by, bz;
-    to_xyz<AX>(n, c1, c2, x, y, z);
-    background(a, x, y, z, bx, by, bz);
-    to_pencil<AX>(bx, by, bz, bn, b1, b2);
-}
-
-// Edge value a_{j+1/2} on nonuniform widths w0..w3 = w_{j-1..j+2}
-// (Colella & Woodward 1984, Eq. 1.6) from the (limited) slopes of zones j
-// and j+1.  The width weights are shared by all variables of a face and
-// folded into three coefficients: a_j + E0 (a_{j+1} - a_j) + E2 da_{j+1} + E3 da_j.
-template <typename T>
-struct EdgeW {
-    T E0, E2, E3;
-    __device__ inline void init(T w0, T w1, T w2, T w3)
-    {
-        T i12 = Ar<T>::rcp(w1 + w2);
-        T id1 = Ar<T>::rcp(T(2) * w1 + w2);
-        T id2 = Ar<T>::rcp(w1 + T(2) * w2);
-        T inv4 = Ar<T>::rcp(w0 + w1 + w2 + w3);
-        T t1 = T(2) * w2 * w1 * i12 * ((w0 + w1) * id1 - (w3 + w2) * id2);
-        E0 = w1 * i12 + t1 * inv4;
-        E2 = -w1 * (w0 + w1) * id1 * inv4;
-        E3 = w2 * (w2 + w3) * id2 * inv4;
-    }
-    __device__ inline T edge(T aj, T ajp, T daj, T dajp) const
-    {
-        return aj + E0 * (ajp - aj) + E2 * dajp + E3 * daj;
-    }
-};
 
 // Median of three.
 __device__ inline float med3_(float x, float y, float z) { return __builtin_amdgcn_fmed3f(x, y, z); }
@@ -252,82 +243,80 @@ __device__ inline double med3_(double x, double y, double z)
     return fmax_(fmin_(x, y), fmin_(fmax_(x, y), z));
 }
 
-// Eq. 1.8 limiter: sgn(da) min(|da|, 2|dm|, 2|dp|) where dm and dp share a
-// sign, else zero.  When they share a sign da shares it too (the weights of
-// Eq. 1.7 are positive).  In single precision this is two medians: med(dm,
-// dp, 0) is the one-sided difference nearer zero when the signs agree and
-// zero otherwise, and med(da, 2 med(dm, dp, 0), 0) clips da to it.
-__device__ inline float limit_slope(float da, float dm, float dp)
+// Half of the Eq. 1.8 limited slope sgn(da) min(|da|, 2|dm|, 2|dp|) (zero
+// where dm and dp differ in sign), from hd = da / 2.  When dm and dp share a
+// sign da shares it too (the weights of Eq. 1.7 are positive).  In single
+// precision this is two medians: med(dm, dp, 0) is the one-sided difference
+// nearer zero when the signs agree and zero otherwise, and med(hd, that, 0)
+// clips hd to it.  The slopes travel halved (the edge weights take the factor
+// back, exactly), which saves the doubling of every variable's clip value.
+__device__ inline float limit_half(float hd, float dm, float dp) { return med3_(hd, med3_(dm, dp, 0.0f), 0.0f); }
+__device__ inline double limit_half(double hd, double dm, double dp)
 {
-    const float mm = med3_(dm, dp, 0.0f);
-    return med3_(da, mm + mm, 0.0f);
-}
-__device__ inline double limit_slope(double da, double dm, double dp)
-{
-    double m = fmin_(fmin_(fabs_(0.5 * da), fabs_(dm)), fabs_(dp));
-    double r = copysign_(m + m, dp);
+    const double r = copysign_(fmin_(fmin_(fabs_(hd), fabs_(dm)), fabs_(dp)), dp);
     return (dp * dm > 0.0) ? r : 0.0;
 }
 
-// Average slope times width in zone j on widths wm, w0, wp (CW84 Eq. 1.7),
-// da = A (a_{j+1} - a_j) + B (a_j - a_{j-1}), limited by Eq. 1.8.
+// Width weights of a zone on widths wm, w0, wp, wpp of zones j-1 .. j+2,
+// shared by all variables: the (halved) average slope times width da_j / 2 =
+// A (a_{j+1} - a_j) + B (a_j - a_{j-1}) (CW84 Eq. 1.7) and the right edge
+// a_{j+1/2} = a_j + E0 (a_{j+1} - a_j) + E3 da_j / 2 - E2 da_{j+1} / 2
+// (Eq. 1.6).
 template <typename T>
-struct SlopeW {
-    T A, B;
-    __device__ inline void init(T wm, T w0, T wp)
+struct Weights {
+    T A, B, E0, E2, E3;
+    __device__ inline Weights(T wm, T w0, T wp, T wpp)
     {
-        T cs = w0 * Ar<T>::rcp(wm + w0 + wp);
-        A = cs * (T(2) * wm + w0) * Ar<T>::rcp(wp + w0);
-        B = cs * (w0 + T(2) * wp) * Ar<T>::rcp(wm + w0);
-    }
-    __device__ inline T slope(T am, T a0, T ap) const
-    {
-        T dp = ap - a0;
-        T dm = a0 - am;
-        return limit_slope(A * dp + B * dm, dm, dp);
+        const T sm = wm + w0, s0 = w0 + wp, sp = wp + wpp;
+        const T i0 = Ar<T>::rcp(s0), q = wp + s0;                    // q = w0 + 2 wp
+        const T cs = T(0.5) * w0 * Ar<T>::rcp(sm + wp);
+        A = cs * (wm + sm) * i0;
+        B = cs * q * Ar<T>::rcp(sm);
+        const T f0 = w0 * i0, inv = Ar<T>::rcp(sm + sp);
+        const T r1 = sm * Ar<T>::rcp(w0 + s0), r2 = sp * Ar<T>::rcp(q);
+        const T u0 = (w0 + w0) * inv, up = (wp + wp) * inv;
+        E0 = f0 + up * f0 * (r1 - r2);
+        E2 = u0 * r1;
+        E3 = up * r2;
     }
 };
 
-// Domain-of-dependence fraction y with its two shared coefficients.
+// Domain-of-dependence fraction y with its two shared coefficients: y / 2 and
+// 6 (y / 2) (1 - 2 y / 3).
 template <typename T>
 struct Frac {
-    T h, c;   // y/2 and 1 - 2y/3
-    __device__ inline explicit Frac(T y) : h(T(0.5) * y), c(T(1) - (T(2) / T(3)) * y) {}
+    T h, c;
+    __device__ inline explicit Frac(T y) : h(T(0.5) * y), c(y * (T(3) - T(2) * y)) {}
 };
 
-// Flattening toward the zone average, then CW84 Eq. 1.10 monotonicity.  At a
-// local extremum both edges take the zone average; otherwise the edge on the
-// far side of an overshooting parabola is moved to 3a - 2a_other.  Both rules
-// are one median each: for a monotone profile (say a_L < a < a_R) the
-// overshoot test a6 > dA reads a_L < 3a - 2a_R, so the new left edge is
-// max(a_L, 3a - 2a_R) = med(a_L, 3a - 2a_R, a) (a is the largest of the
-// three); at an extremum 3a - 2a_R lies beyond a on the far side from a_L, so
-// the median is a.  Likewise on the right with a_L and a_R exchanged.
+// Zone parabola after the CW84 Eq. 1.10 monotonicity constraint: left and
+// right edge L, R, their difference D and a sixth of the curvature, S = a -
+// (L + R) / 2.  At a local extremum both edges take the zone average;
+// otherwise the edge on the far side of an overshooting parabola is moved to
+// 3a - 2a_other.  Both rules are one median each: for a monotone profile (say
+// a_L < a < a_R) the overshoot test a6 > dA reads a_L < 3a - 2a_R, so the new
+// left edge is max(a_L, 3a - 2a_R) = med(a_L, 3a - 2a_R, a) (a is the largest
+// of the three); at an extremum 3a - 2a_R lies beyond a on the far side from
+// a_L, so the median is a.  Likewise on the right with a_L and a_R exchanged.
 template <typename T>
-__device__ inline void parabola(T a, T aL, T aR, T f, T &oL, T &oD, T &o6)
-{
-    aL = aL + f * (a - aL);
-    aR = aR + f * (a - aR);
-    const T a3 = T(3) * a;
-    const T nL = med3_(aL, a3 - T(2) * aR, a);
-    const T nR = med3_(aR, a3 - T(2) * aL, a);
-    oL = nL;
-    oD = nR - nL;
-    o6 = T(6) * (a - T(0.5) * (nL + nR));
-}
-
-// Averages of a zone parabola over the fraction y next to its right edge
-// (avgR) or left edge (avgL) (CW84 Eq. 1.12).
-template <typename T>
-__device__ inline T avgR(T aL, T dA, T a6, const Frac<T> &f)
-{
-    return (aL + dA) - f.h * (dA - f.c * a6);
-}
-template <typename T>
-__device__ inline T avgL(T aL, T dA, T a6, const Frac<T> &f)
-{
-    return aL + f.h * (dA + f.c * a6);
-}
+struct Para {
+    T L, R, D, S;
+    __device__ inline void set(T a, T aL, T aR)
+    {
+        const T a3 = T(3) * a;
+        edges(a, med3_(aL, a3 - T(2) * aR, a), med3_(aR, a3 - T(2) * aL, a));
+    }
+    __device__ inline void edges(T a, T l, T r)
+    {
+        L = l;
+        R = r;
+        D = R - L;
+        S = a - T(0.5) * (L + R);
+    }
+    // averages over the fraction y next to the right or left edge (Eq. 1.12)
+    __device__ inline T right(const Frac<T> &f) const { return R - f.h * D + f.c * S; }
+    __device__ inline T left(const Frac<T> &f) const { return L + f.h * D + f.c * S; }
+};
 
 // Counter update aggregated per wave: the lowest active lane of each group of
 // lanes with the same bin adds the group's population to the workgroup's LDS
@@ -415,8 +404,8 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     static_assert(GUESS == kGuessPlain || (SM > 0 && sizeof(T) == 4 && STATS),
                   "learned / harvest modes are FP32 sweeps with a compile-time stride and counters");
     static_assert(!TRACE || GUESS == kGuessPlain, "the characteristic mode takes the plain interface solve");
-    const int S = SM > 0 ? SM : a.S;                      // LDS stride
-    T *sA = reinterpret_cast<T *>(smem_raw);
+    const int S = SM > 0 ? SM : (int)blockDim.x;          // LDS stride
+    T *sA = reinterpret_cast<T *>(smem_raw + lds_front(a.P, (int)sizeof(T)));
     T *sB = sA + (GUESS == kGuessPlain ? kSlotsA : kSlotsAGuess) * S;
     const int q0 = tq * a.P;
 
@@ -432,7 +421,10 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     const int qd = (int)(((float)tid + 0.5f) * a.inv_div);
     if (AX == 0) { p = qd; i = tid - p * M; }             // zones of a pencil adjacent
     else { i = qd; p = tid - i * P; }                     // pencils adjacent (coalesced)
-    const int d = (AX == 0) ? 1 : P;                      // slot offset of zone i+1
+    // slot offset of zone i+1 (kept from the compiler for x, which would fold
+    // it into address arithmetic per slot)
+    int d = (AX == 0) ? 1 : P;
+    if (AX == 0) asm("" : "+s"(d));
     const int q = q0 + p;
     const int g0 = seg * a.L;                             // first interior zone of the segment
     const int ie = g0 + i;                                // index into the extended tables
@@ -441,11 +433,9 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     const int g = ie - kG;                                // zone index along the pencil
     const int gend = min(g0 + a.L, N);                    // end of the segment's interior
     const bool interior = pen && g >= g0 && g < gend;
-    const int tsafe = slot_ok ? tid : Suse - 1;           // padding lanes read a valid slot
-    auto nb = [&](int k) -> int {                         // slot of zone i+k (clamped)
-        int ii = i + k;
-        return (ii >= 0 && ii < M && ie + k >= 0 && ie + k < Mext && slot_ok) ? tid + k * d : tsafe;
-    };
+    const bool face_ok = pen && i >= 3 && i <= M - 5;     // faces whose two states are complete
+    // slots of the zones i-2 .. i+2 (see the LDS layout for the ends of a tile)
+    const int sm1 = tid - d, sp1 = tid + d, sm2 = sm1 - d, sp2 = sp1 + d;
     // faces owned by this segment (counted and recorded once per pencil):
     // -1/2 .. N-1/2 over all segments
     const int own_lo = seg == 0 ? -1 : g0;
@@ -472,23 +462,23 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     bool inflow_zone = false;
     if (g < 0) {
         if (a.bc_lo == kPeriodic) { src = g % N; if (src < 0) src += N; }
-        else if (a.bc_lo == kOutflow) src = 0;
-        else inflow_zone = true;
+        else { src = 0; inflow_zone = a.bc_lo != kOutflow; }
     } else if (g >= N) {
         if (a.bc_hi == kPeriodic) src = g % N;
-        else if (a.bc_hi == kOutflow) src = N - 1;
-        else inflow_zone = true;
+        else { src = N - 1; inflow_zone = a.bc_hi != kOutflow; }
     }
     // centre and right-face background field (pencil frame)
     T bdn = 0, bd1 = 0, bd2 = 0, bfn = 0, bf1 = 0, bf2 = 0;
     if (a.has_bd) {
-        field_at<AX>(a, xci, c1, c2, bdn, bd1, bd2);
-        field_at<AX>(a, xfr, c1, c2, bfn, bf1, bf2);
+        const PencilField<AX, T> fld(a, c1, c2);
+        fld.at(a, xci, bdn, bd1, bd2);
+        fld.at(a, xfr, bfn, bf1, bf2);
     }
     // conserved state in pencil frame: rho, mn, m1, m2, bn, b1, b2, E
     T Q[8];
     constexpr int kn = AX, k1 = (AX + 1) % 3, k2 = (AX + 2) % 3;
-    if (pen && !inflow_zone) {
+    {
+        // every lane loads a zone of the pencil (inflow ghosts are replaced below)
         const unsigned int o = base + (unsigned int)(src * (int)a.stride_n);
         Q[0] = elem(a.vin[0], o);
         Q[1] = elem(a.vin[1 + kn], o);
@@ -498,7 +488,8 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
         Q[5] = elem(a.vin[4 + k1], o);
         Q[6] = elem(a.vin[4 + k2], o);
         Q[7] = elem(a.vin[7], o);
-    } else if (pen) {
+    }
+    if (inflow_zone) {
         // inflow ghost: primitive inflow state with B' = B_in - B_d(centre)
         // (a time series of inflow states puts this step's in a.in_dev)
         T in[8] = {a.in_rho, a.in_vx, a.in_vy, a.in_vz, a.in_bx, a.in_by, a.in_bz, a.in_p};
@@ -519,39 +510,34 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
         Q[6] = pb2;
         Q[7] = in[7] / (gam - T(1)) + T(0.5) * in[0] * (vn * vn + v1 * v1 + v2 * v2) +
                T(0.5) * (pbn * pbn + pb1 * pb1 + pb2 * pb2);
-    } else {
-        Q[0] = T(1); Q[1] = Q[2] = Q[3] = T(0); Q[4] = Q[5] = Q[6] = T(0); Q[7] = T(1);
     }
     const T rho = Q[0];
     const T irho = Ar<T>::rcp(rho);
     const T un = Q[1] * irho, v1 = Q[2] * irho, v2 = Q[3] * irho;
     const T bn = Q[4], b1 = Q[5], b2 = Q[6];
-    T pth = (gam - T(1)) * (Q[7] - T(0.5) * rho * (un * un + v1 * v1 + v2 * v2) -
-                            T(0.5) * (bn * bn + b1 * b1 + b2 * b2));
+    const T bt2 = b1 * b1 + b2 * b2;
+    T pth = (gam - T(1)) * (Q[7] - T(0.5) * ((Q[1] * un + Q[2] * v1 + Q[3] * v2) + (bn * bn + bt2)));
     const bool floored = pth < a.p_floor;
     if (floored) pth = a.p_floor;
     const T dm = rho * dxi;
-    const T Pt = pth + bd1 * b1 + bd2 * b2 + T(0.5) * (b1 * b1 + b2 * b2);
+    const T Pt = pth + bd1 * b1 + bd2 * b2 + T(0.5) * bt2;
     const T Pa = Pt + T(0.5) * (bd1 * bd1 + bd2 * bd2);
     const bool cnt_floor = interior && floored;
     const bool cnt_bad = interior && (!(rho > T(0)) || !__builtin_isfinite(rho) || !__builtin_isfinite(Q[7]));
     // primitive set used for reconstruction: rho, u, v1, v2, b1, b2, p
     const T W[7] = {rho, un, v1, v2, b1, b2, pth};
-    if (slot_ok) {
 #pragma unroll
-        for (int k = 0; k < 7; ++k) sA[k * S + tid] = W[k];
-        sA[7 * S + tid] = dm;
-        sA[8 * S + tid] = bn;
-        sA[9 * S + tid] = Pt;
-        sA[10 * S + tid] = Pa;
-        sA[11 * S + tid] = bfn;
-        sA[12 * S + tid] = bf1;
-        sA[13 * S + tid] = bf2;
-    }
+    for (int k = 0; k < 7; ++k) sA[k * S + tid] = W[k];
+    sA[7 * S + tid] = dm;
+    sA[8 * S + tid] = bn;
+    sA[9 * S + tid] = Pt;
+    sA[10 * S + tid] = Pa;
+    sA[11 * S + tid] = bfn;
+    sA[12 * S + tid] = bf1;
+    sA[13 * S + tid] = bf2;
     __syncthreads();
 
     // ------------------------------------------------------------ R2
-    const int sm1 = nb(-1), sp1 = nb(1), sp2 = nb(2), sm2 = nb(-2);
     const T dmm = sA[7 * S + sm1], dmp = sA[7 * S + sp1], dmp2 = sA[7 * S + sp2];
     const T bnm = sA[8 * S + sm1], bnp = sA[8 * S + sp1];
     const T bln = sA[11 * S + sm1], bl1 = sA[12 * S + sm1], bl2 = sA[13 * S + sm1];  // left face
@@ -563,16 +549,14 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     T edgeR[7];
     T ftil = T(0);
     {
-        SlopeW<T> s0;
-        s0.init(dmm, dm, dmp);
-        EdgeW<T> ew;
-        ew.init(dmm, dm, dmp, dmp2);
-        T da0[7], apv[7];
+        const Weights<T> w(dmm, dm, dmp, dmp2);
+        // (the edge without the right neighbour's slope waits in edgeR)
+        T da0[7];
 #pragma unroll
         for (int k = 0; k < 7; ++k) {
-            const T am = sA[k * S + sm1];
-            apv[k] = sA[k * S + sp1];
-            da0[k] = s0.slope(am, W[k], apv[k]);
+            const T dmv = W[k] - sA[k * S + sm1], dpv = sA[k * S + sp1] - W[k];
+            da0[k] = limit_half(w.A * dpv + w.B * dmv, dmv, dpv);
+            edgeR[k] = W[k] + w.E0 * dpv + w.E3 * da0[k];
         }
         if (a.flatten) {
             T Ptm2 = sA[9 * S + sm2], Ptp2 = sA[9 * S + sp2];
@@ -588,19 +572,15 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
                 else ftil = T(1);
             }
         }
-        if (slot_ok) {
 #pragma unroll
-            for (int k = 0; k < 7; ++k) sB[k * S + tid] = da0[k];
-            sB[7 * S + tid] = ftil;
-        }
+        for (int k = 0; k < 7; ++k) sB[k * S + tid] = da0[k];
+        sB[7 * S + tid] = ftil;
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 7; ++k) edgeR[k] = ew.edge(W[k], apv[k], da0[k], sB[k * S + sp1]);
+        for (int k = 0; k < 7; ++k) edgeR[k] -= w.E2 * sB[k * S + sp1];
     }
-    if (slot_ok) {
 #pragma unroll
-        for (int k = 0; k < 7; ++k) sA[(9 + k) * S + tid] = edgeR[k];
-    }
+    for (int k = 0; k < 7; ++k) sA[(9 + k) * S + tid] = edgeR[k];
     __syncthreads();
 
     // ------------------------------------------------------------ R3
@@ -609,35 +589,47 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
         T fm = sB[7 * S + sm1], fp = sB[7 * S + sp1];
         fl = tmax(ftil, (Ptp - Ptm < T(0)) ? fp : fm);
     }
-    T pLc[7], pDc[7], p6c[7];
+    // Flattening toward the zone average.  Few zones are near a shock, so a
+    // wave without one skips it (x + 0 (a - x) = x).
+    const bool flat = a.flatten && __any(fl != T(0));
+    T edgeL[7];
 #pragma unroll
-    for (int k = 0; k < 7; ++k) {
-        T aL = sA[(9 + k) * S + sm1];
-        parabola(W[k], aL, edgeR[k], fl, pLc[k], pDc[k], p6c[k]);
+    for (int k = 0; k < 7; ++k) edgeL[k] = sA[(9 + k) * S + sm1];
+    if (flat) {
+#pragma unroll
+        for (int k = 0; k < 7; ++k) {
+            edgeL[k] += fl * (W[k] - edgeL[k]);
+            edgeR[k] += fl * (W[k] - edgeR[k]);
+        }
     }
+    Para<T> pc[7];
+#pragma unroll
+    for (int k = 1; k < 4; ++k) pc[k].set(W[k], edgeL[k], edgeR[k]);
     // tracing speeds (Lagrangian): normal pair C_n, Alfven pair C_A
     const T Bt1c = bd1 + b1, Bt2c = bd2 + b2, Bnc = bdn + bn;
-    const T Cn = Ar<T>::sqrt_(rho * (gam * pth + Bt1c * Bt1c + Bt2c * Bt2c));
-    const T CA = Ar<T>::sqrt_(rho) * tabs(Bnc);
     const T idm = Ar<T>::rcp(dm);
-    const Frac<T> yn(tmin(T(1), Cn * dt * idm));
-    const Frac<T> yA(tmin(T(1), CA * dt * idm));
+    const T tdm = dt * idm;
+    const Frac<T> yn(tmin(T(1), Ar<T>::sqrtp(rho * (gam * pth + Bt1c * Bt1c + Bt2c * Bt2c)) * tdm));
+    const Frac<T> yA(tmin(T(1), Ar<T>::sqrtp(rho) * tabs(Bnc) * tdm));
     // time-centring of the couplings left out of the two decoupled Riemann
     // problems: oblique-field terms and the variation of B_n along the pencil
-    const T hdt = T(0.5) * dt;
-    const T dbn = (bnp - bnm) * Ar<T>::rcp(T(0.5) * dmm + dm + T(0.5) * dmp);
-    const T ddn = (bfn - bln) * idm, dd1 = (bf1 - bl1) * idm, dd2 = (bf2 - bl2) * idm;
-    const T dBn = ddn + dbn;
-    // (the oblique-field terms are in the eigenvectors of the characteristic mode)
-    T corrP = TRACE ? T(0) : hdt * rho * Bnc * (Bt1c * pDc[2] + Bt2c * pDc[3]) * idm;
-    T corrB1 = TRACE ? T(0) : -hdt * rho * Bt1c * pDc[1] * idm;
-    T corrB2 = TRACE ? T(0) : -hdt * rho * Bt2c * pDc[1] * idm;
-    const T corrU = hdt * (Bnc * dbn + bn * ddn);
-    const T corrV1 = hdt * (b1 * dBn + bd1 * dbn + bn * dd1);
-    const T corrV2 = hdt * (b2 * dBn + bd2 * dbn + bn * dd2);
-    corrB1 += hdt * rho * (v1 * dBn - un * dd1);
-    corrB2 += hdt * rho * (v2 * dBn - un * dd2);
-    corrP += hdt * rho * ((Bt1c * v1 + Bt2c * v2) * dBn - un * (Bt1c * dd1 + Bt2c * dd2));
+    // (h*: half a step times the gradients d/dm; dB_d over the zone's faces,
+    // dB'_n between the neighbours' centres)
+    const T htm = T(0.5) * tdm;
+    const T hbn = dt * (bnp - bnm) * Ar<T>::rcp(dmm + dmp + (dm + dm));
+    const T hdn = htm * (bfn - bln), hd1 = htm * (bf1 - bl1), hd2 = htm * (bf2 - bl2);
+    const T hBn = hdn + hbn;
+    const T corrU = Bnc * hbn + bn * hdn;
+    const T corrV1 = b1 * hBn + bd1 * hbn + bn * hd1;
+    const T corrV2 = b2 * hBn + bd2 * hbn + bn * hd2;
+    // (the oblique-field terms, in the gradients of u, v_t1 and v_t2, are in
+    // the eigenvectors of the characteristic mode)
+    const T e1 = v1 * hBn - un * hd1, e2 = v2 * hBn - un * hd2;
+    const T hu = TRACE ? T(0) : htm * pc[1].D;
+    const T corrB1 = rho * (e1 - Bt1c * hu);
+    const T corrB2 = rho * (e2 - Bt2c * hu);
+    const T hB = TRACE ? T(0) : htm * Bnc;
+    const T corrP = rho * (Bt1c * (e1 + hB * pc[2].D) + Bt2c * (e2 + hB * pc[3].D));
 
     // Characteristic mode: the face states traced wave by wave.  The
     // reference is the zone's parabola averaged over the fast wave's domain
@@ -653,9 +645,12 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     // LDS (slots 0..6).
     T WLc[7];
     if constexpr (TRACE) {
+        pc[0].set(W[0], edgeL[0], edgeR[0]);
+#pragma unroll
+        for (int k = 4; k < 7; ++k) pc[k].set(W[k], edgeL[k], edgeR[k]);
         Waves7<T> wz;
         wz.template init<Ar<T>>(rho, pth, gam, Bnc, Bt1c, Bt2c);
-        const T sp = rho * dt * idm;
+        const T sp = rho * tdm;
         const Frac<T> yf(tmin(T(1), wz.cf * sp)), ya(tmin(T(1), wz.ca * sp)), ys(tmin(T(1), wz.cs * sp));
         const T corr[7] = {T(0), corrU, corrV1, corrV2, corrB1, corrB2, T(0)};
         T WRc[7];
@@ -666,13 +661,13 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
 #pragma unroll
             for (int k = 0; k < 7; ++k) {
                 if (side == 0) {
-                    ref[k] = avgR(pLc[k], pDc[k], p6c[k], yf);
-                    DA[k] = ref[k] - avgR(pLc[k], pDc[k], p6c[k], ya);
-                    DS[k] = ref[k] - avgR(pLc[k], pDc[k], p6c[k], ys);
+                    ref[k] = pc[k].right(yf);
+                    DA[k] = ref[k] - pc[k].right(ya);
+                    DS[k] = ref[k] - pc[k].right(ys);
                 } else {
-                    ref[k] = avgL(pLc[k], pDc[k], p6c[k], yf);
-                    DA[k] = ref[k] - avgL(pLc[k], pDc[k], p6c[k], ya);
-                    DS[k] = ref[k] - avgL(pLc[k], pDc[k], p6c[k], ys);
+                    ref[k] = pc[k].left(yf);
+                    DA[k] = ref[k] - pc[k].left(ya);
+                    DS[k] = ref[k] - pc[k].left(ys);
                 }
             }
             T bfa, baa, bsa, bfs, bas, bss;
@@ -684,83 +679,74 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
 #pragma unroll
             for (int k = 0; k < 7; ++k) dst[k] = (phys ? ref[k] : W[k]) + corr[k];
         }
-        if (slot_ok) {
 #pragma unroll
-            for (int k = 0; k < 7; ++k) sA[k * S + tid] = WRc[k];
-        }
+        for (int k = 0; k < 7; ++k) sA[k * S + tid] = WRc[k];
     }
 
     // interface states of this zone: L at its right face (i+1/2), R at its
-    // left face (i-1/2); normal pair traced with y_n, Alfven pair with y_A
-    // right-face (L) state, kept in registers
-    T LPt, Lu, LC, Lk, Lr, Lv1, Lv2, Lb1, Lb2;
+    // left face (i-1/2); normal pair traced with y_n, Alfven pair with y_A.
+    // The normal pair's state is (perturbation total pressure P~, u, 1 / C,
+    // k / P): C = sqrt(rho (gamma p + B_t^2)) the Lagrangian sound speed, and
+    // k = (ge + 1) / (2 ge) = 1/2 + rho P / (2 C^2) with ge = C^2 / (rho P).
+    // The interface solve needs no other form of C, so one reciprocal square
+    // root per side takes the place of a square root and two reciprocals.
+    auto normal_state = [&](T r_, T u_, T p_, T q1, T q2, T g1, T g2, T Pd, T T1, T T2, T &Pt_, T &uu, T &iC, T &kP) {
+        const T TT = T1 * T1 + T2 * T2;
+        iC = Ar<T>::rsqrt(r_ * (gam * p_ + TT));
+        // p + B_d . B' + B'^2 / 2 + the oblique term, at least half the
+        // untraced total pressure
+        Pt_ = (p_ + corrP) + q1 * (g1 + T(0.5) * q1) + q2 * (g2 + T(0.5) * q2);
+        const T least = T(0.5) * (p_ + T(0.5) * TT) - Pd;
+        if (Pt_ < least) Pt_ = least;
+        kP = T(0.5) * (Ar<T>::rcp(Pt_ + Pd) + r_ * (iC * iC));
+        uu = u_ + corrU;
+    };
+    const T PdR = T(0.5) * (bf1 * bf1 + bf2 * bf2);
+    // The right-face (L) state is kept in registers, the left-face (R) state
+    // goes to the zone on the left through LDS, variable by variable (few
+    // parabolas are then live at a time).
+    T LPt, Lu, LiC, LkP, Lr, Lv1, Lv2, Lb1, Lb2;
     T LrN, LT1, LT2;      // normal-pair density and total transverse field (guess features)
-    {
-        T r_ = avgR(pLc[0], pDc[0], p6c[0], yn);
-        T u_ = avgR(pLc[1], pDc[1], p6c[1], yn);
-        T p_ = avgR(pLc[6], pDc[6], p6c[6], yn);
-        T c1_ = avgR(pLc[4], pDc[4], p6c[4], yn);
-        T c2_ = avgR(pLc[5], pDc[5], p6c[5], yn);
-        T T1 = bf1 + c1_, T2 = bf2 + c2_;
-        const T C2 = r_ * (gam * p_ + T1 * T1 + T2 * T2);
-        T C = Ar<T>::sqrt_(C2);
-        T P0 = p_ + T(0.5) * (T1 * T1 + T2 * T2);
-        T Pd = T(0.5) * (bf1 * bf1 + bf2 * bf2);
-        T Pt_ = p_ + bf1 * c1_ + bf2 * c2_ + T(0.5) * (c1_ * c1_ + c2_ * c2_) + corrP;
-        if (Pt_ + Pd < T(0.5) * P0) Pt_ = T(0.5) * P0 - Pd;
-        // k = (ge + 1) / (2 ge) with ge = C^2 / (rho P): 1/2 + rho P / (2 C^2)
-        const T kh = T(0.5) * r_ * (Pt_ + Pd) * Ar<T>::rcp(C2) + T(0.5);
-        LPt = Pt_;
-        LrN = r_;
-        LT1 = T1;
-        LT2 = T2;
-        Lu = u_ + corrU;
-        LC = C;
-        Lk = kh;
-        Lr = Ar<T>::sqrt_(avgR(pLc[0], pDc[0], p6c[0], yA));
-        Lv1 = avgR(pLc[2], pDc[2], p6c[2], yA) + corrV1;
-        Lv2 = avgR(pLc[3], pDc[3], p6c[3], yA) + corrV2;
-        Lb1 = avgR(pLc[4], pDc[4], p6c[4], yA) + corrB1;
-        Lb2 = avgR(pLc[5], pDc[5], p6c[5], yA) + corrB2;
-    }
-    // left-face (R) state, handed to the zone on the left through LDS
-    {
-        T r_ = avgL(pLc[0], pDc[0], p6c[0], yn);
-        T u_ = avgL(pLc[1], pDc[1], p6c[1], yn);
-        T p_ = avgL(pLc[6], pDc[6], p6c[6], yn);
-        T c1_ = avgL(pLc[4], pDc[4], p6c[4], yn);
-        T c2_ = avgL(pLc[5], pDc[5], p6c[5], yn);
-        T T1 = bl1 + c1_, T2 = bl2 + c2_;
-        const T C2 = r_ * (gam * p_ + T1 * T1 + T2 * T2);
-        T C = Ar<T>::sqrt_(C2);
-        T P0 = p_ + T(0.5) * (T1 * T1 + T2 * T2);
-        T Pd = T(0.5) * (bl1 * bl1 + bl2 * bl2);
-        T Pt_ = p_ + bl1 * c1_ + bl2 * c2_ + T(0.5) * (c1_ * c1_ + c2_ * c2_) + corrP;
-        if (Pt_ + Pd < T(0.5) * P0) Pt_ = T(0.5) * P0 - Pd;
-        // k = (ge + 1) / (2 ge) with ge = C^2 / (rho P): 1/2 + rho P / (2 C^2)
-        const T kh = T(0.5) * r_ * (Pt_ + Pd) * Ar<T>::rcp(C2) + T(0.5);
-        if (!TRACE && slot_ok) {
-            sA[0 * S + tid] = Pt_;
-            sA[1 * S + tid] = u_ + corrU;
-            sA[2 * S + tid] = C;
-            sA[3 * S + tid] = kh;
-            sA[4 * S + tid] = Ar<T>::sqrt_(avgL(pLc[0], pDc[0], p6c[0], yA));
-            sA[5 * S + tid] = avgL(pLc[2], pDc[2], p6c[2], yA) + corrV1;
-            sA[6 * S + tid] = avgL(pLc[3], pDc[3], p6c[3], yA) + corrV2;
-            sA[7 * S + tid] = avgL(pLc[4], pDc[4], p6c[4], yA) + corrB1;
-            sA[8 * S + tid] = avgL(pLc[5], pDc[5], p6c[5], yA) + corrB2;
-            if (GUESS != kGuessPlain) {
-                sA[16 * S + tid] = r_;
-                sA[17 * S + tid] = T1;
-                sA[18 * S + tid] = T2;
-            }
+    if constexpr (!TRACE) {
+        sA[5 * S + tid] = pc[2].left(yA) + corrV1;
+        sA[6 * S + tid] = pc[3].left(yA) + corrV2;
+        Lv1 = pc[2].right(yA) + corrV1;
+        Lv2 = pc[3].right(yA) + corrV2;
+        pc[4].set(W[4], edgeL[4], edgeR[4]);
+        sA[7 * S + tid] = pc[4].left(yA) + corrB1;
+        Lb1 = pc[4].right(yA) + corrB1;
+        const T q1l = pc[4].left(yn), q1r = pc[4].right(yn);
+        pc[5].set(W[5], edgeL[5], edgeR[5]);
+        sA[8 * S + tid] = pc[5].left(yA) + corrB2;
+        Lb2 = pc[5].right(yA) + corrB2;
+        const T q2l = pc[5].left(yn), q2r = pc[5].right(yn);
+        pc[0].set(W[0], edgeL[0], edgeR[0]);
+        sA[4 * S + tid] = Ar<T>::sqrtp(pc[0].left(yA));
+        Lr = Ar<T>::sqrtp(pc[0].right(yA));
+        const T rl = pc[0].left(yn);
+        LrN = pc[0].right(yn);
+        pc[6].set(W[6], edgeL[6], edgeR[6]);
+        const T T1 = bl1 + q1l, T2 = bl2 + q2l;
+        T Pt_, u_, iC, kP;
+        normal_state(rl, pc[1].left(yn), pc[6].left(yn), q1l, q2l, bl1, bl2, T(0.5) * (bl1 * bl1 + bl2 * bl2), T1, T2,
+                     Pt_, u_, iC, kP);
+        sA[0 * S + tid] = Pt_;
+        sA[1 * S + tid] = u_;
+        sA[2 * S + tid] = iC;
+        sA[3 * S + tid] = kP;
+        if (GUESS != kGuessPlain) {
+            sA[16 * S + tid] = rl;
+            sA[17 * S + tid] = T1;
+            sA[18 * S + tid] = T2;
         }
+        LT1 = bf1 + q1r;
+        LT2 = bf2 + q2r;
+        normal_state(LrN, pc[1].right(yn), pc[6].right(yn), q1r, q2r, bf1, bf2, PdR, LT1, LT2, LPt, Lu, LiC, LkP);
     }
     __syncthreads();
 
     // ------------------------------------------------------------ R4
     // face i+1/2 between this zone (L) and zone i+1 (R)
-    const bool face_ok = pen && i >= 3 && i <= M - 5;
     // Learned guess: faces with a strong jump are compacted per workgroup into
     // buffer B (free until the fluxes are written) and run through the network
     // 64 at a time on the matrix cores.  This pass comes before the solver's
@@ -775,13 +761,12 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
         float *Yo = reinterpret_cast<float *>(F + kCap * 16);
         int slot = 0;
         {
-            const T Pd_ = T(0.5) * (bf1 * bf1 + bf2 * bf2);
-            const T Ls[7] = {LrN, Lu, Lv1, Lv2, LT1, LT2, LPt + Pd_};
+            const T Ls[7] = {LrN, Lu, Lv1, Lv2, LT1, LT2, LPt + PdR};
             T Rs[7];
             if (face_ok) {
                 Rs[0] = sA[16 * S + sp1]; Rs[1] = sA[1 * S + sp1]; Rs[2] = sA[5 * S + sp1];
                 Rs[3] = sA[6 * S + sp1]; Rs[4] = sA[17 * S + sp1]; Rs[5] = sA[18 * S + sp1];
-                Rs[6] = sA[0 * S + sp1] + Pd_;
+                Rs[6] = sA[0 * S + sp1] + PdR;
             } else {
 #pragma unroll
                 for (int k = 0; k < 7; ++k) Rs[k] = Ls[k];
@@ -814,18 +799,6 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
         lg_have = lg_gate && slot < kCap;
         if (lg_have) lg_y = (T)Yo[slot * 2];
         __syncthreads();   // buffer B is written with the fluxes next
-    }
-    T RPt = sA[0 * S + sp1], Ru = sA[1 * S + sp1], RC = sA[2 * S + sp1], Rk = sA[3 * S + sp1];
-    T Rr = sA[4 * S + sp1], Rv1 = sA[5 * S + sp1], Rv2 = sA[6 * S + sp1];
-    T Rb1 = sA[7 * S + sp1], Rb2 = sA[8 * S + sp1];
-    T RrN = LrN, RT1 = LT1, RT2 = LT2;
-    if (GUESS == kGuessHarvest && face_ok) {
-        RrN = sA[16 * S + sp1];
-        RT1 = sA[17 * S + sp1];
-        RT2 = sA[18 * S + sp1];
-    }
-    if (!face_ok) {  // keep unused lanes trivial (no Newton iterations)
-        RPt = LPt; Ru = Lu; RC = LC; Rk = Lk; Rr = Lr; Rv1 = Lv1; Rv2 = Lv2; Rb1 = Lb1; Rb2 = Lb2;
     }
     T Pst, ust, v1s, b1s, v2s, b2s;
     const T bns = T(0.5) * (bn + bnp);
@@ -862,13 +835,20 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
             wave_add(&s_stat[34], cnt_bad);
         }
     } else {
+    const T Rr = sA[4 * S + sp1], Rv1 = sA[5 * S + sp1], Rv2 = sA[6 * S + sp1];
+    const T Rb1 = sA[7 * S + sp1], Rb2 = sA[8 * S + sp1];
     {
-        const T Pd = T(0.5) * (bf1 * bf1 + bf2 * bf2);
-        const T PL = LPt + Pd, PR = RPt + Pd;
-        const T iPL = Ar<T>::rcp(PL), iPR = Ar<T>::rcp(PR);
-        const T Pfloor = T(1e-6) * tmin(PL, PR) - Pd;
+        const T RPt = sA[0 * S + sp1], Ru = sA[1 * S + sp1], RiC = sA[2 * S + sp1], RkP = sA[3 * S + sp1];
+        const T Pd = PdR;
+        const T Pfloor = T(1e-6) * (tmin(LPt, RPt) + Pd) - Pd;
         const T tol = a.tol;
-        T P = LPt + LC * ((RPt - LPt) + RC * (Lu - Ru)) * Ar<T>::rcp(LC + RC);
+        // The velocity mismatch u*_R - u*_L is formed from differences
+        // ((u_R - u_L) + jumps / W) rather than as the difference of the two
+        // star velocities, so that a large bulk velocity does not bury it in
+        // rounding (same quantity; matters in single precision at high Mach).
+        const T duRL = Ru - Lu;
+        // linear guess P_L + C_L (P_R - P_L - C_R (u_R - u_L)) / (C_L + C_R)
+        T P = LPt + ((RPt - LPt) * RiC - duRL) * Ar<T>::rcp(LiC + RiC);
         P = tmax(P, Pfloor);
         const T P0 = P;
         // Faces with a strong jump are selected for the learned guess.  Its
@@ -879,8 +859,8 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
         bool gate = false;
         T feat[14], Pbar = T(1), cbar = T(1);
         if (GUESS == kGuessHarvest) {
-            const T Ls[7] = {LrN, Lu, Lv1, Lv2, LT1, LT2, PL};
-            const T Rs[7] = {RrN, Ru, Rv1, Rv2, RT1, RT2, PR};
+            const T Ls[7] = {LrN, Lu, Lv1, Lv2, LT1, LT2, LPt + Pd};
+            const T Rs[7] = {sA[16 * S + sp1], Ru, Rv1, Rv2, sA[17 * S + sp1], sA[18 * S + sp1], RPt + Pd};
             gate = face_ok && g >= own_lo && g < gend && guess_features(Ls, Rs, a.gate_p, a.gate_u, feat, Pbar, cbar);
             if (STATS) wave_add(&s_stat[35], gate);
         }
@@ -897,29 +877,22 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
         }
         int it = 0;
         bool conv = true;
-        // The velocity mismatch u*_R - u*_L is formed from differences
-        // ((u_R - u_L) + jumps / W) rather than as the difference of the two
-        // star velocities, so that a large bulk velocity does not bury it in
-        // rounding (same quantity; matters in single precision at high Mach).
-        const T duRL = Ru - Lu;
         // Shock impedances W_s = C_s sqrt(q_s), q_s = 1 + k_s (P - P_s) / P_s,
-        // and Z_s = 2 W_s^3 / (W_s^2 + C_s^2), carried as 1/sqrt(q_s) and
-        // 1/Z_s = (q_s + 1) / (2 C_s q_s^{3/2}): two reciprocal square roots
-        // and one reciprocal per iteration.  Then dP = -mis Z_L Z_R / (Z_L + Z_R)
-        // = -mis / (1/Z_L + 1/Z_R).
-        const T kL = Lk * iPL, kR = Rk * iPR;
-        const T iCL = Ar<T>::rcp(LC), iCR = Ar<T>::rcp(RC);
+        // and Z_s = 2 W_s^3 / (W_s^2 + C_s^2), carried as s = 1/sqrt(q_s) and
+        // g = 2/Z_s = (s + s^3) / C_s: two reciprocal square roots and one
+        // reciprocal per iteration.  Then dP = -mis Z_L Z_R / (Z_L + Z_R) =
+        // -2 mis / (g_L + g_R).
         T jL, gL, ig, dP, mis;
         for (;;) {
-            const T qL = T(1) + kL * (P - LPt), qR = T(1) + kR * (P - RPt);
-            const T sL = Ar<T>::rsqrt(qL), sR = Ar<T>::rsqrt(qR);
-            jL = (P - LPt) * sL * iCL;
-            mis = duRL + (P - RPt) * sR * iCR + jL;
-            gL = T(0.5) * (qL + T(1)) * (sL * sL) * (sL * iCL);
-            const T gR = T(0.5) * (qR + T(1)) * (sR * sR) * (sR * iCR);
-            ig = Ar<T>::rcp(gL + gR);
-            dP = -mis * ig;
-            if (tabs(dP) <= tol * (P + Pd)) break;
+            const T aL = P - LPt, aR = P - RPt;
+            const T sL = Ar<T>::rsqrt(T(1) + LkP * aL), sR = Ar<T>::rsqrt(T(1) + RkP * aR);
+            const T wL = sL * LiC, wR = sR * RiC;
+            jL = aL * wL;
+            mis = (duRL + aR * wR) + jL;
+            gL = wL + (sL * sL) * wL;
+            ig = Ar<T>::rcp(gL + (wR + (sR * sR) * wR));
+            dP = T(-2) * mis * ig;
+            if (!face_ok || tabs(dP) <= tol * (P + Pd)) break;   // (faces in the ghosts do not iterate)
             if (it >= a.max_iter) { conv = false; break; }
             P = tmax(P + dP, Pfloor);
             ++it;
@@ -938,6 +911,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
                 const unsigned long long slot = base + (unsigned long long)__popcll(bal & ((1ull << lane) - 1ull));
                 if (gate && slot < (unsigned long long)a.harvest_cap) {
                     float *rec = a.harvest + slot * mlp::kRecord;
+                    const T LC = Ar<T>::rcp(LiC), RC = Ar<T>::rcp(RiC);
                     const T u0 = (LC * Lu + RC * Ru - (RPt - LPt)) * Ar<T>::rcp(LC + RC);
 #pragma unroll
                     for (int k = 0; k < 14; ++k) rec[k] = (float)feat[k];
@@ -946,7 +920,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
                     rec[16] = (float)LPt; rec[17] = (float)RPt; rec[18] = (float)Pd;
                     rec[19] = (float)Lu;  rec[20] = (float)Ru;
                     rec[21] = (float)LC;  rec[22] = (float)RC;
-                    rec[23] = (float)Lk;  rec[24] = (float)Rk;
+                    rec[23] = (float)(LkP * (LPt + Pd));  rec[24] = (float)(RkP * (RPt + Pd));
                     rec[25] = (float)P0;  rec[26] = (float)Pst; rec[27] = (float)ust;
                 }
             }
@@ -964,10 +938,11 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     // transverse pair: linear Alfven problem, increment form from the left
     const T sig = tsgn(Bns);
     const T irs = Ar<T>::rcp(Lr + Rr);
-    v1s = Lv1 + (Rr * (Rv1 - Lv1) + sig * (Rb1 - Lb1)) * irs;
-    b1s = Lb1 + (Lr * (Rb1 - Lb1) + sig * Lr * Rr * (Rv1 - Lv1)) * irs;
-    v2s = Lv2 + (Rr * (Rv2 - Lv2) + sig * (Rb2 - Lb2)) * irs;
-    b2s = Lb2 + (Lr * (Rb2 - Lb2) + sig * Lr * Rr * (Rv2 - Lv2)) * irs;
+    const T wR = Rr * irs, wL = Lr * irs, ws = sig * irs, wx = sig * Lr * wR;
+    v1s = Lv1 + wR * (Rv1 - Lv1) + ws * (Rb1 - Lb1);
+    b1s = Lb1 + wL * (Rb1 - Lb1) + wx * (Rv1 - Lv1);
+    v2s = Lv2 + wR * (Rv2 - Lv2) + ws * (Rb2 - Lb2);
+    b2s = Lb2 + wL * (Rb2 - Lb2) + wx * (Rv2 - Lv2);
     }
     // Lagrangian fluxes in dipole + deviation flux form
     const T nn = bns * (bfn + T(0.5) * bns);
@@ -978,15 +953,13 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     const T Fb2 = ust * bf2 - Bns * v2s;
     const T Fe = ust * (Pst + nn) - Bns * (ust * bns + v1s * b1s + v2s * b2s);
     const T delR = ust * dt;
-    if (slot_ok) {
-        sB[0 * S + tid] = Fpi;
-        sB[1 * S + tid] = Fv1;
-        sB[2 * S + tid] = Fv2;
-        sB[3 * S + tid] = Fb1;
-        sB[4 * S + tid] = Fb2;
-        sB[5 * S + tid] = Fe;
-        sB[6 * S + tid] = delR;
-    }
+    sB[0 * S + tid] = Fpi;
+    sB[1 * S + tid] = Fv1;
+    sB[2 * S + tid] = Fv2;
+    sB[3 * S + tid] = Fb1;
+    sB[4 * S + tid] = Fb2;
+    sB[5 * S + tid] = Fe;
+    sB[6 * S + tid] = delR;
     __syncthreads();
 
     // ------------------------------------------------------------ R5
@@ -1008,11 +981,9 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     T QL[7];
 #pragma unroll
     for (int k = 0; k < 7; ++k) QL[k] = Qr[k] + (dC[k] - Qr[k] * dd) * idVL;
-    if (slot_ok) {
 #pragma unroll
-        for (int k = 0; k < 7; ++k) sA[k * S + tid] = QL[k];
-        sA[7 * S + tid] = dVL;
-    }
+    for (int k = 0; k < 7; ++k) sA[k * S + tid] = QL[k];
+    sA[7 * S + tid] = dVL;
     __syncthreads();
 
     // ------------------------------------------------------------ R6
@@ -1020,29 +991,22 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     T redgeR[7];
     {
         const T vm = sA[7 * S + sm1], vp = sA[7 * S + sp1], vp2 = sA[7 * S + sp2];
-        SlopeW<T> s0;
-        s0.init(vm, dVL, vp);
-        EdgeW<T> ew;
-        ew.init(vm, dVL, vp, vp2);
-        T da0[7], apv[7];
+        const Weights<T> w(vm, dVL, vp, vp2);
+        T da0[7];
 #pragma unroll
         for (int k = 0; k < 7; ++k) {
-            const T am = sA[k * S + sm1];
-            apv[k] = sA[k * S + sp1];
-            da0[k] = s0.slope(am, QL[k], apv[k]);
+            const T dmv = QL[k] - sA[k * S + sm1], dpv = sA[k * S + sp1] - QL[k];
+            da0[k] = limit_half(w.A * dpv + w.B * dmv, dmv, dpv);
+            redgeR[k] = QL[k] + w.E0 * dpv + w.E3 * da0[k];
         }
-        if (slot_ok) {
 #pragma unroll
-            for (int k = 0; k < 7; ++k) sB[k * S + tid] = da0[k];
-        }
+        for (int k = 0; k < 7; ++k) sB[k * S + tid] = da0[k];
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 7; ++k) redgeR[k] = ew.edge(QL[k], apv[k], da0[k], sB[k * S + sp1]);
+        for (int k = 0; k < 7; ++k) redgeR[k] -= w.E2 * sB[k * S + sp1];
     }
-    if (slot_ok) {
 #pragma unroll
-        for (int k = 0; k < 7; ++k) sA[(8 + k) * S + tid] = redgeR[k];
-    }
+    for (int k = 0; k < 7; ++k) sA[(8 + k) * S + tid] = redgeR[k];
     __syncthreads();
 
     // ------------------------------------------------------------ R7
@@ -1052,16 +1016,51 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
         const bool zone_ok = pen && i >= 6 && i <= M - 7;
         const bool wr = zone_ok && delR >= T(0);
         const bool wl = zone_ok && delL < T(0) && i >= 1;
-        const Frac<T> yR(delR * idVL), yL(-delL * idVL);
+        // (two registers a variable are held over the two directions, of which
+        // most waves take one: left and right edge)
+        T eL[7], eR[7];
+        {
+            T aL[7];
 #pragma unroll
-        for (int k = 0; k < 7; ++k) {
-            T aL = sA[(8 + k) * S + sm1];
-            T cL, cD, c6;
-            parabola(QL[k], aL, redgeR[k], fl, cL, cD, c6);
-            if (wr) sA[k * S + tid] = delR * avgR(cL, cD, c6, yR);
-            if (wl) sA[k * S + tid - d] = delL * avgL(cL, cD, c6, yL);
+            for (int k = 0; k < 7; ++k) aL[k] = sA[(8 + k) * S + sm1];
+            if (flat) {
+#pragma unroll
+                for (int k = 0; k < 7; ++k) {
+                    aL[k] += fl * (QL[k] - aL[k]);
+                    redgeR[k] += fl * (QL[k] - redgeR[k]);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 7; ++k) {
+                Para<T> rc;
+                rc.set(QL[k], aL[k], redgeR[k]);
+                eL[k] = rc.L;
+                eR[k] = rc.R;
+            }
+        }
+        if (wr) {
+            const Frac<T> yR(delR * idVL);
+#pragma unroll
+            for (int k = 0; k < 7; ++k) {
+                Para<T> rc;
+                rc.edges(QL[k], eL[k], eR[k]);
+                sA[k * S + tid] = delR * rc.right(yR);
+            }
+        }
+        if (wl) {
+            const Frac<T> yL(-delL * idVL);
+#pragma unroll
+            for (int k = 0; k < 7; ++k) {
+                Para<T> rc;
+                rc.edges(QL[k], eL[k], eR[k]);
+                sA[k * S + sm1] = delL * rc.left(yL);
+            }
         }
     }
+    // what the update reads from tables, requested ahead of the barrier
+    const int gc = g < 0 ? 0 : (g < N ? g : N - 1);
+    const T idx = elem(a.rdx, gc), idc = elem(a.rdc, gc);
+    const T iwq = FUSE_CFL ? elem(a.rdx_q, qq) : T(0), iwr = FUSE_CFL ? elem(a.rdx_r, r) : T(0);
     __syncthreads();
 
     // ------------------------------------------------------------ R8
@@ -1071,18 +1070,16 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     T smax = T(0);
     if (interior) {
         T out[8];
-        const T idx = Ar<T>::rcp(dxi);
         T nw[7];
 #pragma unroll
         for (int k = 0; k < 7; ++k) nw[k] = Qr[k] + (dC[k] + sA[k * S + sm1] - sA[k * S + tid]) * idx;
         T nbn = bn, nb1 = nw[4], nb2 = nw[5];
         if (a.janhunen) {
             // -v div B' source, split: n-derivative of B'_n, pre-sweep velocity
-            const T xm = elem(a.xc, ie - 1), xp = elem(a.xc, ie + 1);
-            const T divn = (bnp - bnm) * Ar<T>::rcp(xp - xm);
-            nbn -= dt * un * divn;
-            nb1 -= dt * v1 * divn;
-            nb2 -= dt * v2 * divn;
+            const T divn = dt * ((bnp - bnm) * idc);
+            nbn -= un * divn;
+            nb1 -= v1 * divn;
+            nb2 -= v2 * divn;
         }
         out[0] = nw[0];
         out[1 + kn] = nw[1];
@@ -1129,47 +1126,38 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
         if (FUSE_CFL && cfl_max && !masked) {
             // signal speed of the updated zone, for the next step's dt (the
             // maximum is reduced in FP64)
-            int ix, iy, iz;
-            if (AX == 0) { ix = g; iy = j1; iz = j2; }
-            else if (AX == 1) { iy = g; iz = j1; ix = j2; }
-            else { iz = g; ix = j1; iy = j2; }
             const T r_ = out[0];
             const T ir = Ar<T>::rcp(r_);
-            const T vx = out[1] * ir, vy = out[2] * ir, vz = out[3] * ir;
-            const T px = out[4], py = out[5], pz = out[6];
-            T p_ = (gam - T(1)) * (out[7] - T(0.5) * r_ * (vx * vx + vy * vy + vz * vz) -
-                                   T(0.5) * (px * px + py * py + pz * pz));
+            const T vn = nw[1] * ir, w1 = nw[2] * ir, w2 = nw[3] * ir;
+            T p_ = (gam - T(1)) * (nw[6] - T(0.5) * ((nw[1] * vn + nw[2] * w1 + nw[3] * w2) +
+                                                     (nbn * nbn + nb1 * nb1 + nb2 * nb2)));
             // fmax / fabs where they agree with the selects for every input
             // (a NaN p or discriminant gives the floor / zero either way);
             // the running maximum keeps its select, which passes a NaN on
             p_ = fmax_(p_, a.p_floor);
-            T Bx = px, By = py, Bz = pz;
-            if (a.has_bd) {
-                // the zone-centre background field of R1, back from the pencil frame
-                T bx, by, bz;
-                to_xyz<AX>(bdn, bd1, bd2, bx, by, bz);
-                Bx += bx; By += by; Bz += bz;
-            }
+            // total field in the pencil frame (the background of R1)
+            const T Bn = nbn + bdn, B1 = nb1 + bd1, B2 = nb2 + bd2;
             const T a2 = gam * p_ * ir;
-            const T b2 = (Bx * Bx + By * By + Bz * Bz) * ir;
+            const T b2 = (Bn * Bn + B1 * B1 + B2 * B2) * ir;
             const T s2 = a2 + b2;
             const T q4 = T(4) * a2 * ir;
-            const T wx = elem(a.dxw_x, ix), wy = elem(a.dxw_y, iy), wz = elem(a.dxw_z, iz);
+            // q is t1 for the x and z sweeps, t2 for the y sweep
+            const T i1 = AX == 1 ? iwr : iwq, i2 = AX == 1 ? iwq : iwr;
             T sp = T(0);
             {
-                T disc = fmax_(s2 * s2 - q4 * Bx * Bx, T(0));
-                T cf = Ar<T>::sqrt_(T(0.5) * (s2 + Ar<T>::sqrt_(disc)));
-                sp = tmax(sp, (fabs_(vx) + cf) * Ar<T>::rcp(wx));
+                T disc = fmax_(s2 * s2 - q4 * Bn * Bn, T(0));
+                T cf = Ar<T>::sqrtp(T(0.5) * (s2 + Ar<T>::sqrt_(disc)));
+                sp = tmax(sp, (fabs_(vn) + cf) * idx);
             }
             {
-                T disc = fmax_(s2 * s2 - q4 * By * By, T(0));
-                T cf = Ar<T>::sqrt_(T(0.5) * (s2 + Ar<T>::sqrt_(disc)));
-                sp = tmax(sp, (fabs_(vy) + cf) * Ar<T>::rcp(wy));
+                T disc = fmax_(s2 * s2 - q4 * B1 * B1, T(0));
+                T cf = Ar<T>::sqrtp(T(0.5) * (s2 + Ar<T>::sqrt_(disc)));
+                sp = tmax(sp, (fabs_(w1) + cf) * i1);
             }
             {
-                T disc = fmax_(s2 * s2 - q4 * Bz * Bz, T(0));
-                T cf = Ar<T>::sqrt_(T(0.5) * (s2 + Ar<T>::sqrt_(disc)));
-                sp = tmax(sp, (fabs_(vz) + cf) * Ar<T>::rcp(wz));
+                T disc = fmax_(s2 * s2 - q4 * B2 * B2, T(0));
+                T cf = Ar<T>::sqrtp(T(0.5) * (s2 + Ar<T>::sqrt_(disc)));
+                sp = tmax(sp, (fabs_(w2) + cf) * i2);
             }
             smax = sp;
         }
@@ -1198,19 +1186,30 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     }
 }
 
+// Waves per SIMD that the register allocation of a sweep is held to: 6 (80
+// registers) where the LDS of its workgroups (up to 512 lanes, or 768) admits
+// them.  A wave's stages wait on LDS, barriers and loads more than half of
+// their time, so resident waves decide: the ensemble sweep with 82 registers
+// (two workgroups of 512 per CU instead of three) took 59.1 ms against 45.5 ms
+// for four steps of 32 members.
+template <typename T>
+constexpr int sweep_waves(int SM, int GUESS, bool TRACE)
+{
+    if (GUESS == kGuessLearned) return 4;
+    return sizeof(T) == 4 && GUESS == kGuessPlain && !TRACE && ((SM > 0 && SM <= 512) || SM == 768) ? 6 : 1;
+}
+
 // Standalone sweep: one workgroup per tile.  The learned-guess form holds
 // the network pass next to the sweep's registers (~132 VGPRs, 3 waves per
 // SIMD); a budget of 4 waves per SIMD (128 registers, a few bytes spilled
 // in the fused form) makes it ~20 % faster (measured).
 template <int AX, typename T, bool STATS, bool FUSE_CFL, int SM, int GUESS = kGuessPlain, bool TRACE = false>
 __global__ void __launch_bounds__(SM > 0 ? SM : 1024)
-    __attribute__((amdgpu_waves_per_eu(GUESS == kGuessLearned ? 4 : 1))) sweep_kernel(const SweepArgs<T> a)
+    __attribute__((amdgpu_waves_per_eu(sweep_waves<T>(SM, GUESS, TRACE)))) sweep_kernel(const SweepArgs<T> a)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    constexpr int kSlots = (GUESS == kGuessPlain ? kSlotsA : kSlotsAGuess) + kSlotsB;
-    unsigned char *tail = smem_raw + lds_tile_bytes(kSlots, SM > 0 ? SM : a.S, (int)sizeof(T));
-    double *s_red = reinterpret_cast<double *>(tail);
-    unsigned int *s_stat = reinterpret_cast<unsigned int *>(tail + 16 * sizeof(double));
+    double *s_red = reinterpret_cast<double *>(smem_raw);
+    unsigned int *s_stat = reinterpret_cast<unsigned int *>(smem_raw + 16 * sizeof(double));
     unsigned int *s_guess = s_stat + kStatWords;
     // XCD-aware tile order: consecutive workgroups go to different XCDs
     // round-robin, so workgroups b, b+8, b+16, ... (one XCD) take consecutive
@@ -1250,7 +1249,8 @@ struct EnsembleSweepArgs {
 };
 
 template <int AX, typename T, bool STATS, bool FUSE_CFL, int SM>
-__global__ void __launch_bounds__(SM) ensemble_sweep_kernel(const EnsembleSweepArgs<T> e)
+__global__ void __launch_bounds__(SM) __attribute__((amdgpu_waves_per_eu(sweep_waves<T>(SM, kGuessPlain, false))))
+    ensemble_sweep_kernel(const EnsembleSweepArgs<T> e)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int b = blockIdx.x;
@@ -1262,9 +1262,8 @@ __global__ void __launch_bounds__(SM) ensemble_sweep_kernel(const EnsembleSweepA
         if (e.mo[mid] <= j) lo = mid; else hi = mid - 1;
     }
     const SweepArgs<T> &a = e.desc[lo];
-    unsigned char *tail = smem_raw + lds_tile_bytes(kSlotsA + kSlotsB, SM, (int)sizeof(T));
-    double *s_red = reinterpret_cast<double *>(tail);
-    unsigned int *s_stat = reinterpret_cast<unsigned int *>(tail + 16 * sizeof(double));
+    double *s_red = reinterpret_cast<double *>(smem_raw);
+    unsigned int *s_stat = reinterpret_cast<unsigned int *>(smem_raw + 16 * sizeof(double));
     const int t = j - e.mo[lo];
     int seg, tt;                                  // as in the single-run order
     if (a.seg_fast) { seg = t % a.nseg; tt = t / a.nseg; }
