@@ -32,6 +32,12 @@ struct AxisTables {
     float *rdx32 = nullptr, *rdc32 = nullptr;
 };
 
+// Shape of a march (whole pencils in chunks, see sweep_tile): P pencils per
+// workgroup, C chunks of L zones, M = L + 7 zones per chunk, LDS stride SM.
+struct March {
+    int P = 0, C = 0, L = 0, M = 0, SM = 0;
+};
+
 struct ppmlr_ctx {
     int n[3];
     int bc_lo[3], bc_hi[3];
@@ -57,6 +63,8 @@ struct ppmlr_ctx {
     int tile[3] = {0, 0, 0};
     int seg[3] = {0, 0, 0};                  // segments per pencil (0: automatic)
     int seg_order[3] = {0, 0, 0};            // tile order of segments (0: automatic, 1: adjacent, 2: bands)
+    March march[3][2];                       // march per axis and precision (FP32, FP64), for march_req
+    int march_req[3][2] = {{-1, -1}, {-1, -1}, {-1, -1}};   // pencils asked for when it was chosen (-1: not yet)
     void *d_pong = nullptr;                  // second state for segmented sweeps
     size_t pong_bytes = 0;
     int device = 0;
@@ -415,16 +423,142 @@ ppmlr_status launch_axis(ppmlr_ctx *c, const ppmlr::SweepArgs<T> &a, hipStream_t
     return fuse ? launch_sm<AX, T, false, true>(c, a, st) : launch_sm<AX, T, false, false>(c, a, st);
 }
 
+size_t march_lds(const ppmlr_ctx *c, int axis, int P, int SM, int elem)
+{
+    return ppmlr::lds_bytes(kSlotsA + kSlotsB, SM, elem, P) +
+           (c->bc_hi[axis] == PPMLR_PERIODIC ? ppmlr::lds_wrap_bytes(P, elem) : 0);
+}
+
+// The march for whole pencils along axis, with P pencils per workgroup (0:
+// chosen), or none (P = 0): the learned and harvest modes keep whole-pencil
+// tiles, and so does an explicit P that no chunk of four waves holds.
+//
+// Workgroups are held to 4 waves: one per SIMD, so that a CU fills evenly (with
+// 5 or 7 waves, two of a workgroup meet on a SIMD, and half as many workgroups
+// were resident: y sweep 431 and 409 us against 304 us with 4).  Among the
+// shapes the estimated time decides: chunks one after the other, times the
+// rounds of workgroups that the chip holds at once, times the time of a chunk,
+// which grows with the waves that share a CU (FP32, us: 4.5 + 0.155 per wave,
+// from 256x192x192 sweeps at 8, 12, 16 and 20 waves per CU: 560, 413, 336, 295
+// us).  In y and z, rows narrower than 32 B cost more (y, z sweep: 16 B 1.03,
+// 1.30; 8 B 1.35; widths other than powers of two 1.1 to 1.2).
+March march_search(const ppmlr_ctx *c, int axis, int elem, int P_req)
+{
+    March best;
+    const bool trace = c->opt.tracing == PPMLR_TRACE_CHARACTERISTIC;
+    const int N = c->n[axis], nq = axis == 0 ? c->n[1] : c->n[0];
+    const double nr = axis == 2 ? c->n[1] : c->n[2];
+    const int wps = elem == 4 ? (trace ? 4 : 5) : (trace ? 2 : 3);     // waves per SIMD (registers)
+    const double t0 = elem == 4 ? (trace ? 5.0 : 4.5) : 4.2;           // us of a chunk alone, and per wave on its CU
+    const double t1 = elem == 4 ? (trace ? 0.22 : 0.155) : (trace ? 0.78 : 0.52);
+    double best_t = 1e300;
+    for (int P = P_req > 0 ? P_req : 1; P <= (P_req > 0 ? P_req : 8); ++P) {
+        for (int C = 1; C <= N + kG; ++C) {
+            March m;
+            m.P = P;
+            m.C = C;
+            m.L = (N + kG + C - 1) / C;
+            m.M = m.L + kG;
+            if (C > 1 && m.L < 2 * kG) break;
+            if ((C - 1) * m.L >= N + kG) continue;                     // the last chunk would be empty
+            const int waves = block_threads(P, m.M) / 64, slots = P * (m.M + ppmlr::kCarry);
+            if (waves > 4) continue;
+            m.SM = slots <= 128 ? 128 : (slots + 63) / 64 * 64;
+            if (m.SM > 320) continue;
+            const size_t lds = (march_lds(c, axis, P, m.SM, elem) + 1279) / 1280 * 1280;
+            const double per_cu = std::min((int)(160 * 1024 / lds), 4 * wps / waves);
+            const double wgs = (double)((nq + P - 1) / P) * nr, rounds = wgs / (256.0 * per_cu);
+            double row = 1.0;
+            if (axis != 0) {
+                const int w = elem == 4 ? P : 2 * P;
+                row = w >= 8 ? 1.0 : (w == 4 ? (axis == 1 ? 1.03 : 1.25) : (w > 4 ? 1.12 : (w == 3 ? 1.2 : (w == 2 ? 1.35 : 1.8))));
+            }
+            // (a last round that is not full takes a round's time; with many
+            // rounds workgroups follow each other and it is less)
+            const double t = rounds <= 1.0 ? C * row * (t0 + t1 * waves * std::ceil(wgs / 256.0))
+                                           : C * row * (t0 + t1 * waves * per_cu) * (rounds + 0.5);
+            if (t < best_t - 1e-9) { best_t = t; best = m; }
+            if (C > 64) break;
+        }
+    }
+    return best;
+}
+
+const March &march_plan(ppmlr_ctx *c, int axis, int elem)
+{
+    static const March none;
+    if (c->opt.tracing == PPMLR_TRACE_TWO_FAMILY && elem == 4 && c->guess != PPMLR_GUESS_PLAIN) return none;
+    const int f = elem == 8 ? 1 : 0;
+    if (c->march_req[axis][f] != c->tile[axis]) {
+        c->march[axis][f] = march_search(c, axis, elem, c->tile[axis]);
+        c->march_req[axis][f] = c->tile[axis];
+    }
+    return c->march[axis][f];
+}
+
+template <int AX, typename T, bool FUSE, int SM, bool TRACE>
+ppmlr_status launch_march_sm(ppmlr_ctx *c, const ppmlr::SweepArgs<T> &a, hipStream_t st)
+{
+    // (counters are always collected in the kernel, and not stored without a buffer)
+    const size_t lds = march_lds(c, AX, a.P, SM, (int)sizeof(T));
+    auto kern = ppmlr::sweep_kernel<AX, T, true, FUSE, SM, ppmlr::kGuessPlain, TRACE, true>;
+    if (lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return hip_check(c, e, "hipFuncSetAttribute");
+    }
+    hipLaunchKernelGGL(kern, dim3(8 * a.tiles_per_xcd), dim3(block_threads(a.P, a.M)), lds, st, a);
+    return hip_check(c, hipGetLastError(), "sweep launch");
+}
+
+template <int AX, typename T, bool FUSE, bool TRACE>
+ppmlr_status launch_march(ppmlr_ctx *c, const ppmlr::SweepArgs<T> &a, int SM, hipStream_t st)
+{
+    switch (SM) {
+    case 128: return launch_march_sm<AX, T, FUSE, 128, TRACE>(c, a, st);
+    case 192: return launch_march_sm<AX, T, FUSE, 192, TRACE>(c, a, st);
+    case 256: return launch_march_sm<AX, T, FUSE, 256, TRACE>(c, a, st);
+    case 320: return launch_march_sm<AX, T, FUSE, 320, TRACE>(c, a, st);
+    default: return fail(c, PPMLR_EINVAL, "no march of this stride");
+    }
+}
+
+template <int AX, typename T>
+ppmlr_status march_axis(ppmlr_ctx *c, const ppmlr::SweepArgs<T> &a, int SM, hipStream_t st, bool fuse)
+{
+    if (c->opt.tracing == PPMLR_TRACE_CHARACTERISTIC) {
+        if (c->guess != PPMLR_GUESS_PLAIN)
+            return fail(c, PPMLR_EINVAL, "the characteristic mode takes the plain interface solve");
+        return fuse ? launch_march<AX, T, true, true>(c, a, SM, st) : launch_march<AX, T, false, true>(c, a, SM, st);
+    }
+    return fuse ? launch_march<AX, T, true, false>(c, a, SM, st) : launch_march<AX, T, false, false>(c, a, SM, st);
+}
+
 template <typename T>
 ppmlr_status sweep_typed(ppmlr_ctx *c, const T *in, T *u, hipStream_t st, double dt, const double *dt_dev, int axis,
                          bool fuse)
 {
+    const int nseg = seg_count(c, axis, (int)sizeof(T));
+    if (nseg == 1) {
+        const March &m = march_plan(c, axis, (int)sizeof(T));
+        if (m.P > 0) {
+            ppmlr::SweepArgs<T> a;
+            fill_args(c, a, in, u, axis, dt, dt_dev, m.P, 1);
+            a.L = m.L;
+            a.M = m.M;
+            a.nchunk = m.C;
+            a.S = m.P * m.M;
+            a.inv_div = 1.0f / (float)(axis == 0 ? m.M : m.P);
+            if (axis == 0) return march_axis<0, T>(c, a, m.SM, st, fuse);
+            if (axis == 1) return march_axis<1, T>(c, a, m.SM, st, fuse);
+            return march_axis<2, T>(c, a, m.SM, st, fuse);
+        }
+    }
     const int P = pick_tile(c, axis, (int)sizeof(T));
     const int M = tile_M(c, axis, (int)sizeof(T));
     if (block_threads(P, M) > 1024 || ppmlr::lds_bytes(kSlotsA + kSlotsB, P * M, (int)sizeof(T), P) > 160 * 1024)
         return fail(c, PPMLR_EINVAL, "tile does not fit one workgroup");
     ppmlr::SweepArgs<T> a;
-    fill_args(c, a, in, u, axis, dt, dt_dev, P, seg_count(c, axis, (int)sizeof(T)));
+    fill_args(c, a, in, u, axis, dt, dt_dev, P, nseg);
     const bool stats = c->opt.collect_stats != 0;
     if (axis == 0) return launch_axis<0, T>(c, a, st, stats, fuse);
     if (axis == 1) return launch_axis<1, T>(c, a, st, stats, fuse);
@@ -1432,14 +1566,17 @@ ppmlr_status ppmlr_autotune(ppmlr_ctx *c, const ppmlr_state *s, int reps, int ti
             const int M = L + 2 * kG;
             c->seg[axis] = nseg;
             c->seg_order[axis] = nseg == 1 ? 0 : order;
-            for (int P = 1; P <= 32 && !e; ++P) {
-                const int thr = block_threads(P, M);
+            // P = 0: the automatic shape, once (with one segment)
+            for (int P = nseg == 1 ? 0 : 1; P <= 32 && !e; ++P) {
+                const int thr = block_threads(std::max(P, 1), M);
                 if (thr > 1024) break;
                 if (stride_for(thr, (int)elem) < 0) continue;
                 c->tile[axis] = P;
+                if (P == 0) c->seg[axis] = 0;
+                else c->seg[axis] = nseg;
                 float ms = 0.0f;
                 e = time_shape(axis, reps, ms);
-                if (!e) shapes.push_back({ms, P, nseg, c->seg_order[axis]});
+                if (!e) shapes.push_back({ms, P, c->seg[axis], c->seg_order[axis]});
             }
         }
         // the three fastest again, with three times the repetitions
@@ -1457,7 +1594,7 @@ ppmlr_status ppmlr_autotune(ppmlr_ctx *c, const ppmlr_state *s, int reps, int ti
         c->tile[axis] = best.P;
         c->seg[axis] = best.nseg;
         c->seg_order[axis] = best.order;
-        if (tiles) tiles[axis] = best.P;
+        if (tiles) tiles[axis] = pick_tile(c, axis, (int)elem);
     }
     c->profiling = prof;
     c->guess = guess;

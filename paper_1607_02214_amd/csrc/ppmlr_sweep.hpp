@@ -64,6 +64,9 @@ __host__ __device__ constexpr size_t lds_bytes(int slots, int S, int elem, int P
 {
     return lds_front(P, elem) + ((size_t)slots * (size_t)S * (size_t)elem + 15) / 16 * 16 + lds_guard(P, elem);
 }
+// A march keeps the old first kG zones of a periodic axis behind the rows.
+__host__ __device__ constexpr size_t lds_wrap_bytes(int P, int elem) { return (size_t)8 * kG * P * elem; }
+constexpr int kCarry = 6;       // slots of every row that a march keeps for each pencil
 
 enum { kPeriodic = 0, kOutflow = 1, kInflow = 2 };
 
@@ -115,16 +118,18 @@ template <> struct Ar<float> {
 template <typename T> __device__ inline T tmin(T a, T b) { return a < b ? a : b; }
 template <typename T> __device__ inline T tmax(T a, T b) { return a > b ? a : b; }
 template <typename T> __device__ inline T tabs(T a) { return a < T(0) ? -a : a; }
-// Element i of an array at a uniform base address, addressed by a 32-bit byte
-// offset (every array the sweep reads is below 4 GiB), so that the load or
-// store takes the scalar-base + vector-offset form.
-template <typename T> __device__ inline T &elem(T *base, unsigned int i)
+// Element i of a global array at a uniform base address, addressed by a 32-bit
+// byte offset (every array the sweep reads is below 4 GiB), so that the load
+// or store takes the scalar-base + vector-offset form.  The address space is
+// stated, as a base read from a descriptor in memory does not show it.
+template <typename T> using global_t = __attribute__((address_space(1))) T;
+template <typename T> __device__ inline T load(const T *base, unsigned int i)
 {
-    return *reinterpret_cast<T *>(reinterpret_cast<char *>(base) + i * (unsigned int)sizeof(T));
+    return *(const global_t<T> *)((const global_t<char> *)(const char *)base + i * (unsigned int)sizeof(T));
 }
-template <typename T> __device__ inline const T &elem(const T *base, unsigned int i)
+template <typename T> __device__ inline void store(T *base, unsigned int i, T v)
 {
-    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + i * (unsigned int)sizeof(T));
+    *(global_t<T> *)((global_t<char> *)(char *)base + i * (unsigned int)sizeof(T)) = v;
 }
 // IEEE min / |x| / copysign in the type's own precision (the unsuffixed
 // builtins are the double versions and would convert FP32 operands)
@@ -144,6 +149,7 @@ struct SweepArgs {
     long long vol;              // zones per variable
     int N, M;                   // zones along the pencil; zones of one tile's segment, L + 2G
     int L, nseg;                // interior zones per segment (the last may be shorter), segments per pencil
+    int nchunk;                 // march: chunks per pencil of L zones each (the left ghosts included)
     int Mext;                   // N + 2G: extent of the geometry tables along the pencil
     int P;                      // pencils per workgroup
     int S;                      // LDS slots = P * M
@@ -195,7 +201,8 @@ template <int AX, typename T>
 struct PencilField {
     T c1, c2, ct2, mt3;            // transverse position, its square, 3 (m.r) of the transverse part
     T en, e1, e2, mn, m1, m2;      // uniform field, dipole direction
-    __device__ inline PencilField(const SweepArgs<T> &a, T c1_, T c2_) : c1(c1_), c2(c2_)
+    template <typename A>
+    __device__ inline PencilField(const A &a, T c1_, T c2_) : c1(c1_), c2(c2_)
     {
         const T e[3] = {a.bext_x, a.bext_y, a.bext_z}, m[3] = {a.dir_x, a.dir_y, a.dir_z};
         en = e[AX]; e1 = e[(AX + 1) % 3]; e2 = e[(AX + 2) % 3];
@@ -203,7 +210,8 @@ struct PencilField {
         ct2 = c1 * c1 + c2 * c2;
         mt3 = T(3) * (m1 * c1 + m2 * c2);
     }
-    __device__ inline void at(const SweepArgs<T> &a, T n, T &bn, T &b1, T &b2) const
+    template <typename A>
+    __device__ inline void at(const A &a, T n, T &bn, T &b1, T &b2) const
     {
         bn = en;
         b1 = e1;
@@ -384,8 +392,20 @@ __device__ inline bool guess_features(const T *L, const T *R, T gate_p, T gate_u
 // zones).  dt: the time step; cfl_max: target
 // of the fused signal-speed maximum (FUSE_CFL); stat_slot: which copy of the
 // counters this workgroup adds to.
-// SM: LDS stride per stored value (a power of two >= P*M, so that every LDS
-// access uses an immediate offset), or 0 for a runtime stride P*M.
+// SM: LDS stride per stored value (so that every LDS access uses an immediate
+// offset), or 0 for a runtime stride, the workgroup size.
+// MARCH: the workgroup takes its P pencils whole, in a.nchunk chunks of L zones
+// plus 7 ghosts on the right, one after the other and in place.  What a chunk's
+// first zone needs of the zones on its left (primitives, edges, fluxes,
+// Lagrangian contents, remap edges and fluxes) the chunk before left in LDS,
+// so each zone is computed once but for the 7, and bit for bit as in a whole
+// pencil.  A tile of a whole 192-zone pencil needs 13 waves in step and leaves
+// one workgroup on a CU; chunks of 25 zones of 8 pencils are 4 waves, five
+// workgroups a CU, rows of 32 B in y and z.  256x192x192, one sweep, x / y / z:
+// FP32 456 / 515 / 553 us as whole-pencil tiles, 306 / 295 / 291 us as marches;
+// FP64 1394 / 1167 / 1266 us against 745 / 665 / 700 us.  Requesting the next
+// chunk's zones ahead was measured and is not done (315 / 302 / 299 us): with
+// 20 waves on a CU the loads are covered, and the registers are not there.
 // GUESS: initial guess of the normal-pair Newton iteration: the plain linear
 // guess, the learned (MLP) guess on selected faces, or the plain guess with
 // the selected faces' states and solutions recorded for training.  s_guess:
@@ -395,8 +415,9 @@ __device__ inline bool guess_features(const T *L, const T *R, T gate_p, T gate_u
 // at a pressure jump at rest would let rounding noise decide flattening.
 constexpr double kCompMin = 1e-5;
 
-template <int AX, typename T, bool STATS, bool FUSE_CFL, int SM, int GUESS = kGuessPlain, bool TRACE = false>
-__device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, const int r, const int seg, const T dt,
+template <int AX, typename T, bool STATS, bool FUSE_CFL, int SM, int GUESS = kGuessPlain, bool TRACE = false,
+          bool MARCH = false, typename ARGS>
+__device__ __forceinline__ void sweep_tile(const ARGS &args, const int tq, const int r, const int seg, const T dt,
                                            unsigned long long *cfl_max, const int stat_slot,
                                            unsigned char *smem_raw, double *s_red, unsigned int *s_stat,
                                            unsigned int *s_guess = nullptr)
@@ -405,13 +426,28 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
                   "learned / harvest modes are FP32 sweeps with a compile-time stride and counters");
     static_assert(!TRACE || GUESS == kGuessPlain, "the characteristic mode takes the plain interface solve");
     const int S = SM > 0 ? SM : (int)blockDim.x;          // LDS stride
+    if (STATS && threadIdx.x < kStatWords) s_stat[threadIdx.x] = 0u;   // ordered by the first barrier
+    constexpr int kn = AX, k1 = (AX + 1) % 3, k2 = (AX + 2) % 3;
+    T cq;                                                 // the pencil's coordinate along q
+    // signal-speed maximum in the sweep's precision: a maximum selects one
+    // value, so reducing in FP32 and converting the result gives the FP64
+    // maximum of the converted values exactly
+    T smax = T(0);
+    const int nch = MARCH ? args.nchunk : 1;
+    for (int ch = 0; ch < nch; ++ch) {
+    // A march's arguments and lane indices are formed anew in every chunk:
+    // held over the loop they take more scalar and vector registers than there
+    // are, and are spilled (134 lane reads per chunk, measured).
+    const ARGS *ap = &args;
+    int tid = threadIdx.x;
+    if (MARCH) {
+        asm volatile("" : "+s"(ap));
+        asm volatile("" : "+v"(tid));
+    }
+    const ARGS &a = *ap;
     T *sA = reinterpret_cast<T *>(smem_raw + lds_front(a.P, (int)sizeof(T)));
     T *sB = sA + (GUESS == kGuessPlain ? kSlotsA : kSlotsAGuess) * S;
     const int q0 = tq * a.P;
-
-    const int tid = threadIdx.x;
-    if (STATS && tid < kStatWords) s_stat[tid] = 0u;   // ordered by the first barrier
-    if (GUESS == kGuessLearned && tid == 0) s_guess[0] = 0u;
     const int Suse = a.S, M = a.M, N = a.N, P = a.P;
     const bool slot_ok = tid < Suse;
     int p, i;
@@ -426,68 +462,95 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     int d = (AX == 0) ? 1 : P;
     if (AX == 0) asm("" : "+s"(d));
     const int q = q0 + p;
-    const int g0 = seg * a.L;                             // first interior zone of the segment
-    const int ie = g0 + i;                                // index into the extended tables
-    const int Mext = a.Mext;
-    const bool pen = slot_ok && q < a.nq && ie < Mext;
-    const int g = ie - kG;                                // zone index along the pencil
-    const int gend = min(g0 + a.L, N);                    // end of the segment's interior
-    const bool interior = pen && g >= g0 && g < gend;
-    const bool face_ok = pen && i >= 3 && i <= M - 5;     // faces whose two states are complete
-    // slots of the zones i-2 .. i+2 (see the LDS layout for the ends of a tile)
-    const int sm1 = tid - d, sp1 = tid + d, sm2 = sm1 - d, sp2 = sp1 + d;
-    // faces owned by this segment (counted and recorded once per pencil):
-    // -1/2 .. N-1/2 over all segments
-    const int own_lo = seg == 0 ? -1 : g0;
+    const int Mext = a.Mext, L = a.L;
+    // This lane's LDS slot and those of the zones i+1, i+2 (see the LDS layout
+    // for the ends of a tile).  A march keeps kCarry slots of every row before
+    // each pencil's zones, what a chunk's last zone leaves to the next chunk: three
+    // sets, two of each in turn.
+    const int t = tid + (MARCH ? (AX == 0 ? kCarry * (p + 1) : kCarry * P) : 0);
+    const int sp1 = t + d, sp2 = sp1 + d;
+    T *sP = sB + kSlotsB * S;                             // march on a periodic axis: old zones 0 .. 6
+    const bool wrap = MARCH && a.bc_hi == kPeriodic;
     const T gam = a.gamma;
 
-    // transverse coordinates of the pencil
     const int qq = q < a.nq ? q : a.nq - 1;
-    int j1, j2;
-    T c1, c2;
     // q is t1 for the x and z sweeps, t2 for the y sweep
-    if (AX == 1) { j1 = r; j2 = qq; c1 = elem(a.xc_r, r); c2 = elem(a.xc_q, qq); }
-    else { j1 = qq; j2 = r; c1 = elem(a.xc_q, qq); c2 = elem(a.xc_r, r); }
+    const int j1 = AX == 1 ? r : qq, j2 = AX == 1 ? qq : r;
     (void)j1; (void)j2;
     // 32-bit element offsets within one variable (the host keeps a variable
     // below 4 GiB); each variable's base pointer is uniform
     const unsigned int base = (unsigned int)(qq * (int)a.stride_q + r * (int)a.stride_r);
 
     // ------------------------------------------------------------ R1
+    const bool first = !MARCH || ch == 0;                 // ghosts on the left
+    const int ie = (MARCH ? ch : seg) * L + i;            // index into the extended tables
+    if (first) cq = load(a.xc_q, qq);
     const int ic = ie < Mext ? ie : Mext - 1;
-    const T dxi = elem(a.dx, ic);
-    const T xci = elem(a.xc, ic);
-    const T xfr = elem(a.xf, ic + 1);
-    int src = g;
-    bool inflow_zone = false;
-    if (g < 0) {
-        if (a.bc_lo == kPeriodic) { src = g % N; if (src < 0) src += N; }
-        else { src = 0; inflow_zone = a.bc_lo != kOutflow; }
-    } else if (g >= N) {
-        if (a.bc_hi == kPeriodic) src = g % N;
-        else { src = N - 1; inflow_zone = a.bc_hi != kOutflow; }
+    const T dxi = load(a.dx, ic);
+    const T xci = load(a.xc, ic);
+    const T xfr = load(a.xf, ic + 1);
+    int src = ie - kG;
+    if (src < 0) {
+        if (a.bc_lo == kPeriodic) { src = src % N; if (src < 0) src += N; }
+        else src = 0;
+    } else if (src >= N) {
+        src = a.bc_hi == kPeriodic ? src % N : N - 1;
     }
+    // conserved state in pencil frame: rho, mn, m1, m2, bn, b1, b2, E (every
+    // lane loads a zone of the pencil, inflow ghosts are replaced below)
+    T Q[8];
+    {
+        const unsigned int o = base + (unsigned int)(src * (int)a.stride_n);
+        Q[0] = load(a.vin[0], o);
+        Q[1] = load(a.vin[1 + kn], o);
+        Q[2] = load(a.vin[1 + k1], o);
+        Q[3] = load(a.vin[1 + k2], o);
+        Q[4] = load(a.vin[4 + kn], o);
+        Q[5] = load(a.vin[4 + k1], o);
+        Q[6] = load(a.vin[4 + k2], o);
+        Q[7] = load(a.vin[7], o);
+    }
+    // transverse coordinates of the pencil
+    const T cr = load(a.xc_r, r);
+    const T c1 = AX == 1 ? cr : cq, c2 = AX == 1 ? cq : cr;
+    const int g = ie - kG;                                // zone index along the pencil
+    const bool pen = slot_ok && q < a.nq && ie < Mext;
+    // zones that this tile or chunk updates, and the faces it owns (counted
+    // and recorded once per pencil): -1/2 .. N-1/2 over all of them
+    const int glo = MARCH ? (ch == 0 ? 0 : ch * L - kG) : seg * L;
+    const int gend = min(MARCH ? (ch + 1) * L - kG : glo + L, N);
+    const int own_lo = (MARCH ? ch == 0 : seg == 0) ? -1 : glo;
+    const bool interior = pen && g >= glo && g < gend;
+    const bool face_ok = pen && i >= (first ? 3 : 0) && i <= M - 5;   // faces whose two states are complete
+    if (GUESS == kGuessLearned && tid == 0) s_guess[0] = 0u;
+    // lanes past the tile do not write in a march: the slots behind are taken
+    const bool keeps = !MARCH || slot_ok;
+    // March: a chunk's first zone takes what it needs of the zones on its left
+    // from the slots where the chunk before left them, so that no ghost zone
+    // is computed again there.
+    const bool carried = MARCH && ch > 0 && i == 0;
+    const bool leaves = MARCH && slot_ok && i == L - 1;   // the next chunk's left neighbour
+    auto left = [&](int set) -> int { return t - d - (carried ? d * (2 * set + (ch & 1)) : 0); };
+    auto cslot = [&](int set) -> int { return t - d * (L + 2 * set + ((ch + 1) & 1)); };
+    if (wrap && nch > 1) {
+        // the zones behind a periodic end are the first ones, which chunk 0 updates
+        if (ch == 0 && slot_ok && g >= 0 && g < kG) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) sP[(k * kG + g) * P + p] = Q[k];
+        }
+        if (ch > 0 && slot_ok && g >= N) {
+            const int z = min(g - N, kG - 1);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) Q[k] = sP[(k * kG + z) * P + p];
+        }
+    }
+    const bool inflow_zone = (g < 0 && a.bc_lo == kInflow) || (g >= N && a.bc_hi == kInflow);
     // centre and right-face background field (pencil frame)
     T bdn = 0, bd1 = 0, bd2 = 0, bfn = 0, bf1 = 0, bf2 = 0;
     if (a.has_bd) {
         const PencilField<AX, T> fld(a, c1, c2);
         fld.at(a, xci, bdn, bd1, bd2);
         fld.at(a, xfr, bfn, bf1, bf2);
-    }
-    // conserved state in pencil frame: rho, mn, m1, m2, bn, b1, b2, E
-    T Q[8];
-    constexpr int kn = AX, k1 = (AX + 1) % 3, k2 = (AX + 2) % 3;
-    {
-        // every lane loads a zone of the pencil (inflow ghosts are replaced below)
-        const unsigned int o = base + (unsigned int)(src * (int)a.stride_n);
-        Q[0] = elem(a.vin[0], o);
-        Q[1] = elem(a.vin[1 + kn], o);
-        Q[2] = elem(a.vin[1 + k1], o);
-        Q[3] = elem(a.vin[1 + k2], o);
-        Q[4] = elem(a.vin[4 + kn], o);
-        Q[5] = elem(a.vin[4 + k1], o);
-        Q[6] = elem(a.vin[4 + k2], o);
-        Q[7] = elem(a.vin[7], o);
     }
     if (inflow_zone) {
         // inflow ghost: primitive inflow state with B' = B_in - B_d(centre)
@@ -526,18 +589,36 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     const bool cnt_bad = interior && (!(rho > T(0)) || !__builtin_isfinite(rho) || !__builtin_isfinite(Q[7]));
     // primitive set used for reconstruction: rho, u, v1, v2, b1, b2, p
     const T W[7] = {rho, un, v1, v2, b1, b2, pth};
+    if (keeps) {
 #pragma unroll
-    for (int k = 0; k < 7; ++k) sA[k * S + tid] = W[k];
-    sA[7 * S + tid] = dm;
-    sA[8 * S + tid] = bn;
-    sA[9 * S + tid] = Pt;
-    sA[10 * S + tid] = Pa;
-    sA[11 * S + tid] = bfn;
-    sA[12 * S + tid] = bf1;
-    sA[13 * S + tid] = bf2;
+        for (int k = 0; k < 7; ++k) sA[k * S + t] = W[k];
+        sA[7 * S + t] = dm;
+        sA[8 * S + t] = bn;
+        sA[9 * S + t] = Pt;
+        sA[10 * S + t] = Pa;
+        sA[11 * S + t] = bfn;
+        sA[12 * S + t] = bf1;
+        sA[13 * S + t] = bf2;
+    }
+    if (leaves) {
+        const int w = cslot(0);
+#pragma unroll
+        for (int k = 0; k < 7; ++k) sA[k * S + w] = W[k];
+        sA[7 * S + w] = dm;
+        sA[8 * S + w] = bn;
+        sA[9 * S + w] = Pt;
+        sA[10 * S + w] = Pa;
+        sA[11 * S + w] = bfn;
+        sA[12 * S + w] = bf1;
+        sA[13 * S + w] = bf2;
+    }
+    if (MARCH && slot_ok && i == L - 2) sA[15 * S + cslot(0) + d] = Pt;
     __syncthreads();
 
     // ------------------------------------------------------------ R2
+    const int sm1 = left(0);
+    // P~ of the zone i-2 (row 9; carried in row 15)
+    const int sm2 = !MARCH || ch == 0 || i > 1 ? t - 2 * d : (i == 1 ? t - d * (2 + (ch & 1)) : sm1 + 6 * S);
     const T dmm = sA[7 * S + sm1], dmp = sA[7 * S + sp1], dmp2 = sA[7 * S + sp2];
     const T bnm = sA[8 * S + sm1], bnp = sA[8 * S + sp1];
     const T bln = sA[11 * S + sm1], bl1 = sA[12 * S + sm1], bl2 = sA[13 * S + sm1];  // left face
@@ -572,15 +653,25 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
                 else ftil = T(1);
             }
         }
+        if (keeps) {
 #pragma unroll
-        for (int k = 0; k < 7; ++k) sB[k * S + tid] = da0[k];
-        sB[7 * S + tid] = ftil;
+            for (int k = 0; k < 7; ++k) sB[k * S + t] = da0[k];
+            sB[7 * S + t] = ftil;
+        }
+        if (leaves) sB[7 * S + cslot(0)] = ftil;
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 7; ++k) edgeR[k] -= w.E2 * sB[k * S + sp1];
     }
+    if (keeps) {
 #pragma unroll
-    for (int k = 0; k < 7; ++k) sA[(9 + k) * S + tid] = edgeR[k];
+        for (int k = 0; k < 7; ++k) sA[(9 + k) * S + t] = edgeR[k];
+    }
+    if (leaves) {
+        const int w = cslot(1);
+#pragma unroll
+        for (int k = 0; k < 7; ++k) sA[(9 + k) * S + w] = edgeR[k];
+    }
     __syncthreads();
 
     // ------------------------------------------------------------ R3
@@ -593,8 +684,11 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     // wave without one skips it (x + 0 (a - x) = x).
     const bool flat = a.flatten && __any(fl != T(0));
     T edgeL[7];
+    {
+        const int e = left(1);
 #pragma unroll
-    for (int k = 0; k < 7; ++k) edgeL[k] = sA[(9 + k) * S + sm1];
+        for (int k = 0; k < 7; ++k) edgeL[k] = sA[(9 + k) * S + e];
+    }
     if (flat) {
 #pragma unroll
         for (int k = 0; k < 7; ++k) {
@@ -679,8 +773,10 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
 #pragma unroll
             for (int k = 0; k < 7; ++k) dst[k] = (phys ? ref[k] : W[k]) + corr[k];
         }
+        if (keeps) {
 #pragma unroll
-        for (int k = 0; k < 7; ++k) sA[k * S + tid] = WRc[k];
+            for (int k = 0; k < 7; ++k) sA[k * S + t] = WRc[k];
+        }
     }
 
     // interface states of this zone: L at its right face (i+1/2), R at its
@@ -708,20 +804,22 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     T LPt, Lu, LiC, LkP, Lr, Lv1, Lv2, Lb1, Lb2;
     T LrN, LT1, LT2;      // normal-pair density and total transverse field (guess features)
     if constexpr (!TRACE) {
-        sA[5 * S + tid] = pc[2].left(yA) + corrV1;
-        sA[6 * S + tid] = pc[3].left(yA) + corrV2;
+        if (keeps) {
+            sA[5 * S + t] = pc[2].left(yA) + corrV1;
+            sA[6 * S + t] = pc[3].left(yA) + corrV2;
+        }
         Lv1 = pc[2].right(yA) + corrV1;
         Lv2 = pc[3].right(yA) + corrV2;
         pc[4].set(W[4], edgeL[4], edgeR[4]);
-        sA[7 * S + tid] = pc[4].left(yA) + corrB1;
+        if (keeps) sA[7 * S + t] = pc[4].left(yA) + corrB1;
         Lb1 = pc[4].right(yA) + corrB1;
         const T q1l = pc[4].left(yn), q1r = pc[4].right(yn);
         pc[5].set(W[5], edgeL[5], edgeR[5]);
-        sA[8 * S + tid] = pc[5].left(yA) + corrB2;
+        if (keeps) sA[8 * S + t] = pc[5].left(yA) + corrB2;
         Lb2 = pc[5].right(yA) + corrB2;
         const T q2l = pc[5].left(yn), q2r = pc[5].right(yn);
         pc[0].set(W[0], edgeL[0], edgeR[0]);
-        sA[4 * S + tid] = Ar<T>::sqrtp(pc[0].left(yA));
+        if (keeps) sA[4 * S + t] = Ar<T>::sqrtp(pc[0].left(yA));
         Lr = Ar<T>::sqrtp(pc[0].right(yA));
         const T rl = pc[0].left(yn);
         LrN = pc[0].right(yn);
@@ -730,14 +828,16 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
         T Pt_, u_, iC, kP;
         normal_state(rl, pc[1].left(yn), pc[6].left(yn), q1l, q2l, bl1, bl2, T(0.5) * (bl1 * bl1 + bl2 * bl2), T1, T2,
                      Pt_, u_, iC, kP);
-        sA[0 * S + tid] = Pt_;
-        sA[1 * S + tid] = u_;
-        sA[2 * S + tid] = iC;
-        sA[3 * S + tid] = kP;
-        if (GUESS != kGuessPlain) {
-            sA[16 * S + tid] = rl;
-            sA[17 * S + tid] = T1;
-            sA[18 * S + tid] = T2;
+        if (keeps) {
+            sA[0 * S + t] = Pt_;
+            sA[1 * S + t] = u_;
+            sA[2 * S + t] = iC;
+            sA[3 * S + t] = kP;
+            if (GUESS != kGuessPlain) {
+                sA[16 * S + t] = rl;
+                sA[17 * S + t] = T1;
+                sA[18 * S + t] = T2;
+            }
         }
         LT1 = bf1 + q1r;
         LT2 = bf2 + q2r;
@@ -953,26 +1053,39 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     const T Fb2 = ust * bf2 - Bns * v2s;
     const T Fe = ust * (Pst + nn) - Bns * (ust * bns + v1s * b1s + v2s * b2s);
     const T delR = ust * dt;
-    sB[0 * S + tid] = Fpi;
-    sB[1 * S + tid] = Fv1;
-    sB[2 * S + tid] = Fv2;
-    sB[3 * S + tid] = Fb1;
-    sB[4 * S + tid] = Fb2;
-    sB[5 * S + tid] = Fe;
-    sB[6 * S + tid] = delR;
+    if (keeps) {
+        sB[0 * S + t] = Fpi;
+        sB[1 * S + t] = Fv1;
+        sB[2 * S + t] = Fv2;
+        sB[3 * S + t] = Fb1;
+        sB[4 * S + t] = Fb2;
+        sB[5 * S + t] = Fe;
+        sB[6 * S + t] = delR;
+    }
+    if (leaves) {
+        const int w = cslot(0);
+        sB[0 * S + w] = Fpi;
+        sB[1 * S + w] = Fv1;
+        sB[2 * S + w] = Fv2;
+        sB[3 * S + w] = Fb1;
+        sB[4 * S + w] = Fb2;
+        sB[5 * S + w] = Fe;
+        sB[6 * S + w] = delR;
+    }
     __syncthreads();
 
     // ------------------------------------------------------------ R5
     // Lagrangian update of the zone contents (faces i-1/2, i+1/2)
-    const T delL = sB[6 * S + sm1];
+    const int fm1 = left(0);
+    const T delL = sB[6 * S + fm1];
     T dC[7];
     dC[0] = T(0);
-    dC[1] = -dt * (Fpi - sB[0 * S + sm1]);
-    dC[2] = -dt * (Fv1 - sB[1 * S + sm1]);
-    dC[3] = -dt * (Fv2 - sB[2 * S + sm1]);
-    dC[4] = -dt * (Fb1 - sB[3 * S + sm1]);
-    dC[5] = -dt * (Fb2 - sB[4 * S + sm1]);
-    dC[6] = -dt * (Fe - sB[5 * S + sm1]);
+    dC[1] = -dt * (Fpi - sB[0 * S + fm1]);
+    dC[2] = -dt * (Fv1 - sB[1 * S + fm1]);
+    dC[3] = -dt * (Fv2 - sB[2 * S + fm1]);
+    dC[4] = -dt * (Fb1 - sB[3 * S + fm1]);
+    dC[5] = -dt * (Fb2 - sB[4 * S + fm1]);
+    dC[6] = -dt * (Fe - sB[5 * S + fm1]);
     // remapped quantities per volume: rho, mn, m1, m2, b1, b2, E
     const T Qr[7] = {Q[0], Q[1], Q[2], Q[3], Q[5], Q[6], Q[7]};
     const T dd = delR - delL;
@@ -981,39 +1094,57 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
     T QL[7];
 #pragma unroll
     for (int k = 0; k < 7; ++k) QL[k] = Qr[k] + (dC[k] - Qr[k] * dd) * idVL;
+    if (keeps) {
 #pragma unroll
-    for (int k = 0; k < 7; ++k) sA[k * S + tid] = QL[k];
-    sA[7 * S + tid] = dVL;
+        for (int k = 0; k < 7; ++k) sA[k * S + t] = QL[k];
+        sA[7 * S + t] = dVL;
+    }
+    if (leaves) {
+        const int w = cslot(1);
+#pragma unroll
+        for (int k = 0; k < 7; ++k) sA[k * S + w] = QL[k];
+        sA[7 * S + w] = dVL;
+    }
     __syncthreads();
 
     // ------------------------------------------------------------ R6
     // slopes shared through buffer B as in R2; edges to buffer A, slots 8..14
     T redgeR[7];
     {
-        const T vm = sA[7 * S + sm1], vp = sA[7 * S + sp1], vp2 = sA[7 * S + sp2];
+        const int qm1 = left(1);
+        const T vm = sA[7 * S + qm1], vp = sA[7 * S + sp1], vp2 = sA[7 * S + sp2];
         const Weights<T> w(vm, dVL, vp, vp2);
         T da0[7];
 #pragma unroll
         for (int k = 0; k < 7; ++k) {
-            const T dmv = QL[k] - sA[k * S + sm1], dpv = sA[k * S + sp1] - QL[k];
+            const T dmv = QL[k] - sA[k * S + qm1], dpv = sA[k * S + sp1] - QL[k];
             da0[k] = limit_half(w.A * dpv + w.B * dmv, dmv, dpv);
             redgeR[k] = QL[k] + w.E0 * dpv + w.E3 * da0[k];
         }
+        if (keeps) {
 #pragma unroll
-        for (int k = 0; k < 7; ++k) sB[k * S + tid] = da0[k];
+            for (int k = 0; k < 7; ++k) sB[k * S + t] = da0[k];
+        }
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 7; ++k) redgeR[k] -= w.E2 * sB[k * S + sp1];
     }
+    if (keeps) {
 #pragma unroll
-    for (int k = 0; k < 7; ++k) sA[(8 + k) * S + tid] = redgeR[k];
+        for (int k = 0; k < 7; ++k) sA[(8 + k) * S + t] = redgeR[k];
+    }
+    if (leaves) {
+        const int w = cslot(2);
+#pragma unroll
+        for (int k = 0; k < 7; ++k) sA[(8 + k) * S + w] = redgeR[k];
+    }
     __syncthreads();
 
     // ------------------------------------------------------------ R7
     // donor-cell remap fluxes: this zone gives its right part across face
     // i+1/2 when delta > 0 and its left part across i-1/2 when delta < 0
     {
-        const bool zone_ok = pen && i >= 6 && i <= M - 7;
+        const bool zone_ok = pen && i >= (first ? 6 : 0) && i <= M - 7;
         const bool wr = zone_ok && delR >= T(0);
         const bool wl = zone_ok && delL < T(0) && i >= 1;
         // (two registers a variable are held over the two directions, of which
@@ -1021,8 +1152,9 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
         T eL[7], eR[7];
         {
             T aL[7];
+            const int e = left(2);
 #pragma unroll
-            for (int k = 0; k < 7; ++k) aL[k] = sA[(8 + k) * S + sm1];
+            for (int k = 0; k < 7; ++k) aL[k] = sA[(8 + k) * S + e];
             if (flat) {
 #pragma unroll
                 for (int k = 0; k < 7; ++k) {
@@ -1044,7 +1176,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
             for (int k = 0; k < 7; ++k) {
                 Para<T> rc;
                 rc.edges(QL[k], eL[k], eR[k]);
-                sA[k * S + tid] = delR * rc.right(yR);
+                sB[k * S + t] = delR * rc.right(yR);
             }
         }
         if (wl) {
@@ -1053,26 +1185,31 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
             for (int k = 0; k < 7; ++k) {
                 Para<T> rc;
                 rc.edges(QL[k], eL[k], eR[k]);
-                sA[k * S + sm1] = delL * rc.left(yL);
+                sB[k * S + t - d] = delL * rc.left(yL);
             }
         }
     }
     // what the update reads from tables, requested ahead of the barrier
     const int gc = g < 0 ? 0 : (g < N ? g : N - 1);
-    const T idx = elem(a.rdx, gc), idc = elem(a.rdc, gc);
-    const T iwq = FUSE_CFL ? elem(a.rdx_q, qq) : T(0), iwr = FUSE_CFL ? elem(a.rdx_r, r) : T(0);
+    const T idx = load(a.rdx, gc), idc = load(a.rdc, gc);
+    const T iwq = FUSE_CFL ? load(a.rdx_q, qq) : T(0), iwr = FUSE_CFL ? load(a.rdx_r, r) : T(0);
     __syncthreads();
 
     // ------------------------------------------------------------ R8
-    // signal-speed maximum in the sweep's precision: a maximum selects one
-    // value, so reducing in FP32 and converting the result gives the FP64
-    // maximum of the converted values exactly
-    T smax = T(0);
+    T fr[7];
+#pragma unroll
+    for (int k = 0; k < 7; ++k) fr[k] = sB[k * S + t];
+    if (leaves) {
+        const int w = cslot(1);
+#pragma unroll
+        for (int k = 0; k < 7; ++k) sB[k * S + w] = fr[k];
+    }
     if (interior) {
+        const int rm1 = left(1);
         T out[8];
         T nw[7];
 #pragma unroll
-        for (int k = 0; k < 7; ++k) nw[k] = Qr[k] + (dC[k] + sA[k * S + sm1] - sA[k * S + tid]) * idx;
+        for (int k = 0; k < 7; ++k) nw[k] = Qr[k] + (dC[k] + sB[k * S + rm1] - fr[k]) * idx;
         T nbn = bn, nb1 = nw[4], nb2 = nw[5];
         if (a.janhunen) {
             // -v div B' source, split: n-derivative of B'_n, pre-sweep velocity
@@ -1122,7 +1259,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
         }
         const unsigned int o = base + (unsigned int)(g * (int)a.stride_n);
 #pragma unroll
-        for (int v = 0; v < 8; ++v) elem(a.var[v], o) = out[v];
+        for (int v = 0; v < 8; ++v) store(a.var[v], o, out[v]);
         if (FUSE_CFL && cfl_max && !masked) {
             // signal speed of the updated zone, for the next step's dt (the
             // maximum is reduced in FP64)
@@ -1159,13 +1296,15 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
                 T cf = Ar<T>::sqrtp(T(0.5) * (s2 + Ar<T>::sqrt_(disc)));
                 sp = tmax(sp, (fabs_(w2) + cf) * i2);
             }
-            smax = sp;
+            smax = smax > sp ? smax : sp;
         }
+    }
     }
     if (STATS) {
         __syncthreads();
-        if (tid < kStatWords && s_stat[tid] != 0u && a.stats)
-            atomicAdd(&a.stats[stat_slot * kStatWords + tid], (unsigned long long)s_stat[tid]);
+        const int w = threadIdx.x;
+        if (w < kStatWords && s_stat[w] != 0u && args.stats)
+            atomicAdd(&args.stats[stat_slot * kStatWords + w], (unsigned long long)s_stat[w]);
     }
     if (FUSE_CFL && cfl_max) {
         // wave max (all lanes active), workgroup max, one atomic per workgroup
@@ -1175,9 +1314,9 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
             T o = __shfl_xor(smax, off);
             smax = o > smax ? o : smax;
         }
-        if (__lane_id() == 0) s_red[tid >> 6] = (double)smax;
+        if (__lane_id() == 0) s_red[threadIdx.x >> 6] = (double)smax;
         __syncthreads();
-        if (tid == 0) {
+        if (threadIdx.x == 0) {
             double m = 0.0;
             const int nw = (blockDim.x + 63) >> 6;
             for (int w = 0; w < nw; ++w) m = s_red[w] > m ? s_red[w] : m;
@@ -1191,11 +1330,14 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<T> &a, const int tq, 
 // them.  A wave's stages wait on LDS, barriers and loads more than half of
 // their time, so resident waves decide: the ensemble sweep with 82 registers
 // (two workgroups of 512 per CU instead of three) took 59.1 ms against 45.5 ms
-// for four steps of 32 members.
+// for four steps of 32 members.  A march's workgroups of 256 lanes leave room
+// for 5 waves per SIMD in FP32 (88 registers, 95 in the fused form) and for 3
+// in FP64 (168).
 template <typename T>
-constexpr int sweep_waves(int SM, int GUESS, bool TRACE)
+constexpr int sweep_waves(int SM, int GUESS, bool TRACE, bool MARCH = false)
 {
     if (GUESS == kGuessLearned) return 4;
+    if (MARCH) return sizeof(T) == 4 ? (TRACE ? 4 : 5) : (TRACE ? 2 : 3);
     return sizeof(T) == 4 && GUESS == kGuessPlain && !TRACE && ((SM > 0 && SM <= 512) || SM == 768) ? 6 : 1;
 }
 
@@ -1203,9 +1345,10 @@ constexpr int sweep_waves(int SM, int GUESS, bool TRACE)
 // the network pass next to the sweep's registers (~132 VGPRs, 3 waves per
 // SIMD); a budget of 4 waves per SIMD (128 registers, a few bytes spilled
 // in the fused form) makes it ~20 % faster (measured).
-template <int AX, typename T, bool STATS, bool FUSE_CFL, int SM, int GUESS = kGuessPlain, bool TRACE = false>
+template <int AX, typename T, bool STATS, bool FUSE_CFL, int SM, int GUESS = kGuessPlain, bool TRACE = false,
+          bool MARCH = false>
 __global__ void __launch_bounds__(SM > 0 ? SM : 1024)
-    __attribute__((amdgpu_waves_per_eu(sweep_waves<T>(SM, GUESS, TRACE)))) sweep_kernel(const SweepArgs<T> a)
+    __attribute__((amdgpu_waves_per_eu(sweep_waves<T>(SM, GUESS, TRACE, MARCH)))) sweep_kernel(const SweepArgs<T> a)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     double *s_red = reinterpret_cast<double *>(smem_raw);
@@ -1226,8 +1369,17 @@ __global__ void __launch_bounds__(SM > 0 ? SM : 1024)
     const int tq = tile - r * a.tiles_q;
     const T dt = a.dt_dev ? T(*a.dt_dev) : a.dt;
     unsigned long long *cm = a.cfl_max ? a.cfl_max + (b % kCflSlots) * kCflStride : nullptr;
-    sweep_tile<AX, T, STATS, FUSE_CFL, SM, GUESS, TRACE>(a, tq, r, seg, dt, cm, b % kStatSlots, smem_raw, s_red, s_stat,
-                                                  s_guess);
+    if constexpr (MARCH) {
+        // the arguments where the launch put them (the first bytes of the
+        // kernel's argument segment), so that each chunk reads them from there
+        typedef const __attribute__((address_space(4))) SweepArgs<T> kernarg_t;
+        const kernarg_t &ka = *(kernarg_t *)__builtin_amdgcn_kernarg_segment_ptr();
+        sweep_tile<AX, T, STATS, FUSE_CFL, SM, GUESS, TRACE, true>(ka, tq, r, seg, dt, cm, b % kStatSlots, smem_raw,
+                                                                   s_red, s_stat, s_guess);
+    } else {
+        sweep_tile<AX, T, STATS, FUSE_CFL, SM, GUESS, TRACE>(a, tq, r, seg, dt, cm, b % kStatSlots, smem_raw, s_red,
+                                                             s_stat, s_guess);
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -1,0 +1,97 @@
+"""Whole pencils swept in chunks by one workgroup (the path of a context without
+pencil segments): bit for bit the result of the segmented tile path, whose own
+results the oracle tests pin, at the sizes where chunks begin and end."""
+import numpy as np
+import pytest
+import torch
+
+from tests import gpu_cases as GC
+from paper_1607_02214_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def _faces(n, seed):
+    rng = np.random.default_rng(seed)
+    f = [np.concatenate([[0.0], np.cumsum(rng.uniform(0.7, 1.3, k))]) for k in n]
+    return [x / x[-1] for x in f]
+
+
+def _case(kind, n, tracing):
+    nx, ny, nz = n
+    if kind == "dipole":
+        case = GC.dipole_case(nx=nx, ny=ny, nz=nz)
+    elif kind == "blast":
+        case = GC.blast_case(n=n)
+    else:
+        case = GC.Case("smooth", _faces(n, 7), I.random_smooth_state((nz, ny, nx), seed=9))
+    case.tracing = tracing
+    return case
+
+
+def _run(case, dtype, segments, tile=0):
+    ctx = case.context()
+    for axis in range(3):
+        n = ctx.n[axis]
+        ctx.set_segments(axis, min(segments, n // 7) if segments > 1 else 0)
+        ctx.set_tile(axis, tile)
+    u = torch.from_numpy(case.U).to("cuda", dtype).contiguous()
+    ctx.advance(u, 3, 0.4)                     # both sweep orders, the fused signal speed
+    return u, ctx.stats(), ctx.time(u)
+
+
+# axis sizes around one, two and more chunks of 25 to 121 zones, one zone more
+# or less than full chunks, pencil counts that leave the last workgroup short
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("kind,n", [
+    ("smooth", (14, 18, 16)), ("smooth", (43, 69, 93)), ("smooth", (17, 118, 44)),
+    ("blast", (50, 21, 68)), ("blast", (171, 19, 67)),
+    ("dipole", (64, 43, 28)), ("dipole", (121, 32, 45)),
+])
+def test_march_equals_segments(kind, n, dtype):
+    case = _case(kind, n, 0)
+    ref, st, t = _run(case, dtype, 2)
+    got, st2, t2 = _run(case, dtype, 1)
+    assert torch.equal(got, ref) and st2 == st and t2 == t
+
+
+@pytest.mark.parametrize("tile", [1, 2, 3, 8])
+def test_march_of_given_pencils(tile):
+    case = _case("smooth", (40, 53, 61), 0)
+    ref, st, _ = _run(case, torch.float32, 3)
+    got, st2, _ = _run(case, torch.float32, 1, tile)
+    assert torch.equal(got, ref) and st2 == st
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_march_characteristic(dtype):
+    case = _case("dipole", (96, 43, 60), 1)
+    ref, st, _ = _run(case, dtype, 2)
+    got, st2, _ = _run(case, dtype, 1)
+    assert torch.equal(got, ref) and st2 == st
+
+
+def test_march_in_a_graph():
+    # nothing of the path allocates or synchronises: captured once, replayed on
+    # new states, with eager work between the replays
+    case = _case("blast", (40, 33, 30), 0)
+    ctx = case.context()
+    start = torch.from_numpy(case.U).to("cuda", torch.float32).contiguous()
+    dt = ctx.cfl_dt(start, 0.4)
+    u = start.clone()
+    ctx.sweep(u, dt, 0)                        # loads the kernels
+    s = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        for axis in range(3):
+            ctx.sweep(u, dt, axis)
+    for k in range(3):
+        u.copy_(start * (1.0 + 0.25 * k))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        ref = start * (1.0 + 0.25 * k)
+        for axis in range(3):
+            ctx.sweep(ref, dt, axis)
+        torch.cuda.synchronize()
+        assert torch.equal(u, ref)
