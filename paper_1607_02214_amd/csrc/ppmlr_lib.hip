@@ -441,7 +441,8 @@ size_t march_lds(const ppmlr_ctx *c, int axis, int P, int SM, int elem)
 // which grows with the waves that share a CU (FP32, us: 4.5 + 0.155 per wave,
 // from 256x192x192 sweeps at 8, 12, 16 and 20 waves per CU: 560, 413, 336, 295
 // us).  In y and z, rows narrower than 32 B cost more (y, z sweep: 16 B 1.03,
-// 1.30; 8 B 1.35; widths other than powers of two 1.1 to 1.2).
+// 1.30; 8 B 1.35; widths other than powers of two 1.1 to 1.2); less so where
+// the state stays in the last-level cache (128x96x96: 16 B 1.0, 8 B 1.15).
 March march_search(const ppmlr_ctx *c, int axis, int elem, int P_req)
 {
     March best;
@@ -451,6 +452,7 @@ March march_search(const ppmlr_ctx *c, int axis, int elem, int P_req)
     const int wps = elem == 4 ? (trace ? 4 : 5) : (trace ? 2 : 3);     // waves per SIMD (registers)
     const double t0 = elem == 4 ? (trace ? 5.0 : 4.5) : 4.2;           // us of a chunk alone, and per wave on its CU
     const double t1 = elem == 4 ? (trace ? 0.22 : 0.155) : (trace ? 0.78 : 0.52);
+    const bool cached = 8.0 * c->n[0] * c->n[1] * c->n[2] * elem < 128e6;
     double best_t = 1e300;
     for (int P = P_req > 0 ? P_req : 1; P <= (P_req > 0 ? P_req : 8); ++P) {
         for (int C = 1; C <= N + kG; ++C) {
@@ -471,12 +473,13 @@ March march_search(const ppmlr_ctx *c, int axis, int elem, int P_req)
             double row = 1.0;
             if (axis != 0) {
                 const int w = elem == 4 ? P : 2 * P;
-                row = w >= 8 ? 1.0 : (w == 4 ? (axis == 1 ? 1.03 : 1.25) : (w > 4 ? 1.12 : (w == 3 ? 1.2 : (w == 2 ? 1.35 : 1.8))));
+                if (cached) row = w >= 4 ? 1.0 : (w == 3 ? 1.1 : (w == 2 ? 1.15 : 1.7));
+                else row = w >= 8 ? 1.0 : (w == 4 ? (axis == 1 ? 1.03 : 1.25) : (w > 4 ? 1.12 : (w == 3 ? 1.2 : (w == 2 ? 1.35 : 1.8))));
             }
             // (a last round that is not full takes a round's time; with many
             // rounds workgroups follow each other and it is less)
             const double t = rounds <= 1.0 ? C * row * (t0 + t1 * waves * std::ceil(wgs / 256.0))
-                                           : C * row * (t0 + t1 * waves * per_cu) * (rounds + 0.5);
+                                           : C * row * (t0 + t1 * waves * per_cu) * (rounds + 0.2);
             if (t < best_t - 1e-9) { best_t = t; best = m; }
             if (C > 64) break;
         }
