@@ -95,8 +95,7 @@ struct ppmlr_ctx {
 struct ppmlr_mlp {
     int device = 0;
     int max_batch = 0;
-    unsigned short *d_frag = nullptr;        // packed fragments of the current parameters
-    float *d_partials = nullptr;             // [max_batch / 64][kNPar + 1]
+    float *d_partials = nullptr;             // [workgroups of a gradient launch][kNPar + 1]
     std::string err;
 };
 
@@ -2385,6 +2384,14 @@ static ppmlr_status mlp_check(ppmlr_mlp *w, hipError_t e, const char *what)
                     std::string(what) + ": " + hipGetErrorString(e));
 }
 
+// Whether a matrix's rows can be read 16 bytes at a time.
+static bool mlp_vec(const float *X, int ldx) { return ((uintptr_t)X & 15) == 0 && (ldx & 3) == 0; }
+
+// Workgroups of a gradient launch: one per 64 samples (four waves of a tile of
+// 16), at most one per CU (the waves then take several tiles, and the partials
+// to add stay few); the workspace holds one partial per 64 samples.
+static int mlp_blocks(int n) { return std::min((n + 63) / 64, 256); }
+
 ppmlr_status ppmlr_mlp_create(int max_batch, ppmlr_mlp **out)
 {
     if (!out || max_batch < 1) return PPMLR_EINVAL;
@@ -2392,8 +2399,7 @@ ppmlr_status ppmlr_mlp_create(int max_batch, ppmlr_mlp **out)
     ppmlr_mlp *w = new ppmlr_mlp();
     w->max_batch = max_batch;
     ppmlr_status e = mlp_check(w, hipGetDevice(&w->device), "hipGetDevice");
-    const size_t blocks = (size_t)(max_batch + 63) / 64;
-    if (!e) e = mlp_check(w, hipMalloc((void **)&w->d_frag, sizeof(unsigned short) * 256 * ppmlr::mlp::kTiles), "hipMalloc");
+    const size_t blocks = (size_t)mlp_blocks(max_batch);
     if (!e) e = mlp_check(w, hipMalloc((void **)&w->d_partials, sizeof(float) * blocks * (ppmlr::mlp::kNPar + 1)),
                           "hipMalloc");
     if (e) {
@@ -2408,20 +2414,11 @@ void ppmlr_mlp_destroy(ppmlr_mlp *w)
 {
     if (!w) return;
     (void)hipDeviceSynchronize();
-    if (w->d_frag) (void)hipFree(w->d_frag);
     if (w->d_partials) (void)hipFree(w->d_partials);
     delete w;
 }
 
 const char *ppmlr_mlp_last_error(const ppmlr_mlp *w) { return w ? w->err.c_str() : "null workspace"; }
-
-static ppmlr_status mlp_pack(ppmlr_mlp *w, const float *theta, hipStream_t st)
-{
-    const int n = 256 * ppmlr::mlp::kTiles;
-    hipLaunchKernelGGL(ppmlr::mlp::pack_kernel, dim3((n + 255) / 256), dim3(256), 0, st, theta, w->d_frag,
-                       ppmlr::mlp::kTiles);
-    return mlp_check(w, hipGetLastError(), "pack launch");
-}
 
 ppmlr_status ppmlr_mlp_forward(ppmlr_mlp *w, const float *theta, const float *X, int ldx, int n, float *Y, int ldy,
                                void *stream)
@@ -2432,10 +2429,12 @@ ppmlr_status ppmlr_mlp_forward(ppmlr_mlp *w, const float *theta, const float *X,
     if (!theta || !X || !Y || ldx < ppmlr::mlp::kIn || ldy < ppmlr::mlp::kOut)
         return mlp_fail(w, PPMLR_EINVAL, "bad forward arguments");
     hipStream_t st = (hipStream_t)stream;
-    ppmlr_status e = mlp_pack(w, theta, st);
-    if (e) return e;
-    hipLaunchKernelGGL(ppmlr::mlp::forward_kernel, dim3((n + 63) / 64), dim3(64), 0, st, X, ldx, n,
-                       (const unsigned short *)w->d_frag, theta, Y, ldy);
+    // three workgroups of four waves per CU at most, each wave over several tiles
+    const dim3 grid((unsigned)std::min<long long>(((long long)n + 63) / 64, 768));
+    if (mlp_vec(X, ldx))
+        hipLaunchKernelGGL(ppmlr::mlp::forward_kernel<true>, grid, dim3(256), 0, st, X, ldx, n, theta, Y, ldy);
+    else
+        hipLaunchKernelGGL(ppmlr::mlp::forward_kernel<false>, grid, dim3(256), 0, st, X, ldx, n, theta, Y, ldy);
     return mlp_check(w, hipGetLastError(), "forward launch");
 }
 
@@ -2444,10 +2443,13 @@ static ppmlr_status mlp_grad_launch(ppmlr_mlp *w, const float *theta, const floa
 {
     if (!theta || !X || !Y || n < 1 || n > w->max_batch || ldx < ppmlr::mlp::kIn || ldy < ppmlr::mlp::kOut)
         return mlp_fail(w, PPMLR_EINVAL, "bad batch arguments (1 <= n <= max_batch)");
-    ppmlr_status e = mlp_pack(w, theta, st);
-    if (e) return e;
-    hipLaunchKernelGGL(ppmlr::mlp::grad_kernel, dim3((n + 63) / 64), dim3(64), 0, st, X, ldx, Y, ldy, n,
-                       (const unsigned short *)w->d_frag, theta, w->d_partials);
+    const dim3 grid((unsigned)mlp_blocks(n));
+    if (mlp_vec(X, ldx))
+        hipLaunchKernelGGL(ppmlr::mlp::grad_kernel<true>, grid, dim3(256), 0, st, X, ldx, Y, ldy, n, theta,
+                           w->d_partials);
+    else
+        hipLaunchKernelGGL(ppmlr::mlp::grad_kernel<false>, grid, dim3(256), 0, st, X, ldx, Y, ldy, n, theta,
+                           w->d_partials);
     return mlp_check(w, hipGetLastError(), "grad launch");
 }
 
@@ -2459,9 +2461,9 @@ ppmlr_status ppmlr_mlp_grad(ppmlr_mlp *w, const float *theta, const float *X, in
     ppmlr_status e = mlp_grad_launch(w, theta, X, ldx, Y, ldy, n, st);
     if (e) return e;
     const int np = ppmlr::mlp::kNPar + 1;
-    hipLaunchKernelGGL(ppmlr::mlp::reduce_adam_kernel, dim3((np + 255) / 256), dim3(256), 0, st, w->d_partials,
-                       (n + 63) / 64, grad, loss, (float *)nullptr, (float *)nullptr, (float *)nullptr, 0, 0, 0.0f,
-                       0.0f, 0.0f, 0.0f);
+    hipLaunchKernelGGL(ppmlr::mlp::reduce_adam_kernel, dim3((np + 63) / 64), dim3(256), 0, st, w->d_partials,
+                       mlp_blocks(n), grad, loss, (float *)nullptr, (float *)nullptr, (float *)nullptr, 0, 1.0f, 1.0f,
+                       0.0f, 0.0f, 0.0f, 0.0f);
     return mlp_check(w, hipGetLastError(), "reduce launch");
 }
 
@@ -2475,8 +2477,9 @@ ppmlr_status ppmlr_mlp_train_step(ppmlr_mlp *w, float *theta, float *m, float *v
     ppmlr_status e = mlp_grad_launch(w, theta, X, ldx, Y, ldy, n, st);
     if (e) return e;
     const int np = ppmlr::mlp::kNPar + 1;
-    hipLaunchKernelGGL(ppmlr::mlp::reduce_adam_kernel, dim3((np + 255) / 256), dim3(256), 0, st, w->d_partials,
-                       (n + 63) / 64, (float *)nullptr, loss, theta, m, v, 1, t, lr, beta1, beta2, eps);
+    const float c1 = (float)(1.0 - std::pow((double)beta1, t)), c2 = (float)(1.0 - std::pow((double)beta2, t));
+    hipLaunchKernelGGL(ppmlr::mlp::reduce_adam_kernel, dim3((np + 63) / 64), dim3(256), 0, st, w->d_partials,
+                       mlp_blocks(n), (float *)nullptr, loss, theta, m, v, 1, c1, c2, lr, beta1, beta2, eps);
     return mlp_check(w, hipGetLastError(), "adam launch");
 }
 

@@ -50,11 +50,16 @@ __device__ __forceinline__ unsigned short f2bf(float f)
 }
 __device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float((unsigned int)h << 16); }
 
+// four FP32 -> BF16 (round to nearest even, as f2bf), two per instruction
 __device__ __forceinline__ bf16x4 pack4(float a, float b, float c, float d)
 {
-    bf16x4 r;
-    r[0] = (short)f2bf(a); r[1] = (short)f2bf(b); r[2] = (short)f2bf(c); r[3] = (short)f2bf(d);
-    return r;
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    const f2 ab = {a, b}, cd = {c, d};
+    const u2 r = {__builtin_bit_cast(unsigned int, __builtin_convertvector(ab, b2)),
+                  __builtin_bit_cast(unsigned int, __builtin_convertvector(cd, b2))};
+    return __builtin_bit_cast(bf16x4, r);
 }
 
 __device__ __forceinline__ f32x4 mfma(bf16x4 a, bf16x4 b, f32x4 c)
@@ -168,212 +173,331 @@ __device__ __forceinline__ void forward_wave(const unsigned short *F, const unsi
     }
 }
 
-// Forward over n samples: one wave per 64 samples.
-__global__ void __launch_bounds__(64) forward_kernel(const float *__restrict__ X, int ldx, int n,
-                                                     const unsigned short *__restrict__ frag,
-                                                     const float *__restrict__ theta, float *__restrict__ Y, int ldy)
+// Fragment of tile t of the packed set for this lane, from the FP32 parameters.
+__device__ __forceinline__ bf16x4 theta_frag(const float *__restrict__ th, int t, int lane)
 {
-    __shared__ __align__(16) unsigned short F[64 * 16];
-    __shared__ float O[64 * 2];
-    const int lane = threadIdx.x;
-    const long long s = (long long)blockIdx.x * 64 + lane;
+    return pack4(frag_value(th, t, lane, 0), frag_value(th, t, lane, 1), frag_value(th, t, lane, 2),
+                 frag_value(th, t, lane, 3));
+}
+
+// Features of sample s for this lane as B operand (k = 4q .. 4q + 3; features
+// 14, 15 are zero).  VEC: rows on 16-byte boundaries.
+template <bool VEC>
+__device__ __forceinline__ bf16x4 load_x(const float *__restrict__ X, int ldx, long long s, int q)
+{
+    const float *x = X + s * ldx + 4 * q;
+    float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (VEC && q < 3) {
+        const float4 w = *reinterpret_cast<const float4 *>(x);
+        v[0] = w.x; v[1] = w.y; v[2] = w.z; v[3] = w.w;
+    } else if (VEC) {
+        const float2 w = *reinterpret_cast<const float2 *>(x);
+        v[0] = w.x; v[1] = w.y;
+    } else {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) F[lane * 16 + k] = (s < n && k < kIn) ? f2bf(X[s * ldx + k]) : (unsigned short)0;
-    __syncthreads();
-    forward_wave(F, frag, theta, O, 2);
-    __syncthreads();
-    if (s < n) {
-        Y[s * ldy + 0] = O[lane * 2 + 0];
-        Y[s * ldy + 1] = O[lane * 2 + 1];
+        for (int i = 0; i < 4; ++i)
+            if (4 * q + i < kIn) v[i] = x[i];
     }
+    return pack4(v[0], v[1], v[2], v[3]);
 }
 
-// Loss and gradient of L = (1 / 2n) sum (o - y)^2 over one wave's 64 samples
-// (rows beyond n contribute nothing).  Writes the partial gradient of this
-// workgroup, in theta order, and its partial loss to part[kNPar].  The
-// backward pass uses the same BF16 operands / FP32 accumulation; the GELU
-// derivatives are kept in BF16.
-__global__ void __launch_bounds__(64) grad_kernel(const float *__restrict__ X, int ldx, const float *__restrict__ Yt,
-                                                  int ldy, int n, const unsigned short *__restrict__ frag,
-                                                  const float *__restrict__ theta, float *__restrict__ partials)
+// Forward over n samples.  A wave keeps the whole network in registers (24
+// fragments and the biases, ~80 registers, built from theta once) and takes
+// tiles of 16 samples in turn, the next tile's features requested ahead; nothing
+// goes through LDS.  What bounds it is the GELU of 128 hidden units a sample
+// (10 vector instructions, two of them transcendental): the matrix products
+// take a quarter of that and the records 112 MB.  1 M records with rows of 28
+// floats: 170 us as one wave per 64 samples with the weights re-read per tile
+// (and a launch to pack them), 68 us now.
+template <bool VEC>
+__global__ void __launch_bounds__(256) forward_kernel(const float *__restrict__ X, int ldx, int n,
+                                                      const float *__restrict__ theta, float *__restrict__ Y, int ldy)
 {
-    __shared__ __align__(16) unsigned short XT[16 * 64];   // [f][s]
-    __shared__ __align__(16) unsigned short H1T[64 * 64];  // [hid][s]
-    __shared__ __align__(16) unsigned short H2T[64 * 64];
-    __shared__ __align__(16) unsigned short D2T[64 * 64];  // dZ2^T
-    __shared__ __align__(16) unsigned short D1T[64 * 64];  // dZ1^T
-    __shared__ __align__(16) unsigned short DOT[16 * 64];  // dO^T, rows >= 2 zero
-    __shared__ __align__(16) bf16x4 G1F[16 * 64];          // gelu'(Z1), fragment order
-    __shared__ __align__(16) bf16x4 G2F[16 * 64];
-    __shared__ float red[64];
-    const int lane = threadIdx.x;
-    const int r = lane & 15, q = lane >> 4;
-    const long long s0 = (long long)blockIdx.x * 64;
+    const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+    const int tiles = (int)(((long long)n + 15) / 16), nw = (int)gridDim.x * 4;
+    int tile = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+    if (tile >= tiles) return;
+    auto sample = [&](int t) { const long long s = (long long)t * 16 + r; return s < n ? s : (long long)n - 1; };
+    bf16x4 xb = load_x<VEC>(X, ldx, sample(tile), q);
+    bf16x4 w1[4], w2[16], w3[4];
+    f32x4 b1[4], b2[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        w1[t] = theta_frag(theta, kTA1 + t, lane);
+        w3[t] = theta_frag(theta, kTA3 + t, lane);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            b1[t][i] = theta[kOffB1 + t * 16 + 4 * q + i];
+            b2[t][i] = theta[kOffB2 + t * 16 + 4 * q + i];
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < 16; ++t) w2[t] = theta_frag(theta, kTA2 + t, lane);
+    const float b30 = theta[kOffB3], b31 = theta[kOffB3 + 1];
     const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    float *part = partials + (size_t)blockIdx.x * (kNPar + 1);
-    for (int k = 0; k < 16; ++k) {
-        const long long s = s0 + lane;
-        XT[k * 64 + lane] = (s < n && k < kIn) ? f2bf(X[s * ldx + k]) : (unsigned short)0;
-    }
-    __syncthreads();
-    auto fragT = [&](const unsigned short *M, int row0, int kt) -> bf16x4 {   // M[row][s]: rows row0 + r
-        return *reinterpret_cast<const bf16x4 *>(M + (row0 + r) * 64 + kt * 16 + 4 * q);
-    };
-    // ---- forward (transposed), keeping activations and GELU derivatives
-    bf16x4 xb[4];
-    for (int st = 0; st < 4; ++st)
-        for (int i = 0; i < 4; ++i) xb[st][i] = (short)XT[(4 * q + i) * 64 + st * 16 + r];
-    bf16x4 h1[4][4];
-    for (int mt = 0; mt < 4; ++mt) {
-        const bf16x4 a = load_frag(frag, kTA1 + mt, lane);
-        for (int st = 0; st < 4; ++st) {
-            f32x4 z = mfma(a, xb[st], zero);
-            for (int i = 0; i < 4; ++i) z[i] += theta[kOffB1 + mt * 16 + 4 * q + i];
-            G1F[(mt * 4 + st) * 64 + lane] = pack4(gelu_grad(z[0]), gelu_grad(z[1]), gelu_grad(z[2]), gelu_grad(z[3]));
-            h1[mt][st] = pack4(gelu(z[0]), gelu(z[1]), gelu(z[2]), gelu(z[3]));
-            for (int i = 0; i < 4; ++i) H1T[(mt * 16 + 4 * q + i) * 64 + st * 16 + r] = (unsigned short)h1[mt][st][i];
+    for (; tile < tiles; tile += nw) {
+        const bf16x4 x0 = xb;
+        if (tile + nw < tiles) xb = load_x<VEC>(X, ldx, sample(tile + nw), q);
+        bf16x4 h1[4], h2[4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+            const f32x4 z = mfma(w1[mt], x0, zero);
+            h1[mt] = pack4(gelu(z[0] + b1[mt][0]), gelu(z[1] + b1[mt][1]), gelu(z[2] + b1[mt][2]),
+                           gelu(z[3] + b1[mt][3]));
         }
-    }
-    bf16x4 h2[4][4];
-    for (int mt = 0; mt < 4; ++mt) {
-        f32x4 acc[4] = {zero, zero, zero, zero};
-        for (int kt = 0; kt < 4; ++kt) {
-            const bf16x4 a = load_frag(frag, kTA2 + mt * 4 + kt, lane);
-            for (int st = 0; st < 4; ++st) acc[st] = mfma(a, h1[kt][st], acc[st]);
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+            f32x4 z = zero;
+#pragma unroll
+            for (int kt = 0; kt < 4; ++kt) z = mfma(w2[mt * 4 + kt], h1[kt], z);
+            h2[mt] = pack4(gelu(z[0] + b2[mt][0]), gelu(z[1] + b2[mt][1]), gelu(z[2] + b2[mt][2]),
+                           gelu(z[3] + b2[mt][3]));
         }
-        for (int st = 0; st < 4; ++st) {
-            f32x4 z = acc[st];
-            for (int i = 0; i < 4; ++i) z[i] += theta[kOffB2 + mt * 16 + 4 * q + i];
-            G2F[(mt * 4 + st) * 64 + lane] = pack4(gelu_grad(z[0]), gelu_grad(z[1]), gelu_grad(z[2]), gelu_grad(z[3]));
-            h2[mt][st] = pack4(gelu(z[0]), gelu(z[1]), gelu(z[2]), gelu(z[3]));
-            for (int i = 0; i < 4; ++i) H2T[(mt * 16 + 4 * q + i) * 64 + st * 16 + r] = (unsigned short)h2[mt][st][i];
+        f32x4 o = zero;
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) o = mfma(w3[kt], h2[kt], o);
+        const long long s = (long long)tile * 16 + r;
+        if (q == 0 && s < n) {
+            Y[s * ldy + 0] = o[0] + b30;
+            Y[s * ldy + 1] = o[1] + b31;
         }
-    }
-    f32x4 o[4] = {zero, zero, zero, zero};
-    for (int kt = 0; kt < 4; ++kt) {
-        const bf16x4 a = load_frag(frag, kTA3 + kt, lane);
-        for (int st = 0; st < 4; ++st) o[st] = mfma(a, h2[kt][st], o[st]);
-    }
-    // ---- output error dO = (o - y) / n (rows 0, 1 of the output tile), loss
-    const float inv_n = 1.0f / (float)n;
-    float sq = 0.0f;
-    bf16x4 dob[4];
-    float db3[2] = {0.0f, 0.0f};
-    for (int st = 0; st < 4; ++st) {
-        const long long ss = s0 + st * 16 + r;
-        float d[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (q == 0 && ss < n) {
-            for (int k = 0; k < kOut; ++k) {
-                const float e = o[st][k] + theta[kOffB3 + k] - Yt[ss * ldy + k];
-                sq += e * e;
-                d[k] = e * inv_n;
-            }
-        }
-        db3[0] += d[0];
-        db3[1] += d[1];
-        dob[st] = pack4(d[0], d[1], d[2], d[3]);
-        for (int i = 0; i < 4; ++i) DOT[(4 * q + i) * 64 + st * 16 + r] = (unsigned short)dob[st][i];
-    }
-    // ---- through layer 3: dH2^T = W3 dO^T, dZ2 = dH2 gelu'(Z2)
-    bf16x4 d2[4][4];
-    float gb2[4][4];
-    for (int mt = 0; mt < 4; ++mt) {
-        const bf16x4 a = load_frag(frag, kTB3 + mt, lane);
-        for (int i = 0; i < 4; ++i) gb2[mt][i] = 0.0f;
-        for (int st = 0; st < 4; ++st) {
-            f32x4 g = mfma(a, dob[st], zero);
-            const bf16x4 gz = G2F[(mt * 4 + st) * 64 + lane];
-            for (int i = 0; i < 4; ++i) {
-                g[i] *= bf2f((unsigned short)gz[i]);
-                gb2[mt][i] += g[i];
-            }
-            d2[mt][st] = pack4(g[0], g[1], g[2], g[3]);
-            for (int i = 0; i < 4; ++i) D2T[(mt * 16 + 4 * q + i) * 64 + st * 16 + r] = (unsigned short)d2[mt][st][i];
-        }
-    }
-    // ---- through layer 2: dH1^T = W2 dZ2^T, dZ1 = dH1 gelu'(Z1)
-    float gb1[4][4];
-    for (int mt = 0; mt < 4; ++mt) {
-        f32x4 acc[4] = {zero, zero, zero, zero};
-        for (int kt = 0; kt < 4; ++kt) {
-            const bf16x4 a = load_frag(frag, kTB2 + mt * 4 + kt, lane);
-            for (int st = 0; st < 4; ++st) acc[st] = mfma(a, d2[kt][st], acc[st]);
-        }
-        for (int i = 0; i < 4; ++i) gb1[mt][i] = 0.0f;
-        for (int st = 0; st < 4; ++st) {
-            f32x4 g = acc[st];
-            const bf16x4 gz = G1F[(mt * 4 + st) * 64 + lane];
-            for (int i = 0; i < 4; ++i) {
-                g[i] *= bf2f((unsigned short)gz[i]);
-                gb1[mt][i] += g[i];
-            }
-            const bf16x4 gb = pack4(g[0], g[1], g[2], g[3]);
-            for (int i = 0; i < 4; ++i) D1T[(mt * 16 + 4 * q + i) * 64 + st * 16 + r] = (unsigned short)gb[i];
-        }
-    }
-    __syncthreads();
-    // ---- weight gradients: contractions over the 64 samples (K dimension)
-    for (int mt = 0; mt < 4; ++mt) {               // dW3[hid][o] = sum_s H2[s][hid] dO[s][o]
-        f32x4 acc = zero;
-        for (int kt = 0; kt < 4; ++kt) acc = mfma(fragT(H2T, mt * 16, kt), fragT(DOT, 0, kt), acc);
-        if (r < kOut)
-            for (int i = 0; i < 4; ++i) part[kOffW3 + (mt * 16 + 4 * q + i) * kOut + r] = acc[i];
-    }
-    for (int mt = 0; mt < 4; ++mt)                 // dW2[h1][h2] = sum_s H1[s][h1] dZ2[s][h2]
-        for (int nt = 0; nt < 4; ++nt) {
-            f32x4 acc = zero;
-            for (int kt = 0; kt < 4; ++kt) acc = mfma(fragT(H1T, mt * 16, kt), fragT(D2T, nt * 16, kt), acc);
-            for (int i = 0; i < 4; ++i) part[kOffW2 + (mt * 16 + 4 * q + i) * kH + nt * 16 + r] = acc[i];
-        }
-    for (int nt = 0; nt < 4; ++nt) {               // dW1[f][h] = sum_s X[s][f] dZ1[s][h]
-        f32x4 acc = zero;
-        for (int kt = 0; kt < 4; ++kt) acc = mfma(fragT(XT, 0, kt), fragT(D1T, nt * 16, kt), acc);
-        for (int i = 0; i < 4; ++i) {
-            const int f = 4 * q + i;
-            if (f < kIn) part[kOffW1 + f * kH + nt * 16 + r] = acc[i];
-        }
-    }
-    // ---- bias gradients: FP32 row sums over the samples (16 lanes of a row group)
-    for (int mt = 0; mt < 4; ++mt)
-        for (int i = 0; i < 4; ++i) {
-            float v1 = gb1[mt][i], v2 = gb2[mt][i];
-            for (int w = 1; w < 16; w <<= 1) {
-                v1 += __shfl_xor(v1, w);
-                v2 += __shfl_xor(v2, w);
-            }
-            if (r == 0) {
-                part[kOffB1 + mt * 16 + 4 * q + i] = v1;
-                part[kOffB2 + mt * 16 + 4 * q + i] = v2;
-            }
-        }
-    for (int w = 1; w < 16; w <<= 1) {
-        db3[0] += __shfl_xor(db3[0], w);
-        db3[1] += __shfl_xor(db3[1], w);
-    }
-    if (lane == 0) {
-        part[kOffB3] = db3[0];
-        part[kOffB3 + 1] = db3[1];
-    }
-    red[lane] = sq;
-    __syncthreads();
-    if (lane == 0) {
-        float t = 0.0f;
-        for (int i = 0; i < 64; ++i) t += red[i];
-        part[kNPar] = 0.5f * t * inv_n;
     }
 }
 
-// Sum the per-workgroup partials in a fixed order.  grad (may be null)
-// receives the gradient, loss (may be null) the loss; with adam != 0 the
-// bias-corrected Adam step (Kingma & Ba 2015) is applied to theta in place.
-__global__ void reduce_adam_kernel(const float *__restrict__ partials, int nblk, float *grad, float *loss,
-                                   float *theta, float *m, float *v, int adam, int t, float lr, float b1, float b2,
-                                   float eps)
+// Sum over the 16 lanes of a row (every lane gets it), in registers.
+__device__ __forceinline__ float row_sum(float v)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > kNPar) return;
+#define PPMLR_ROR(n) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + n, 0xf, 0xf, true))
+    PPMLR_ROR(8);
+    PPMLR_ROR(4);
+    PPMLR_ROR(2);
+    PPMLR_ROR(1);
+#undef PPMLR_ROR
+    return v;
+}
+
+// Loss and gradient of L = (1 / 2n) sum (o - y)^2.  A workgroup of four waves
+// packs the parameters into LDS fragments, then every wave takes tiles of 16
+// samples: forward and backward as matrix products that hand their result
+// tiles on in registers, the weight gradients as contractions over the
+// tile's samples (operands transposed through the wave's own part of LDS),
+// accumulated in registers over the wave's tiles.  At the end the four waves'
+// gradients are added in LDS in a fixed order and the workgroup writes one
+// partial gradient, in theta order, and its partial loss to part[kNPar].  The
+// backward pass uses BF16 operands / FP32 accumulation; the GELU derivatives
+// are rounded to BF16.
+// Tiles of 16 samples a wave put a batch of 4096 on 256 waves (64 samples a
+// wave, whose loops over register arrays were not unrolled either, left 64
+// waves on 64 CUs: 80 us and a launch to pack; now 24 us, a training step on 4096
+// records 98 -> 26 us).
+constexpr int kGradWave = (16 + 64 * 4 + 16) * 16;                 // BF16 values of a wave's transposed operands
+constexpr size_t kGradLds = (size_t)kTiles * 512 + 4 * (size_t)kGradWave * 2;
+static_assert(kGradLds >= 2 * (size_t)(kNPar + 1) * 4, "the reduction reuses the operands' LDS");
+
+template <bool VEC>
+__global__ void __launch_bounds__(256) grad_kernel(const float *__restrict__ X, int ldx, const float *__restrict__ Yt,
+                                                   int ldy, int n, const float *__restrict__ theta,
+                                                   float *__restrict__ partials)
+{
+    __shared__ __align__(16) unsigned char lds[kGradLds];
+    unsigned short *frag = reinterpret_cast<unsigned short *>(lds);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, q = lane >> 4;
+    unsigned short *XT = frag + kTiles * 256 + wave * kGradWave;    // [feature][sample]
+    unsigned short *H1T = XT + 16 * 16, *H2T = H1T + 64 * 16;       // [hidden][sample]
+    unsigned short *D2T = H2T + 64 * 16, *D1T = D2T + 64 * 16;      // dZ2^T, dZ1^T
+    unsigned short *DOT = D1T + 64 * 16;                            // dO^T, rows >= 2 zero
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int t = wave; t < kTiles; t += 4)
+        *reinterpret_cast<bf16x4 *>(frag + (t * 64 + lane) * 4) = theta_frag(theta, t, lane);
+    f32x4 b1[4], b2[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            b1[t][i] = theta[kOffB1 + t * 16 + 4 * q + i];
+            b2[t][i] = theta[kOffB2 + t * 16 + 4 * q + i];
+        }
+    const float b30 = theta[kOffB3], b31 = theta[kOffB3 + 1];
+    __syncthreads();
+    auto weights = [&](int t) { return *reinterpret_cast<const bf16x4 *>(frag + (t * 64 + lane) * 4); };
+    auto put = [&](unsigned short *M, int row0, const bf16x4 &v) {  // rows row0 + 4q .. + 3 of sample r
+#pragma unroll
+        for (int i = 0; i < 4; ++i) M[(row0 + 4 * q + i) * 16 + r] = (unsigned short)v[i];
+    };
+    auto get = [&](const unsigned short *M, int row0) {             // row row0 + r, samples 4q .. 4q + 3
+        return *reinterpret_cast<const bf16x4 *>(M + (row0 + r) * 16 + 4 * q);
+    };
+    f32x4 gw1[4], gw2[16], gw3[4], gb1[4], gb2[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) { gw1[t] = gw3[t] = gb1[t] = gb2[t] = zero; }
+#pragma unroll
+    for (int t = 0; t < 16; ++t) gw2[t] = zero;
+    float sq = 0.0f, gb30 = 0.0f, gb31 = 0.0f;
+    const float inv_n = 1.0f / (float)n;
+    const int tiles = (n + 15) / 16;
+    for (int tile = (int)blockIdx.x * 4 + wave; tile < tiles; tile += (int)gridDim.x * 4) {
+        const long long s = (long long)tile * 16 + r;
+        const bool in = s < n;
+        bf16x4 x = load_x<VEC>(X, ldx, in ? s : (long long)n - 1, q);
+        if (!in) x = bf16x4{0, 0, 0, 0};
+        put(XT, 0, x);
+        // ---- forward, keeping the activations and the GELU derivatives
+        bf16x4 h1[4], h2[4], g1[4], g2[4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+            f32x4 z = mfma(weights(kTA1 + mt), x, zero);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) z[i] += b1[mt][i];
+            g1[mt] = pack4(gelu_grad(z[0]), gelu_grad(z[1]), gelu_grad(z[2]), gelu_grad(z[3]));
+            h1[mt] = pack4(gelu(z[0]), gelu(z[1]), gelu(z[2]), gelu(z[3]));
+            put(H1T, mt * 16, h1[mt]);
+        }
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+            f32x4 z = zero;
+#pragma unroll
+            for (int kt = 0; kt < 4; ++kt) z = mfma(weights(kTA2 + mt * 4 + kt), h1[kt], z);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) z[i] += b2[mt][i];
+            g2[mt] = pack4(gelu_grad(z[0]), gelu_grad(z[1]), gelu_grad(z[2]), gelu_grad(z[3]));
+            h2[mt] = pack4(gelu(z[0]), gelu(z[1]), gelu(z[2]), gelu(z[3]));
+            put(H2T, mt * 16, h2[mt]);
+        }
+        f32x4 o = zero;
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) o = mfma(weights(kTA3 + kt), h2[kt], o);
+        // ---- output error dO = (o - y) / n (rows 0, 1 of the output tile), loss
+        float d0 = 0.0f, d1 = 0.0f;
+        if (q == 0 && in) {
+            const float e0 = o[0] + b30 - Yt[s * ldy], e1 = o[1] + b31 - Yt[s * ldy + 1];
+            sq += e0 * e0;
+            sq += e1 * e1;
+            d0 = e0 * inv_n;
+            d1 = e1 * inv_n;
+        }
+        gb30 += d0;
+        gb31 += d1;
+        const bf16x4 dO = pack4(d0, d1, 0.0f, 0.0f);
+        put(DOT, 0, dO);
+        // ---- through layer 3: dH2^T = W3 dO^T, dZ2 = dH2 gelu'(Z2)
+        bf16x4 d2[4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+            f32x4 g = mfma(weights(kTB3 + mt), dO, zero);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) g[i] *= bf2f((unsigned short)g2[mt][i]);
+            gb2[mt] += g;
+            d2[mt] = pack4(g[0], g[1], g[2], g[3]);
+            put(D2T, mt * 16, d2[mt]);
+        }
+        // ---- through layer 2: dH1^T = W2 dZ2^T, dZ1 = dH1 gelu'(Z1)
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+            f32x4 g = zero;
+#pragma unroll
+            for (int kt = 0; kt < 4; ++kt) g = mfma(weights(kTB2 + mt * 4 + kt), d2[kt], g);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) g[i] *= bf2f((unsigned short)g1[mt][i]);
+            gb1[mt] += g;
+            put(D1T, mt * 16, pack4(g[0], g[1], g[2], g[3]));
+        }
+        __builtin_amdgcn_wave_barrier();                            // (a wave's LDS accesses stay in order)
+        // ---- weight gradients: contractions over the 16 samples
+        const bf16x4 dot = get(DOT, 0), xt = get(XT, 0);
+        bf16x4 d2t[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            d2t[t] = get(D2T, t * 16);
+            gw3[t] = mfma(get(H2T, t * 16), dot, gw3[t]);           // dW3[hid][o] = sum_s H2[s][hid] dO[s][o]
+            gw1[t] = mfma(xt, get(D1T, t * 16), gw1[t]);            // dW1[f][h] = sum_s X[s][f] dZ1[s][h]
+        }
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {                            // dW2[h1][h2] = sum_s H1[s][h1] dZ2[s][h2]
+            const bf16x4 h = get(H1T, mt * 16);
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) gw2[mt * 4 + nt] = mfma(h, d2t[nt], gw2[mt * 4 + nt]);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    // ---- the waves' gradients, in theta order: waves 2, 3 into LDS, added by
+    // waves 0, 1; wave 1's into LDS, added by wave 0, which writes the partial
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            gb1[t][i] = row_sum(gb1[t][i]);
+            gb2[t][i] = row_sum(gb2[t][i]);
+        }
+    gb30 = row_sum(gb30);
+    gb31 = row_sum(gb31);
+    sq = row_sum(sq);
+    auto each = [&](auto &&f) __attribute__((always_inline)) {                                     // value = f(theta index, value), all this lane holds
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int m = mt * 16 + 4 * q + i;
+                if (4 * q + i < kIn) gw1[mt][i] = f(kOffW1 + (4 * q + i) * kH + mt * 16 + r, gw1[mt][i]);
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt)
+                    gw2[mt * 4 + nt][i] = f(kOffW2 + m * kH + nt * 16 + r, gw2[mt * 4 + nt][i]);
+                if (r < kOut) gw3[mt][i] = f(kOffW3 + m * kOut + r, gw3[mt][i]);
+                if (r == 0) gb1[mt][i] = f(kOffB1 + m, gb1[mt][i]);
+                if (r == 0) gb2[mt][i] = f(kOffB2 + m, gb2[mt][i]);
+            }
+        if (lane == 0) {
+            gb30 = f(kOffB3, gb30);
+            gb31 = f(kOffB3 + 1, gb31);
+            sq = f(kNPar, sq);
+        }
+    };
+    float *buf = reinterpret_cast<float *>(lds);
+    auto put_at = [&](float *b) __attribute__((always_inline)) {
+        each([&](int p, float v) __attribute__((always_inline)) { b[p] = v; return v; });
+    };
+    auto add_from = [&](const float *b) __attribute__((always_inline)) {
+        each([&](int p, float v) __attribute__((always_inline)) { return v + b[p]; });
+    };
+    __syncthreads();
+    if (wave >= 2) put_at(buf + (wave - 2) * (kNPar + 1));
+    __syncthreads();
+    if (wave < 2) add_from(buf + wave * (kNPar + 1));
+    __syncthreads();
+    if (wave == 1) put_at(buf);
+    __syncthreads();
+    if (wave == 0) {
+        add_from(buf);
+        put_at(buf);
+    }
+    __syncthreads();
+    float *part = partials + (size_t)blockIdx.x * (kNPar + 1);
+    for (int p = threadIdx.x; p <= kNPar; p += 256) part[p] = p == kNPar ? 0.5f * buf[p] * inv_n : buf[p];
+}
+
+// Sum the per-workgroup partials in a fixed order: 64 parameters per workgroup,
+// four threads each (consecutive quarters of the partials, added in LDS).
+// grad (may be null) receives the gradient, loss (may be null) the loss; with
+// adam != 0 the bias-corrected Adam step (Kingma & Ba 2015; c1, c2 = 1 - beta^t)
+// is applied to theta in place.  One thread per parameter over all 64 partials
+// of a batch of 4096 was 21 workgroups waiting on 64 loads each (16.9 us; now
+// 4.2 us).
+__global__ void __launch_bounds__(256) reduce_adam_kernel(const float *__restrict__ partials, int nblk, float *grad,
+                                                          float *loss, float *theta, float *m, float *v, int adam,
+                                                          float c1, float c2, float lr, float b1, float b2, float eps)
+{
+    __shared__ float part[4][64];
+    const int j = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int p = blockIdx.x * 64 + j;
+    const int per = (nblk + 3) / 4, lo = w * per, hi = min(nblk, lo + per);
     float g = 0.0f;
-    for (int b = 0; b < nblk; ++b) g += partials[(size_t)b * (kNPar + 1) + p];
+    if (p <= kNPar) {
+#pragma unroll 16
+        for (int b = lo; b < hi; ++b) g += partials[(size_t)b * (kNPar + 1) + p];
+    }
+    part[w][j] = g;
+    __syncthreads();
+    if (w != 0 || p > kNPar) return;
+    g = ((part[0][j] + part[1][j]) + part[2][j]) + part[3][j];
     if (p == kNPar) {
         if (loss) *loss = g;
         return;
@@ -384,7 +508,6 @@ __global__ void reduce_adam_kernel(const float *__restrict__ partials, int nblk,
         const float vv = b2 * v[p] + (1.0f - b2) * g * g;
         m[p] = mm;
         v[p] = vv;
-        const float c1 = 1.0f - powf(b1, (float)t), c2 = 1.0f - powf(b2, (float)t);
         theta[p] -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
     }
 }
