@@ -6,7 +6,7 @@
 //
 // Three kernels, FP64 throughout (a few thousand shell cells and the zones
 // inside the inner boundary: negligible next to a sweep):
-//   iono_fac_kernel    one thread per shell cell: J = curl B' at the zone
+//   iono_fac_kernel    eight lanes per shell cell: J = curl B' at the zone
 //                      centres around the point where the cell's field line
 //                      crosses r_fac (central differences, trilinear
 //                      interpolation), its component along the dipole, and
@@ -42,6 +42,7 @@ struct IonoArgs {
     double r_shell, r_fac, theta_c, dth, dph, sigma;
     double *jr;                        // [2][nt][nph] radial current density at the shell
     double *phi;                       // [2][nt][nph] shell potential
+    double *jr_out, *phi_out;          // the caller's copies of both (may be null)
     double *pole;                      // [2] mean of the first ring (value at the pole)
     double r_inner2;
     int box[6];                        // i0, i1, j0, j1, k0, k1 (half-open)
@@ -99,12 +100,15 @@ __device__ inline void iono_curl(const IonoArgs &a, int i, int j, int k, double 
     J[2] = dBy_dx - dBx_dy;
 }
 
+// Eight lanes per cell, one for each zone centre around the cell's point at
+// r_fac (one thread per cell read its 96 field values one curl after the other
+// on 16 CUs: 21 us for 2 x 32 x 64 cells, now 13 us).
 template <typename T>
-__global__ void __launch_bounds__(256) iono_fac_kernel(IonoArgs a)
+__global__ void __launch_bounds__(64) iono_fac_kernel(IonoArgs a)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
     const int ncell = a.nt * a.nph;
-    if (t >= 2 * ncell) return;
+    const int t = (int)(blockIdx.x * 64 + threadIdx.x) >> 3, corner = threadIdx.x & 7;
+    if (t >= 2 * ncell) return;                       // (a cell's eight lanes leave together)
     const int h = t / ncell, q = t - h * ncell, k = q / a.nph, j = q - k * a.nph;
     const double th = (k + 0.5) * a.dth, ph = (j + 0.5) * a.dph;
     const double sgn = h == 0 ? 1.0 : -1.0;
@@ -121,22 +125,24 @@ __global__ void __launch_bounds__(256) iono_fac_kernel(IonoArgs a)
     const int i0 = iono_locate(a.xc, a.nx, P[0], wx);
     const int j0 = iono_locate(a.yc, a.ny, P[1], wy);
     const int k0 = iono_locate(a.zc, a.nz, P[2], wz);
-    double JP[3] = {0.0, 0.0, 0.0};
-    for (int dk = 0; dk < 2; ++dk)
-        for (int dj = 0; dj < 2; ++dj)
-            for (int di = 0; di < 2; ++di) {
-                const double wt = (di ? wx : 1.0 - wx) * (dj ? wy : 1.0 - wy) * (dk ? wz : 1.0 - wz);
-                double J[3];
-                iono_curl<T>(a, i0 + di, j0 + dj, k0 + dk, J);
-                for (int d = 0; d < 3; ++d) JP[d] += wt * J[d];
-            }
+    const int di = corner & 1, dj = (corner >> 1) & 1, dk = corner >> 2;
+    const double wt = (di ? wx : 1.0 - wx) * (dj ? wy : 1.0 - wy) * (dk ? wz : 1.0 - wz);
+    double JP[3];
+    iono_curl<T>(a, i0 + di, j0 + dj, k0 + dk, JP);
+    for (int d = 0; d < 3; ++d) {
+        JP[d] *= wt;
+        for (int o = 1; o < 8; o <<= 1) JP[d] += __shfl_xor(JP[d], o);
+    }
+    if (corner != 0) return;
     double BP[3], Bs[3];
     iono_dipole(a, P[0], P[1], P[2], BP);
     iono_dipole(a, a.r_shell * rs[0], a.r_shell * rs[1], a.r_shell * rs[2], Bs);
     const double nP = sqrt(BP[0] * BP[0] + BP[1] * BP[1] + BP[2] * BP[2]);
     const double ns = sqrt(Bs[0] * Bs[0] + Bs[1] * Bs[1] + Bs[2] * Bs[2]);
     const double jpar = (JP[0] * BP[0] + JP[1] * BP[1] + JP[2] * BP[2]) / nP;
-    a.jr[t] = jpar * (ns / nP) * (Bs[0] * rs[0] + Bs[1] * rs[1] + Bs[2] * rs[2]) / ns;
+    const double jr = jpar * (ns / nP) * (Bs[0] * rs[0] + Bs[1] * rs[1] + Bs[2] * rs[2]) / ns;
+    a.jr[t] = jr;
+    if (a.jr_out) a.jr_out[t] = jr;
 }
 
 // One workgroup per hemisphere: the potential on the cap by a direct solve.
@@ -148,14 +154,17 @@ __global__ void __launch_bounds__(256) iono_fac_kernel(IonoArgs a)
 //   cN_k P_{k-1} + cS_k P_{k+1} - (cN_k + cS_k + 2 b_k (1 - cos(2 pi m / n_phi))) P_k = F_k
 // (cN_0 = 0 at the pole; for the last ring cS is the edge term on the
 // diagonal alone, Phi = 0 half a cell outside), solved by elimination; the
-// inverse transform gives Phi.  LDS: the complex right-hand side / solution
-// [n_theta][n_phi] (re, im), the Thomas factors [n_phi][n_theta], the
-// per-ring coefficients and the twiddles.
+// inverse transform gives Phi.  The right-hand side is real, so the modes m and
+// n_phi - m are conjugate and half of them are solved.  LDS: the complex
+// right-hand side / solution [n_theta][n_phi] (re, im), the Thomas factors
+// [n_phi][n_theta], the per-ring coefficients and the twiddles.  2 x 32 x 64
+// cells: 59 us with every mode, an integer remainder per term and three
+// divisions per row of the elimination, 32 us now.
 __global__ void __launch_bounds__(kIonoThreads) iono_solve_kernel(IonoArgs a)
 {
     extern __shared__ __align__(16) double sm[];
     const int h = blockIdx.x;
-    const int nt = a.nt, nph = a.nph, N = nt * nph;
+    const int nt = a.nt, nph = a.nph, N = nt * nph, nm = nph / 2 + 1;
     double *re = sm, *im = sm + N;                     // [k][m]
     double *cp = sm + 2 * N;                           // Thomas factors [m][k]
     double *cS = cp + N, *cN = cS + nt, *cB = cN + nt;
@@ -179,30 +188,31 @@ __global__ void __launch_bounds__(kIonoThreads) iono_solve_kernel(IonoArgs a)
     }
     __syncthreads();
     // forward transform along longitude: F[k][m] = sum_j src[k][j] e^{-2 pi i m j / n_phi}
-    for (int q = tid; q < N; q += nthr) {
-        const int k = q / nph, m = q - k * nph;
+    for (int q = tid; q < nt * nm; q += nthr) {
+        const int k = q / nm, m = q - k * nm;
         double sr = 0.0, si = 0.0;
-        for (int j = 0; j < nph; ++j) {
-            const int t = (m * j) % nph;
+        for (int j = 0, t = 0; j < nph; ++j) {            // t = m j mod n_phi
             sr += src[k * nph + j] * tc[t];
             si -= src[k * nph + j] * ts[t];
+            t += m;
+            t -= t >= nph ? nph : 0;
         }
-        re[q] = sr;
-        im[q] = si;
+        re[k * nph + m] = sr;
+        im[k * nph + m] = si;
     }
     __syncthreads();
     // one tridiagonal system per mode (the same real matrix for both parts)
-    for (int m = tid; m < nph; m += nthr) {
+    for (int m = tid; m < nm; m += nthr) {
         const double lam = 2.0 * (1.0 - tc[m]);
         double prev_c = 0.0, prev_r = 0.0, prev_i = 0.0;
         for (int k = 0; k < nt; ++k) {
             const double diag = -(cN[k] + cS[k] + cB[k] * lam);
             const double lower = cN[k];                       // coefficient of P_{k-1}
             const double upper = k + 1 < nt ? cS[k] : 0.0;    // of P_{k+1}
-            const double den = diag - lower * prev_c;
-            const double c = upper / den;
-            const double r = (re[k * nph + m] - lower * prev_r) / den;
-            const double i = (im[k * nph + m] - lower * prev_i) / den;
+            const double inv = 1.0 / (diag - lower * prev_c);
+            const double c = upper * inv;
+            const double r = (re[k * nph + m] - lower * prev_r) * inv;
+            const double i = (im[k * nph + m] - lower * prev_i) * inv;
             cp[m * nt + k] = c;
             re[k * nph + m] = r;
             im[k * nph + m] = i;
@@ -222,12 +232,17 @@ __global__ void __launch_bounds__(kIonoThreads) iono_solve_kernel(IonoArgs a)
     for (int q = tid; q < N; q += nthr) {
         const int k = q / nph, j = q - k * nph;
         double s = 0.0;
-        for (int m = 0; m < nph; ++m) {
-            const int t = (m * j) % nph;
+        for (int m = 1, t = j; 2 * m < nph; ++m) {        // t = m j mod n_phi
             s += re[k * nph + m] * tc[t] - im[k * nph + m] * ts[t];
+            t += j;
+            t -= t >= nph ? nph : 0;
         }
-        src[q] = s / nph;
-        out[q] = s / nph;
+        s = re[k * nph] + 2.0 * s;
+        if ((nph & 1) == 0) s += (j & 1) ? -re[k * nph + nph / 2] : re[k * nph + nph / 2];
+        s /= nph;
+        src[q] = s;
+        out[q] = s;
+        if (a.phi_out) a.phi_out[(size_t)h * N + q] = s;
     }
     __syncthreads();
     if (tid == 0) {
@@ -276,7 +291,7 @@ __device__ inline bool iono_phi_at(const IonoArgs &a, const double *pos, double 
     return true;
 }
 
-__global__ void __launch_bounds__(256) iono_drift_kernel(IonoArgs a)
+__global__ void __launch_bounds__(64) iono_drift_kernel(IonoArgs a)
 {
     const int bi = a.box[1] - a.box[0], bj = a.box[3] - a.box[2], bk = a.box[5] - a.box[4];
     const long long nb = (long long)bi * bj * bk;
@@ -289,14 +304,15 @@ __global__ void __launch_bounds__(256) iono_drift_kernel(IonoArgs a)
     const int idx[3] = {i, j, k}, n[3] = {a.nx, a.ny, a.nz};
     const double *cs[3] = {a.xc, a.yc, a.zc};
     bool ok = pos[0] * pos[0] + pos[1] * pos[1] + pos[2] * pos[2] < a.r_inner2;
-    double E[3] = {0.0, 0.0, 0.0};
+    double E[3] = {0.0, 0.0, 0.0}, f0;
+    ok = ok && iono_phi_at(a, pos, f0);               // (zero inside the shell)
     for (int d = 0; d < 3 && ok; ++d) {
         if (idx[d] == 0 || idx[d] == n[d] - 1) { ok = false; break; }
         double pp[3] = {pos[0], pos[1], pos[2]}, pm[3] = {pos[0], pos[1], pos[2]};
         pp[d] = cs[d][idx[d] + 1];
         pm[d] = cs[d][idx[d] - 1];
-        double fp, fm, f0;
-        if (!iono_phi_at(a, pp, fp) || !iono_phi_at(a, pm, fm) || !iono_phi_at(a, pos, f0)) { ok = false; break; }
+        double fp, fm;
+        if (!iono_phi_at(a, pp, fp) || !iono_phi_at(a, pm, fm)) { ok = false; break; }
         E[d] = -(fp - fm) / (pp[d] - pm[d]);
     }
     if (ok) {

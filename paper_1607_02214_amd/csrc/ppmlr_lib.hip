@@ -540,9 +540,13 @@ ppmlr_status sweep_typed(ppmlr_ctx *c, const T *in, T *u, hipStream_t st, double
                          bool fuse)
 {
     const int nseg = seg_count(c, axis, (int)sizeof(T));
+    int P = 0;
     if (nseg == 1) {
+        // (pencils of one chunk are a tile of whole pencils, whose kernel sets up
+        // less: 32^3 FP64, 20 steps 661 us against 688 us)
         const March &m = march_plan(c, axis, (int)sizeof(T));
-        if (m.P > 0) {
+        if (m.C == 1) P = m.P;
+        else if (m.P > 0) {
             ppmlr::SweepArgs<T> a;
             fill_args(c, a, in, u, axis, dt, dt_dev, m.P, 1);
             a.L = m.L;
@@ -555,7 +559,7 @@ ppmlr_status sweep_typed(ppmlr_ctx *c, const T *in, T *u, hipStream_t st, double
             return march_axis<2, T>(c, a, m.SM, st, fuse);
         }
     }
-    const int P = pick_tile(c, axis, (int)sizeof(T));
+    if (P == 0) P = pick_tile(c, axis, (int)sizeof(T));
     const int M = tile_M(c, axis, (int)sizeof(T));
     if (block_threads(P, M) > 1024 || ppmlr::lds_bytes(kSlotsA + kSlotsB, P * M, (int)sizeof(T), P) > 160 * 1024)
         return fail(c, PPMLR_EINVAL, "tile does not fit one workgroup");
@@ -668,7 +672,7 @@ struct CflArgs {
     const T *u;
     int nx, ny, nz;
     long long vol;
-    const double *dx, *dy, *dz, *xc, *yc, *zc;
+    const double *rdx, *rdy, *rdz, *xc, *yc, *zc;   // 1 / width, centres
     double gamma, p_floor, r_inner2;
     int has_inner;
     double dip_m, dir[3], bext[3];
@@ -694,67 +698,120 @@ __device__ inline void bg64(double dip_m, const double *dir, const double *bext,
     }
 }
 
-// Signal speed of zone z outside the inner boundary (0 inside): max_a
-// (|v_a| + c_f,a) / dx_a in FP64.
-template <typename T>
-__device__ inline double cfl_zone(const CflArgs<T> &a, long long z)
+// Largest value of a wave's lanes.
+__device__ inline float wave_max(float v)
 {
-    int i = (int)(z % a.nx);
-    int j = (int)((z / a.nx) % a.ny);
-    int k = (int)(z / ((long long)a.nx * a.ny));
-    double x = a.xc[i], y = a.yc[j], zz = a.zc[k];
-    if (a.has_inner && x * x + y * y + zz * zz < a.r_inner2) return 0.0;
-    double r = (double)a.u[z];
-    double vx = (double)a.u[a.vol + z] / r, vy = (double)a.u[2 * a.vol + z] / r, vz = (double)a.u[3 * a.vol + z] / r;
-    double px = (double)a.u[4 * a.vol + z], py = (double)a.u[5 * a.vol + z], pz = (double)a.u[6 * a.vol + z];
-    double p = (a.gamma - 1.0) * ((double)a.u[7 * a.vol + z] - 0.5 * r * (vx * vx + vy * vy + vz * vz) -
-                                  0.5 * (px * px + py * py + pz * pz));
-    if (p < a.p_floor) p = a.p_floor;
-    double bx, by, bz;
-    bg64(a.dip_m, a.dir, a.bext, x, y, zz, bx, by, bz);
-    bx += px; by += py; bz += pz;
-    double a2 = a.gamma * p / r;
-    double b2 = (bx * bx + by * by + bz * bz) / r;
-    double w[3] = {a.dx[i], a.dy[j], a.dz[k]};
-    double v[3] = {vx, vy, vz};
-    double B[3] = {bx, by, bz};
+    for (int off = 32; off > 0; off >>= 1) v = __builtin_fmaxf(v, __shfl_xor(v, off));
+    return v;
+}
+
+// Signal-speed maximum of the rows of zones along x that wave `wave` of `nw`
+// takes, outside the inner boundary: max_a (|v_a| + c_f,a) / dx_a in FP64, with
+// c_f,a the fast speed along axis a.  Most zones are far from the maximum, and
+// c_f,a <= sqrt(a^2 + b^2): a wave whose lanes' bounds all lie at or below a
+// value that it has reached skips the three fast speeds (six FP64 square
+// roots).  The maximum is the same.  Rows are addressed without divisions per
+// zone; grids narrower than a wave put several rows on one.  256x192x192 FP32:
+// 149 us with a grid-stride loop over zones and every speed, 84 us now (a copy of
+// the same bytes takes 62 us).
+template <typename T>
+__device__ inline double cfl_rows(const CflArgs<T> &a, int wave, int nw)
+{
+    const int lane = (int)__lane_id();
+    int shift = 6;                                       // lanes per row: 64, or the power of two that holds nx
+    while (shift > 0 && (1 << (shift - 1)) >= a.nx) --shift;
+    const int sub = lane >> shift, i0 = lane & ((1 << shift) - 1), per = 64 >> shift, step = 1 << shift;
+    const int rows = a.ny * a.nz;
     double smax = 0.0;
-    for (int c = 0; c < 3; ++c) {
-        double ba2 = B[c] * B[c] / r;
-        double disc = (a2 + b2) * (a2 + b2) - 4.0 * a2 * ba2;
-        disc = disc > 0.0 ? disc : 0.0;
-        double cf = __builtin_sqrt(0.5 * (a2 + b2 + __builtin_sqrt(disc)));
-        double s = (__builtin_fabs(v[c]) + cf) / w[c];
-        smax = s > smax ? s : smax;
+    float reached = -1.0f;                               // a lower bound of the wave's maximum so far
+    for (int row0 = wave * per; row0 < rows; row0 += nw * per) {
+        const int row = min(row0 + sub, rows - 1);
+        const int k = row / a.ny, j = row - k * a.ny;
+        const double y = a.yc[j], z = a.zc[k], iy = a.rdy[j], iz = a.rdz[k];
+        for (int ii = 0; ii < a.nx; ii += step) {
+            const int i = min(ii + i0, a.nx - 1);
+            const double x = a.xc[i], ix = a.rdx[i];
+            const T *u = a.u + ((long long)row * a.nx + i);
+            const double r = (double)u[0];
+            const double m0 = (double)u[a.vol], m1 = (double)u[2 * a.vol], m2 = (double)u[3 * a.vol];
+            const double px = (double)u[4 * a.vol], py = (double)u[5 * a.vol], pz = (double)u[6 * a.vol];
+            const double e = (double)u[7 * a.vol];
+            const double ir = 1.0 / r;
+            const double vx = m0 * ir, vy = m1 * ir, vz = m2 * ir;
+            double p = (a.gamma - 1.0) * (e - 0.5 * r * (vx * vx + vy * vy + vz * vz) - 0.5 * (px * px + py * py + pz * pz));
+            if (p < a.p_floor) p = a.p_floor;
+            double bx, by, bz;
+            bg64(a.dip_m, a.dir, a.bext, x, y, z, bx, by, bz);
+            bx += px; by += py; bz += pz;
+            const double a2 = a.gamma * p * ir;
+            const double b2 = (bx * bx + by * by + bz * bz) * ir;
+            const double s2 = a2 + b2;
+            const bool masked = a.has_inner && x * x + y * y + z * z < a.r_inner2;
+            // (rounded up: the conversions and the square root are good to 1e-7;
+            // 1e-36 stands for what single precision loses near zero)
+            const float c = __builtin_amdgcn_sqrtf((float)s2 + 1e-36f);
+            const float bound = 1.000001f * __builtin_fmaxf(((float)__builtin_fabs(vx) + c) * (float)ix,
+                                                 __builtin_fmaxf(((float)__builtin_fabs(vy) + c) * (float)iy,
+                                                                 ((float)__builtin_fabs(vz) + c) * (float)iz));
+            // (no bound that is not finite counts, nor a maximum next to zero; a
+            // c that is not a number may be lost in the maximum and is tested too)
+            const bool below = bound <= reached && reached > 1e-30f && bound <= 3.0e38f && c <= 3.0e38f;
+            if (__any(!masked && !below)) {
+                const double v[3] = {vx, vy, vz}, B[3] = {bx, by, bz}, iw[3] = {ix, iy, iz};
+                double s = 0.0;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    double disc = s2 * s2 - 4.0 * a2 * (B[q] * B[q] * ir);
+                    disc = disc > 0.0 ? disc : 0.0;
+                    const double cf = __builtin_sqrt(0.5 * (s2 + __builtin_sqrt(disc)));
+                    const double sp = (__builtin_fabs(v[q]) + cf) * iw[q];
+                    s = sp > s ? sp : s;
+                }
+                if (!masked && s > smax) smax = s;
+                reached = wave_max((float)smax) * 0.999999f;
+            }
+        }
     }
     return smax;
 }
 
-// Signal-speed maximum over all zones outside the inner boundary: per zone
-// cfl_zone; wave shuffles, then one atomic per workgroup on the bits of the
-// (non-negative) double.
-template <typename T>
-__global__ void __launch_bounds__(256) cfl_kernel(const CflArgs<T> a)
+// The workgroup's maximum of smax (red: one double per wave), in thread 0.
+__device__ inline double block_max(double smax, double *red)
 {
-    __shared__ double red[4];
-    double smax = 0.0;
-    for (long long z = (long long)blockIdx.x * blockDim.x + threadIdx.x; z < a.vol;
-         z += (long long)gridDim.x * blockDim.x) {
-        const double s = cfl_zone(a, z);
-        smax = s > smax ? s : smax;
-    }
     for (int off = 32; off > 0; off >>= 1) {
         double o = __shfl_xor(smax, off);
         smax = o > smax ? o : smax;
     }
     if (__lane_id() == 0) red[threadIdx.x >> 6] = smax;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double m = red[0];
-        for (int w = 1; w < 4; ++w) m = red[w] > m ? red[w] : m;
+    double m = red[0];
+    if (threadIdx.x == 0)
+        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = red[w] > m ? red[w] : m;
+    return m;
+}
+
+// Signal-speed maximum over all zones outside the inner boundary: one atomic
+// per workgroup on the bits of the (non-negative) double.
+template <typename T>
+__global__ void __launch_bounds__(256) cfl_kernel(const CflArgs<T> a)
+{
+    __shared__ double red[4];
+    const double m = block_max(cfl_rows(a, (int)(blockIdx.x * 4 + (threadIdx.x >> 6)), (int)gridDim.x * 4), red);
+    if (threadIdx.x == 0)
         atomicMax(a.out + (blockIdx.x % ppmlr::kCflSlots) * ppmlr::kCflStride,
                   (unsigned long long)__double_as_longlong(m));
-    }
+}
+
+// ... of every member of an ensemble (one row of workgroups each)
+template <typename T>
+__global__ void __launch_bounds__(256) ens_cfl_kernel(const CflArgs<T> *args)
+{
+    __shared__ double red[4];
+    const CflArgs<T> a = args[blockIdx.y];
+    const double m = block_max(cfl_rows(a, (int)(blockIdx.x * 4 + (threadIdx.x >> 6)), (int)gridDim.x * 4), red);
+    if (threadIdx.x == 0)
+        atomicMax(a.out + (blockIdx.x % ppmlr::kCflSlots) * ppmlr::kCflStride,
+                  (unsigned long long)__double_as_longlong(m));
 }
 
 // Maximum of the signal-speed slots (one wave; the bits of non-negative
@@ -869,12 +926,22 @@ __global__ void __launch_bounds__(256) totals_partial(const T *u, long long vol,
     if (threadIdx.x < 8) partials[blockIdx.x * 8 + threadIdx.x] = red[threadIdx.x][0];
 }
 
-__global__ void totals_final(const double *partials, int nblocks, double *out)
+// (256 threads: 32 for each variable, each over a consecutive part of the
+// blocks, then their sums in index order)
+__global__ void __launch_bounds__(256) totals_final(const double *partials, int nblocks, double *out)
 {
+    __shared__ double part[32][8];
+    const int v = threadIdx.x & 7, w = threadIdx.x >> 3;
+    const int per = (nblocks + 31) / 32, lo = w * per, hi = min(nblocks, lo + per);
+    double s = 0.0;
+#pragma unroll 8
+    for (int b = lo; b < hi; ++b) s += partials[b * 8 + v];
+    part[w][v] = s;
+    __syncthreads();
     if (threadIdx.x < 8) {
-        double s = 0.0;
-        for (int b = 0; b < nblocks; ++b) s += partials[b * 8 + threadIdx.x];
-        out[threadIdx.x] = s;
+        double t = 0.0;
+        for (int k = 0; k < 32; ++k) t += part[k][threadIdx.x];
+        out[threadIdx.x] = t;
     }
 }
 
@@ -885,7 +952,7 @@ CflArgs<T> cfl_args(const ppmlr_ctx *c, const T *u)
     a.u = u;
     a.nx = c->n[0]; a.ny = c->n[1]; a.nz = c->n[2];
     a.vol = (long long)a.nx * a.ny * a.nz;
-    a.dx = c->tab[0].dxi64; a.dy = c->tab[1].dxi64; a.dz = c->tab[2].dxi64;
+    a.rdx = c->tab[0].rdx64; a.rdy = c->tab[1].rdx64; a.rdz = c->tab[2].rdx64;
     a.xc = c->tab[0].xci64; a.yc = c->tab[1].xci64; a.zc = c->tab[2].xci64;
     a.gamma = c->gamma;
     a.p_floor = c->opt.p_floor;
@@ -897,12 +964,19 @@ CflArgs<T> cfl_args(const ppmlr_ctx *c, const T *u)
     return a;
 }
 
+// Workgroups of four waves that take every row of zones (or rows, where several
+// fit a wave) once.
+long long cfl_blocks(const ppmlr_ctx *c)
+{
+    const int per = c->n[0] > 32 ? 1 : (c->n[0] > 16 ? 2 : 4);
+    return ((long long)c->n[1] * c->n[2] + 4 * per - 1) / (4 * per);
+}
+
 template <typename T>
 ppmlr_status cfl_typed(ppmlr_ctx *c, const T *u, hipStream_t st)
 {
     const CflArgs<T> a = cfl_args(c, u);
-    long long blocks = (a.vol + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
+    const long long blocks = std::min<long long>(cfl_blocks(c), 2048);
     hipLaunchKernelGGL(cfl_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, st, a);
     return hip_check(c, hipGetLastError(), "cfl launch");
 }
@@ -1222,15 +1296,17 @@ ppmlr_status ppmlr_ionosphere_couple(ppmlr_ctx *c, const ppmlr_state *s, const p
         if (e) return e;
         c->inner_v_bytes = vneed;
     }
+    a.jr_out = jr;
+    a.phi_out = phi;
     a.jr = c->d_iono;
     a.phi = c->d_iono + 2 * N;
     a.pole = c->d_iono + 4 * N;
     a.v = c->d_inner_v;
-    const unsigned fac_blocks = (unsigned)((2 * N + 255) / 256);
+    const unsigned fac_blocks = (unsigned)((8 * 2 * N + 63) / 64);      // eight lanes per cell
     if (s->dtype == PPMLR_F64)
-        hipLaunchKernelGGL(ppmlr::iono_fac_kernel<double>, dim3(fac_blocks), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(ppmlr::iono_fac_kernel<double>, dim3(fac_blocks), dim3(64), 0, st, a);
     else
-        hipLaunchKernelGGL(ppmlr::iono_fac_kernel<float>, dim3(fac_blocks), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(ppmlr::iono_fac_kernel<float>, dim3(fac_blocks), dim3(64), 0, st, a);
     e = hip_check(c, hipGetLastError(), "ionosphere current launch");
     if (e) return e;
     if (lds > 64 * 1024) {
@@ -1243,13 +1319,10 @@ ppmlr_status ppmlr_ionosphere_couple(ppmlr_ctx *c, const ppmlr_state *s, const p
     e = hip_check(c, hipGetLastError(), "ionosphere potential launch");
     if (e) return e;
     if (nb > 0) {
-        hipLaunchKernelGGL(ppmlr::iono_drift_kernel, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(ppmlr::iono_drift_kernel, dim3((unsigned)((nb + 63) / 64)), dim3(64), 0, st, a);
         e = hip_check(c, hipGetLastError(), "ionosphere drift launch");
         if (e) return e;
     }
-    if (jr) e = hip_check(c, hipMemcpyAsync(jr, a.jr, sizeof(double) * 2 * N, hipMemcpyDeviceToDevice, st), "hipMemcpyAsync");
-    if (!e && phi)
-        e = hip_check(c, hipMemcpyAsync(phi, a.phi, sizeof(double) * 2 * N, hipMemcpyDeviceToDevice, st), "hipMemcpyAsync");
     if (!e) e = hip_check(c, hipStreamSynchronize(st), "hipStreamSynchronize");
     if (e) return e;
     for (int q = 0; q < 6; ++q) c->inner_box[q] = a.box[q];
@@ -1421,7 +1494,7 @@ ppmlr_status ppmlr_totals(ppmlr_ctx *c, const ppmlr_state *s, double out[8])
     else
         hipLaunchKernelGGL(totals_partial<float>, dim3(kTotBlocks), dim3(256), 0, st, (const float *)s->u, vol,
                            c->n[0], c->n[1], c->tab[0].dxi64, c->tab[1].dxi64, c->tab[2].dxi64, c->d_partials);
-    hipLaunchKernelGGL(totals_final, dim3(1), dim3(64), 0, st, c->d_partials, kTotBlocks, c->d_partials + 8 * kTotBlocks);
+    hipLaunchKernelGGL(totals_final, dim3(1), dim3(256), 0, st, c->d_partials, kTotBlocks, c->d_partials + 8 * kTotBlocks);
     e = hip_check(c, hipGetLastError(), "totals launch");
     if (!e) e = hip_check(c, hipMemcpyAsync(out, c->d_partials + 8 * kTotBlocks, sizeof(double) * 8,
                                             hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
@@ -1635,6 +1708,12 @@ __global__ void ens_dt_kernel(unsigned long long *const *smax_bits, double *cons
     *t[m] += d;
 }
 
+// The members' signal-speed slots cleared (one wave per member).
+__global__ void ens_clear_kernel(unsigned long long *const *smax_bits)
+{
+    smax_bits[blockIdx.x][threadIdx.x * ppmlr::kCflStride] = 0ull;
+}
+
 // Device work tables of one ensemble call: the sweep descriptors (3 axes x 2
 // buffer parities x members), the tile offsets (3 axes x (members + 1)), the
 // per-member signal-speed / dt / time pointers (3 x members), the members'
@@ -1741,11 +1820,7 @@ __global__ void __launch_bounds__(SM) ensemble_persistent_kernel(const PersistAr
     // start-of-call signal-speed maximum of every member
     for (int m = 0; m < n; ++m) {
         const CflArgs<T> &ca = p.cfla[m];
-        double smax = 0.0;
-        for (long long z = (long long)b * SM + threadIdx.x; z < ca.vol; z += (long long)G * SM) {
-            const double s = cfl_zone(ca, z);
-            smax = s > smax ? s : smax;
-        }
+        double smax = cfl_rows(ca, b * (SM / 64) + (int)(threadIdx.x >> 6), (int)G * (SM / 64));
         for (int off = 32; off > 0; off >>= 1) {
             double o = __shfl_xor(smax, off);
             smax = o > smax ? o : smax;
@@ -1929,11 +2004,9 @@ ppmlr_status ensemble_typed(ppmlr_ctx *const *ctxs, const ppmlr_state *const *st
         up(d_desc, desc.data(), sizeof(ppmlr::SweepArgs<T>) * desc.size());
         up(d_mo, mo.data(), sizeof(int) * mo.size());
         up(d_ptr, ptr.data(), sizeof(void *) * ptr.size());
-        if (persistent) {
-            for (int m = 0; m < n; ++m) cfla[m] = cfl_args(ctxs[m], (const T *)states[m]->u);
-            up(d_cfl, cfla.data(), sizeof(CflArgs<T>) * cfla.size());
-            up(d_bar, bar0.data(), sizeof(unsigned int) * bar0.size());
-        }
+        for (int m = 0; m < n; ++m) cfla[m] = cfl_args(ctxs[m], (const T *)states[m]->u);
+        up(d_cfl, cfla.data(), sizeof(CflArgs<T>) * cfla.size());
+        if (persistent) up(d_bar, bar0.data(), sizeof(unsigned int) * bar0.size());
         // the host tables must stay alive until the copies have been made
         if (!err) err = hip_check(c0, hipStreamSynchronize(st), "hipStreamSynchronize");
     }
@@ -1999,10 +2072,18 @@ ppmlr_status ensemble_typed(ppmlr_ctx *const *ctxs, const ppmlr_state *const *st
             err = fail(c0, PPMLR_EDEVICE, "ensemble kernel: a grid barrier wait gave up (workgroups not co-resident?)");
         j = 3LL * steps;
     }
-    // one launch per sweep: the start-of-call maximum, then per step the dt
-    // kernel and three sweep kernels
-    if (!persistent)
-        for (int m = 0; m < n && !err; ++m) err = cfl_launch(ctxs[m], states[m]);
+    // one launch per sweep: the start-of-call maximum of all members, then per
+    // step the dt kernel and three sweep kernels
+    if (!persistent && !err) {
+        long long rows = 1;
+        for (int m = 0; m < n; ++m) rows = std::max(rows, cfl_blocks(ctxs[m]));
+        const unsigned gx = (unsigned)std::min<long long>(rows, std::max(64, 2048 / n));
+        hipLaunchKernelGGL(ens_clear_kernel, dim3(n), dim3(ppmlr::kCflSlots), 0, st, (unsigned long long *const *)d_ptr);
+        for (int m0 = 0; m0 < n; m0 += 65535)
+            hipLaunchKernelGGL(ens_cfl_kernel<T>, dim3(gx, (unsigned)std::min(n - m0, 65535)), dim3(256), 0, st,
+                               d_cfl + m0);
+        err = hip_check(c0, hipGetLastError(), "ensemble cfl launch");
+    }
     static const int even[3] = {0, 1, 2}, odd[3] = {2, 1, 0};
     for (int s = 0; s < steps && !err && !persistent; ++s) {
         hipLaunchKernelGGL(ens_dt_kernel, dim3(n), dim3(ppmlr::kCflSlots), 0, st, (unsigned long long *const *)d_ptr,
