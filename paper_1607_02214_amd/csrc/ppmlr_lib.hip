@@ -428,6 +428,31 @@ size_t march_lds(const ppmlr_ctx *c, int axis, int P, int SM, int elem)
            (c->bc_hi[axis] == PPMLR_PERIODIC ? ppmlr::lds_wrap_bytes(P, elem) : 0);
 }
 
+// The march of P pencils of N zones in C chunks; P = 0 where the last chunk would
+// be empty, a chunk shorter than 14 zones (but for a single one), or its zones
+// and carries more than 4 waves or max_slots LDS slots per row.
+March march_shape(int N, int P, int C, int max_slots)
+{
+    March m;
+    m.L = (N + kG + C - 1) / C;
+    if ((C > 1 && m.L < 2 * kG) || (C - 1) * m.L >= N + kG) return m;
+    m.M = m.L + kG;
+    const int slots = P * (m.M + ppmlr::kCarry);
+    m.SM = slots <= 128 ? 128 : (slots + 63) / 64 * 64;
+    if (block_threads(P, m.M) > 256 || m.SM > max_slots) return m;
+    m.C = C;
+    m.P = P;
+    return m;
+}
+
+// How much a y or z sweep is slowed by rows of w 4-byte words (see march_search).
+double row_cost(int axis, int w, bool cached)
+{
+    if (axis == 0) return 1.0;
+    if (cached) return w >= 4 ? 1.0 : (w == 3 ? 1.1 : (w == 2 ? 1.15 : 1.7));
+    return w >= 8 ? 1.0 : (w == 4 ? (axis == 1 ? 1.03 : 1.25) : (w > 4 ? 1.12 : (w == 3 ? 1.2 : (w == 2 ? 1.35 : 1.8))));
+}
+
 // The march for whole pencils along axis, with P pencils per workgroup (0:
 // chosen), or none (P = 0): the learned and harvest modes keep whole-pencil
 // tiles, and so does an explicit P that no chunk of four waves holds.
@@ -454,33 +479,19 @@ March march_search(const ppmlr_ctx *c, int axis, int elem, int P_req)
     const bool cached = 8.0 * c->n[0] * c->n[1] * c->n[2] * elem < 128e6;
     double best_t = 1e300;
     for (int P = P_req > 0 ? P_req : 1; P <= (P_req > 0 ? P_req : 8); ++P) {
-        for (int C = 1; C <= N + kG; ++C) {
-            March m;
-            m.P = P;
-            m.C = C;
-            m.L = (N + kG + C - 1) / C;
-            m.M = m.L + kG;
-            if (C > 1 && m.L < 2 * kG) break;
-            if ((C - 1) * m.L >= N + kG) continue;                     // the last chunk would be empty
-            const int waves = block_threads(P, m.M) / 64, slots = P * (m.M + ppmlr::kCarry);
-            if (waves > 4) continue;
-            m.SM = slots <= 128 ? 128 : (slots + 63) / 64 * 64;
-            if (m.SM > 320) continue;
+        for (int C = 1; C <= 64 && (C == 1 || (N + kG) / C >= kG); ++C) {
+            const March m = march_shape(N, P, C, 320);
+            if (m.P == 0) continue;
+            const int waves = block_threads(P, m.M) / 64;
             const size_t lds = (march_lds(c, axis, P, m.SM, elem) + 1279) / 1280 * 1280;
             const double per_cu = std::min((int)(160 * 1024 / lds), 4 * wps / waves);
             const double wgs = (double)((nq + P - 1) / P) * nr, rounds = wgs / (256.0 * per_cu);
-            double row = 1.0;
-            if (axis != 0) {
-                const int w = elem == 4 ? P : 2 * P;
-                if (cached) row = w >= 4 ? 1.0 : (w == 3 ? 1.1 : (w == 2 ? 1.15 : 1.7));
-                else row = w >= 8 ? 1.0 : (w == 4 ? (axis == 1 ? 1.03 : 1.25) : (w > 4 ? 1.12 : (w == 3 ? 1.2 : (w == 2 ? 1.35 : 1.8))));
-            }
+            const double row = row_cost(axis, P * elem / 4, cached);
             // (a last round that is not full takes a round's time; with many
             // rounds workgroups follow each other and it is less)
             const double t = rounds <= 1.0 ? C * row * (t0 + t1 * waves * std::ceil(wgs / 256.0))
                                            : C * row * (t0 + t1 * waves * per_cu) * (rounds + 0.2);
             if (t < best_t - 1e-9) { best_t = t; best = m; }
-            if (C > 64) break;
         }
     }
     return best;
@@ -535,6 +546,17 @@ ppmlr_status march_axis(ppmlr_ctx *c, const ppmlr::SweepArgs<T> &a, int SM, hipS
     return fuse ? launch_march<AX, T, true, false>(c, a, SM, st) : launch_march<AX, T, false, false>(c, a, SM, st);
 }
 
+// A sweep's arguments as a march.
+template <typename T>
+void set_march(ppmlr::SweepArgs<T> &a, int axis, const March &m)
+{
+    a.L = m.L;
+    a.M = m.M;
+    a.nchunk = m.C;
+    a.S = m.P * m.M;
+    a.inv_div = 1.0f / (float)(axis == 0 ? m.M : m.P);
+}
+
 template <typename T>
 ppmlr_status sweep_typed(ppmlr_ctx *c, const T *in, T *u, hipStream_t st, double dt, const double *dt_dev, int axis,
                          bool fuse)
@@ -549,11 +571,7 @@ ppmlr_status sweep_typed(ppmlr_ctx *c, const T *in, T *u, hipStream_t st, double
         else if (m.P > 0) {
             ppmlr::SweepArgs<T> a;
             fill_args(c, a, in, u, axis, dt, dt_dev, m.P, 1);
-            a.L = m.L;
-            a.M = m.M;
-            a.nchunk = m.C;
-            a.S = m.P * m.M;
-            a.inv_div = 1.0f / (float)(axis == 0 ? m.M : m.P);
+            set_march(a, axis, m);
             if (axis == 0) return march_axis<0, T>(c, a, m.SM, st, fuse);
             if (axis == 1) return march_axis<1, T>(c, a, m.SM, st, fuse);
             return march_axis<2, T>(c, a, m.SM, st, fuse);
@@ -1906,6 +1924,29 @@ __global__ void __launch_bounds__(SM) ensemble_persistent_kernel(const PersistAr
     }
 }
 
+// Workgroup and LDS stride of an ensemble's marching sweeps, the same for all
+// members: 4 waves; 5 workgroups per CU in FP32, 3 in FP64.
+constexpr int kEnsMarchBlock = 256;
+constexpr int ens_march_stride(int elem) { return elem == 4 ? 320 : 256; }
+
+// The march of one ensemble member along axis: the least time of its chunks,
+// which all cost about what a full workgroup does (idle lanes save little).
+March ens_march(const ppmlr_ctx *c, int axis, int elem)
+{
+    const int N = c->n[axis], nq = axis == 0 ? c->n[1] : c->n[0];
+    March best;
+    double best_t = 1e300;
+    for (int P = 1; P <= 8; ++P)
+        for (int C = 1; C <= 64; ++C) {
+            const March m = march_shape(N, P, C, ens_march_stride(elem));
+            if (m.P == 0) continue;
+            const double t = (double)((nq + P - 1) / P) * C * (block_threads(P, m.M) / 64 + 1) *
+                             row_cost(axis, P * elem / 4, false);
+            if (t < best_t - 1e-9) { best_t = t; best = m; }
+        }
+    return best;
+}
+
 template <typename T>
 struct EnsTables {
     static constexpr size_t up256(size_t b) { return (b + 255) / 256 * 256; }
@@ -1956,25 +1997,50 @@ ppmlr_status ensemble_typed(ppmlr_ctx *const *ctxs, const ppmlr_state *const *st
     std::vector<ppmlr::SweepArgs<T>> desc((size_t)6 * n);
     std::vector<int> mo((size_t)3 * (n + 1));
     bool stats = false;
+    // Axes that no member cuts into segments are swept by marches (whole pencils
+    // in chunks, in place), whatever the block size: one launch of 256 lanes
+    // (32 members of 96^3 to 160^3, FP32, four steps: 43.6 ms as whole-pencil
+    // tiles of 512 lanes, 36.9 ms; 43.4 ms with the tiles of all members dealt
+    // out to the XCDs as one list).  The persistent launch has no registers for
+    // them and keeps tiles.
+    bool march[3];
+    int pmax = 1;
+    bool periodic = false;
+    std::vector<March> plan((size_t)3 * n);
     for (int ax = 0; ax < 3; ++ax) {
-        long long off = 0;
+        march[ax] = !persistent;
+        for (int m = 0; m < n && march[ax]; ++m) {
+            plan[(size_t)ax * n + m] = ens_march(ctxs[m], ax, (int)sizeof(T));
+            march[ax] = seg_count(ctxs[m], ax, (int)sizeof(T)) == 1 && plan[(size_t)ax * n + m].P > 0;
+            pmax = std::max(pmax, plan[(size_t)ax * n + m].P);
+            periodic = periodic || ctxs[m]->bc_hi[ax] == PPMLR_PERIODIC;
+        }
+    }
+    for (int ax = 0; ax < 3; ++ax) {
+        long long off = 0, total = 0;
         for (int m = 0; m < n; ++m) {
             ppmlr_ctx *c = ctxs[m];
             if (c->opt.collect_stats) stats = true;
             const int nseg = seg_count(c, ax, (int)sizeof(T));
             const int M = tile_M(c, ax, (int)sizeof(T));
             const int nq = (ax == 0) ? c->n[1] : c->n[0];
-            const int P = std::max(1, std::min(block / M, nq));
+            const March &mp = plan[(size_t)ax * n + m];
+            const int P = march[ax] ? mp.P : std::max(1, std::min(block / M, nq));
             T *home = (T *)states[m]->u, *pong = (T *)c->d_pong;
             for (int par = 0; par < 2; ++par) {
                 const T *in = (pp[m] && par) ? pong : home;
                 T *out = pp[m] ? (par ? home : pong) : home;
-                fill_args(c, desc[((size_t)ax * 2 + par) * n + m], in, out, ax, 0.0, c->d_dt, P, nseg);
+                ppmlr::SweepArgs<T> &d = desc[((size_t)ax * 2 + par) * n + m];
+                fill_args(c, d, in, out, ax, 0.0, c->d_dt, P, nseg);
+                if (march[ax]) set_march(d, ax, mp);
             }
             mo[(size_t)ax * (n + 1) + m] = (int)off;
-            off += (long long)desc[(size_t)ax * 2 * n + m].ntiles * nseg;
+            // (the per-sweep launch counts the tiles of one XCD's share)
+            const long long tiles = (long long)desc[(size_t)ax * 2 * n + m].ntiles * nseg;
+            off += persistent ? tiles : (tiles + 7) / 8;
+            total += tiles;
         }
-        if (off > (long long)INT_MAX / 2) return fail(c0, PPMLR_EINVAL, "ensemble too large for one launch");
+        if (total > (long long)INT_MAX / 2) return fail(c0, PPMLR_EINVAL, "ensemble too large for one launch");
         mo[(size_t)ax * (n + 1) + n] = (int)off;
     }
     ppmlr_status err = PPMLR_OK;
@@ -2095,17 +2161,30 @@ ppmlr_status ensemble_typed(ppmlr_ctx *const *ctxs, const ppmlr_state *const *st
             e.desc = d_desc + ((size_t)ax * 2 + (size_t)(j & 1)) * n;
             e.mo = d_mo + (size_t)ax * (n + 1);
             e.members = n;
-            e.total = mo[(size_t)ax * (n + 1) + n];
-            e.per_xcd = (e.total + 7) / 8;
+            e.per_xcd = mo[(size_t)ax * (n + 1) + n];
             const dim3 grid(8 * e.per_xcd);
-            auto launch = [&](auto kern) {
-                if (lds > 64 * 1024) {
+            auto launch_as = [&](auto kern, int threads, size_t bytes) {
+                if (bytes > 64 * 1024) {
                     hipError_t he = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                        (int)lds);
+                                                        (int)bytes);
                     if (he != hipSuccess) { err = hip_check(c0, he, "hipFuncSetAttribute"); return; }
                 }
-                hipLaunchKernelGGL(kern, grid, dim3(block), lds, st, e);
+                hipLaunchKernelGGL(kern, grid, dim3(threads), bytes, st, e);
             };
+            if (march[ax]) {
+                constexpr int SM = ens_march_stride((int)sizeof(T));
+                const size_t bytes = ppmlr::lds_bytes(kSlotsA + kSlotsB, SM, (int)sizeof(T), pmax) +
+                                     (periodic ? ppmlr::lds_wrap_bytes(pmax, (int)sizeof(T)) : 0);
+#define PPMLR_ENSM(AX_)                                                                                                \
+                if (k == 2) launch_as(ppmlr::ensemble_sweep_kernel<AX_, T, true, true, SM, true>, kEnsMarchBlock, bytes); \
+                else launch_as(ppmlr::ensemble_sweep_kernel<AX_, T, true, false, SM, true>, kEnsMarchBlock, bytes);
+                if (ax == 0) { PPMLR_ENSM(0) } else if (ax == 1) { PPMLR_ENSM(1) } else { PPMLR_ENSM(2) }
+#undef PPMLR_ENSM
+                if (!err) err = hip_check(c0, hipGetLastError(), "ensemble sweep launch");
+                ++j;
+                continue;
+            }
+            auto launch = [&](auto kern) { launch_as(kern, block, lds); };
 #define PPMLR_ENS3(AX_, B_)                                                                              \
             if (stats) { if (k == 2) launch(ppmlr::ensemble_sweep_kernel<AX_, T, true, true, B_>);         \
                          else launch(ppmlr::ensemble_sweep_kernel<AX_, T, true, false, B_>); }             \

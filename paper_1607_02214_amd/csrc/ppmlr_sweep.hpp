@@ -1385,9 +1385,10 @@ __global__ void __launch_bounds__(SM > 0 ? SM : 1024)
 // ---------------------------------------------------------------------------
 // Batched ensemble sweep: one launch performs the same sweep (one axis) of
 // every member of an ensemble of independent runs (different sizes, inflows
-// and dt).  The tiles of all members are concatenated in member order
-// (mo[m] = first tile of member m, mo[members] = total) and dealt out with the
-// same XCD-aware order as the single-run kernel.  Each member's geometry, dt
+// and dt).  Every member's tiles are dealt out to the eight XCDs in equal
+// shares of adjacent tiles, and an XCD takes the members one after the other:
+// members' tiles differ in their work (a march of one chunk, or of six), so an
+// even share of all tiles is not one of the work.  Each member's geometry, dt
 // pointer, signal-speed slot and counters are in its own descriptor, so a
 // member's arithmetic is exactly that of a single-run sweep with the same
 // tiles (and segments: a segmented member reads one state and writes the
@@ -1396,27 +1397,38 @@ __global__ void __launch_bounds__(SM > 0 ? SM : 1024)
 template <typename T>
 struct EnsembleSweepArgs {
     const SweepArgs<T> *desc;      // [members]: this axis's descriptor of each member
-    const int *mo;                 // [members + 1]: tile offsets
-    int members, total, per_xcd;
+    const int *mo;                 // [members + 1]: first tile of each member in an XCD's share
+    int members, per_xcd;          // per_xcd = mo[members]
 };
 
-template <int AX, typename T, bool STATS, bool FUSE_CFL, int SM>
-__global__ void __launch_bounds__(SM) __attribute__((amdgpu_waves_per_eu(sweep_waves<T>(SM, kGuessPlain, false))))
+// The largest m below members with mo[m] <= j (mo ascends from mo[0] = 0): 64
+// members per load, one per lane, where a bisection would wait for as many
+// loads as it takes steps.  All lanes of the wave must be active.
+__device__ inline int member_of(const int *mo, int members, int j)
+{
+    const int lane = threadIdx.x & 63;
+    int m = -1;
+    for (int i = 0; i < members; i += 64) {
+        const int k = min(i + lane, members - 1);
+        m += __popcll(__ballot(i + lane < members && mo[k] <= j));
+    }
+    return m;
+}
+
+template <int AX, typename T, bool STATS, bool FUSE_CFL, int SM, bool MARCH = false>
+__global__ void __launch_bounds__(SM) __attribute__((amdgpu_waves_per_eu(sweep_waves<T>(SM, kGuessPlain, false, MARCH))))
     ensemble_sweep_kernel(const EnsembleSweepArgs<T> e)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int b = blockIdx.x;
-    const int j = (b & 7) * e.per_xcd + (b >> 3);
-    if (j >= e.total) return;
-    int lo = 0, hi = e.members - 1;               // largest m with mo[m] <= j
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (e.mo[mid] <= j) lo = mid; else hi = mid - 1;
-    }
+    const int j = b >> 3;
+    const int lo = member_of(e.mo, e.members, j);
     const SweepArgs<T> &a = e.desc[lo];
     double *s_red = reinterpret_cast<double *>(smem_raw);
     unsigned int *s_stat = reinterpret_cast<unsigned int *>(smem_raw + 16 * sizeof(double));
-    const int t = j - e.mo[lo];
+    const int share = e.mo[lo + 1] - e.mo[lo];
+    const int t = (b & 7) * share + (j - e.mo[lo]);
+    if (t >= a.ntiles * a.nseg) return;
     int seg, tt;                                  // as in the single-run order
     if (a.seg_fast) { seg = t % a.nseg; tt = t / a.nseg; }
     else { seg = t / a.ntiles; tt = t - seg * a.ntiles; }
@@ -1424,7 +1436,16 @@ __global__ void __launch_bounds__(SM) __attribute__((amdgpu_waves_per_eu(sweep_w
     const int r = tt / a.tiles_q;
     const T dt = a.dt_dev ? T(*a.dt_dev) : a.dt;
     unsigned long long *cm = a.cfl_max ? a.cfl_max + (b % kCflSlots) * kCflStride : nullptr;
-    sweep_tile<AX, T, STATS, FUSE_CFL, SM>(a, tq, r, seg, dt, cm, b % kStatSlots, smem_raw, s_red, s_stat);
+    if constexpr (MARCH) {
+        // (the descriptor as constant memory: each chunk reads it again, by
+        // scalar loads)
+        typedef const __attribute__((address_space(4))) SweepArgs<T> desc_t;
+        const desc_t &da = *(desc_t *)&a;
+        sweep_tile<AX, T, STATS, FUSE_CFL, SM, kGuessPlain, false, true>(da, tq, r, seg, dt, cm, b % kStatSlots, smem_raw,
+                                                                         s_red, s_stat);
+    } else {
+        sweep_tile<AX, T, STATS, FUSE_CFL, SM>(a, tq, r, seg, dt, cm, b % kStatSlots, smem_raw, s_red, s_stat);
+    }
 }
 
 }  // namespace ppmlr

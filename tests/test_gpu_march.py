@@ -95,3 +95,23 @@ def test_march_in_a_graph():
             ctx.sweep(ref, dt, axis)
         torch.cuda.synchronize()
         assert torch.equal(u, ref)
+
+
+# An ensemble's marches: members of one chunk and of many, fewer tiles than
+# XCDs, periodic and other ends together, more members than lanes of a wave;
+# with one member cut into segments, its axis goes by tiles for all.
+@pytest.mark.parametrize("dtype,cut", [(torch.float32, False), (torch.float64, False), (torch.float32, True)])
+def test_march_of_an_ensemble(dtype, cut):
+    from paper_1607_02214_amd import ppmlr
+    kinds = [_case("smooth", (14, 18, 16), 0), _case("blast", (171, 19, 67), 0), _case("smooth", (43, 8, 93), 0),
+             _case("dipole", (64, 43, 28), 0)]
+    want = [_run(c, dtype, 2) for c in kinds]
+    pick = [0] * 35 + [1, 3, 2] + [0] * 29 + [2, 1, 3]
+    ctxs = [kinds[k].context() for k in pick]
+    us = [torch.from_numpy(kinds[k].U).to("cuda", dtype).contiguous() for k in pick]
+    if cut:
+        ctxs[36].set_segments(1, 3)
+    ppmlr.ensemble_run(ctxs, us, 3, 0.4)
+    for k, c, u in zip(pick, ctxs, us):
+        ref, st, t = want[k]
+        assert torch.equal(u, ref) and c.time(u) == t and c.stats() == st
