@@ -63,8 +63,8 @@ struct ppmlr_ctx {
     int tile[3] = {0, 0, 0};
     int seg[3] = {0, 0, 0};                  // segments per pencil (0: automatic)
     int seg_order[3] = {0, 0, 0};            // tile order of segments (0: automatic, 1: adjacent, 2: bands)
-    March march[3][2];                       // march per axis and precision (FP32, FP64), for march_req
-    int march_req[3][2] = {{-1, -1}, {-1, -1}, {-1, -1}};   // pencils asked for when it was chosen (-1: not yet)
+    March march[3][3];                       // march per axis and kind (FP32, FP64, FP32 learned), for march_req
+    int march_req[3][3] = {{-1, -1, -1}, {-1, -1, -1}, {-1, -1, -1}};   // pencils asked for when it was chosen (-1: not yet)
     void *d_pong = nullptr;                  // second state for segmented sweeps
     size_t pong_bytes = 0;
     int device = 0;
@@ -422,9 +422,15 @@ ppmlr_status launch_axis(ppmlr_ctx *c, const ppmlr::SweepArgs<T> &a, hipStream_t
     return fuse ? launch_sm<AX, T, false, true>(c, a, st) : launch_sm<AX, T, false, false>(c, a, st);
 }
 
+// Whether FP32 sweeps of this context take the learned guess.
+bool learned_f32(const ppmlr_ctx *c, int elem)
+{
+    return elem == 4 && c->guess == PPMLR_GUESS_LEARNED && c->opt.tracing == PPMLR_TRACE_TWO_FAMILY;
+}
+
 size_t march_lds(const ppmlr_ctx *c, int axis, int P, int SM, int elem)
 {
-    return ppmlr::lds_bytes(kSlotsA + kSlotsB, SM, elem, P) +
+    return ppmlr::lds_bytes((learned_f32(c, elem) ? ppmlr::kSlotsAGuess : kSlotsA) + kSlotsB, SM, elem, P) +
            (c->bc_hi[axis] == PPMLR_PERIODIC ? ppmlr::lds_wrap_bytes(P, elem) : 0);
 }
 
@@ -473,7 +479,7 @@ March march_search(const ppmlr_ctx *c, int axis, int elem, int P_req)
     const bool trace = c->opt.tracing == PPMLR_TRACE_CHARACTERISTIC;
     const int N = c->n[axis], nq = axis == 0 ? c->n[1] : c->n[0];
     const double nr = axis == 2 ? c->n[1] : c->n[2];
-    const int wps = elem == 4 ? (trace ? 4 : 5) : (trace ? 2 : 3);     // waves per SIMD (registers)
+    const int wps = elem == 4 ? (trace || learned_f32(c, elem) ? 4 : 5) : (trace ? 2 : 3);     // waves per SIMD (registers)
     const double t0 = elem == 4 ? (trace ? 5.0 : 4.5) : 4.2;           // us of a chunk alone, and per wave on its CU
     const double t1 = elem == 4 ? (trace ? 0.22 : 0.155) : (trace ? 0.78 : 0.52);
     const bool cached = 8.0 * c->n[0] * c->n[1] * c->n[2] * elem < 128e6;
@@ -500,8 +506,8 @@ March march_search(const ppmlr_ctx *c, int axis, int elem, int P_req)
 const March &march_plan(ppmlr_ctx *c, int axis, int elem)
 {
     static const March none;
-    if (c->opt.tracing == PPMLR_TRACE_TWO_FAMILY && elem == 4 && c->guess != PPMLR_GUESS_PLAIN) return none;
-    const int f = elem == 8 ? 1 : 0;
+    if (c->opt.tracing == PPMLR_TRACE_TWO_FAMILY && elem == 4 && c->guess == PPMLR_GUESS_HARVEST) return none;
+    const int f = elem == 8 ? 1 : (learned_f32(c, elem) ? 2 : 0);
     if (c->march_req[axis][f] != c->tile[axis]) {
         c->march[axis][f] = march_search(c, axis, elem, c->tile[axis]);
         c->march_req[axis][f] = c->tile[axis];
@@ -509,12 +515,12 @@ const March &march_plan(ppmlr_ctx *c, int axis, int elem)
     return c->march[axis][f];
 }
 
-template <int AX, typename T, bool FUSE, int SM, bool TRACE>
+template <int AX, typename T, bool FUSE, int SM, bool TRACE, int GUESS>
 ppmlr_status launch_march_sm(ppmlr_ctx *c, const ppmlr::SweepArgs<T> &a, hipStream_t st)
 {
     // (counters are always collected in the kernel, and not stored without a buffer)
     const size_t lds = march_lds(c, AX, a.P, SM, (int)sizeof(T));
-    auto kern = ppmlr::sweep_kernel<AX, T, true, FUSE, SM, ppmlr::kGuessPlain, TRACE, true>;
+    auto kern = ppmlr::sweep_kernel<AX, T, true, FUSE, SM, GUESS, TRACE, true>;
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return hip_check(c, e, "hipFuncSetAttribute");
@@ -523,14 +529,14 @@ ppmlr_status launch_march_sm(ppmlr_ctx *c, const ppmlr::SweepArgs<T> &a, hipStre
     return hip_check(c, hipGetLastError(), "sweep launch");
 }
 
-template <int AX, typename T, bool FUSE, bool TRACE>
+template <int AX, typename T, bool FUSE, bool TRACE, int GUESS = ppmlr::kGuessPlain>
 ppmlr_status launch_march(ppmlr_ctx *c, const ppmlr::SweepArgs<T> &a, int SM, hipStream_t st)
 {
     switch (SM) {
-    case 128: return launch_march_sm<AX, T, FUSE, 128, TRACE>(c, a, st);
-    case 192: return launch_march_sm<AX, T, FUSE, 192, TRACE>(c, a, st);
-    case 256: return launch_march_sm<AX, T, FUSE, 256, TRACE>(c, a, st);
-    case 320: return launch_march_sm<AX, T, FUSE, 320, TRACE>(c, a, st);
+    case 128: return launch_march_sm<AX, T, FUSE, 128, TRACE, GUESS>(c, a, st);
+    case 192: return launch_march_sm<AX, T, FUSE, 192, TRACE, GUESS>(c, a, st);
+    case 256: return launch_march_sm<AX, T, FUSE, 256, TRACE, GUESS>(c, a, st);
+    case 320: return launch_march_sm<AX, T, FUSE, 320, TRACE, GUESS>(c, a, st);
     default: return fail(c, PPMLR_EINVAL, "no march of this stride");
     }
 }
@@ -542,6 +548,11 @@ ppmlr_status march_axis(ppmlr_ctx *c, const ppmlr::SweepArgs<T> &a, int SM, hipS
         if (c->guess != PPMLR_GUESS_PLAIN)
             return fail(c, PPMLR_EINVAL, "the characteristic mode takes the plain interface solve");
         return fuse ? launch_march<AX, T, true, true>(c, a, SM, st) : launch_march<AX, T, false, true>(c, a, SM, st);
+    }
+    if constexpr (sizeof(T) == 4) {
+        if (c->guess == PPMLR_GUESS_LEARNED)
+            return fuse ? launch_march<AX, T, true, false, ppmlr::kGuessLearned>(c, a, SM, st)
+                        : launch_march<AX, T, false, false, ppmlr::kGuessLearned>(c, a, SM, st);
     }
     return fuse ? launch_march<AX, T, true, false>(c, a, SM, st) : launch_march<AX, T, false, false>(c, a, SM, st);
 }
@@ -2405,6 +2416,10 @@ ppmlr_status ppmlr_ensemble_autotune(ppmlr_ctx *const *ctxs, const ppmlr_state *
         const int B = cands[cand / 5], len = lens[cand % 5];
         set_lengths(len);
         if (ensemble_check(ctxs, tptr.data(), n, reps, cfl, B) != PPMLR_OK) continue;
+        // (whole pencils march, whatever the block: the usual one is tried if it may be)
+        if (len == 0 && B != 512 && g_ensemble_launch == PPMLR_ENSEMBLE_PER_SWEEP &&
+            ensemble_check(ctxs, tptr.data(), n, reps, cfl, 512) == PPMLR_OK)
+            continue;
         e = hip_check(ctxs[0], hipEventRecord(t0, st), "hipEventRecord");
         if (!e) e = ppmlr_ensemble_run(ctxs, tptr.data(), n, reps, cfl, B, nullptr);
         if (!e) e = hip_check(ctxs[0], hipEventRecord(t1, st), "hipEventRecord");

@@ -50,16 +50,18 @@ __device__ __forceinline__ unsigned short f2bf(float f)
 }
 __device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float((unsigned int)h << 16); }
 
-// four FP32 -> BF16 (round to nearest even, as f2bf), two per instruction
-__device__ __forceinline__ bf16x4 pack4(float a, float b, float c, float d)
+// two FP32 -> BF16 in one instruction (round to nearest even, as f2bf; a in the
+// lower half)
+__device__ __forceinline__ unsigned int pack2(float a, float b)
 {
     typedef float f2 __attribute__((ext_vector_type(2)));
     typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
-    const f2 ab = {a, b}, cd = {c, d};
-    const u2 r = {__builtin_bit_cast(unsigned int, __builtin_convertvector(ab, b2)),
-                  __builtin_bit_cast(unsigned int, __builtin_convertvector(cd, b2))};
-    return __builtin_bit_cast(bf16x4, r);
+    const f2 ab = {a, b};
+    return __builtin_bit_cast(unsigned int, __builtin_convertvector(ab, b2));
+}
+__device__ __forceinline__ bf16x4 pack4(float a, float b, float c, float d)
+{
+    return __builtin_bit_cast(bf16x4, make_uint2(pack2(a, b), pack2(c, d)));
 }
 
 __device__ __forceinline__ f32x4 mfma(bf16x4 a, bf16x4 b, f32x4 c)
@@ -124,53 +126,47 @@ __device__ __forceinline__ bf16x4 load_frag(const unsigned short *frag, int t, i
     return *reinterpret_cast<const bf16x4 *>(frag + ((size_t)t * 64 + lane) * 4);
 }
 
-// Forward pass of one wave over 64 samples.  F: BF16 features, row-major
-// [64][16] (columns 14, 15 zero), in LDS.  Writes the two outputs of sample s
-// to out[s * ldo + o] (lanes 0..15 hold them).  Must be called by all 64
-// lanes of the wave.  The 64 samples are taken as four tiles of 16, one after
-// the other, so that only one tile's activations are live (this runs inside
-// the sweep, next to the solver's own registers); the weight fragments are
-// re-read per tile from the L2-resident packed buffer.
-__device__ __forceinline__ void forward_wave(const unsigned short *F, const unsigned short *frag,
-                                             const float *__restrict__ theta, float *out, int ldo)
+// Forward pass of one wave over 16 samples.  f0, f1: BF16 features 4q .. 4q + 3
+// (q = lane / 16; columns 14, 15 zero) of sample lane mod 16, the lower one in
+// the lower half.  Returns output 0 (the pressure) of that sample in lanes
+// 0..15.  Must be called by all 64 lanes of the wave.  Only one tile's
+// activations are live (this runs inside the sweep, next to the solver's own
+// registers); the weight fragments are re-read per tile from the L2-resident
+// packed buffer.
+__device__ __forceinline__ float forward_tile(unsigned int f0, unsigned int f1, const unsigned short *frag,
+                                              const float *__restrict__ theta)
 {
     const int lane = threadIdx.x & 63;
-    const int r = lane & 15, q = lane >> 4;
+    const int q = lane >> 4;
     const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 1
-    for (int st = 0; st < 4; ++st) {
-        // keeps the weight loads inside the loop (not hoisted into registers)
-        asm volatile("" ::: "memory");
-        const bf16x4 xb = *reinterpret_cast<const bf16x4 *>(F + (st * 16 + r) * 16 + 4 * q);
-        // layer 1: Z1^T[64 x 16] = W1^T[64 x 16] X^T[16 x 16]
-        bf16x4 h1[4];
+    // keeps the weight loads inside the caller's loop (not hoisted into registers)
+    asm volatile("" ::: "memory");
+    const bf16x4 xb = __builtin_bit_cast(bf16x4, make_uint2(f0, f1));
+    // layer 1: Z1^T[64 x 16] = W1^T[64 x 16] X^T[16 x 16]
+    bf16x4 h1[4];
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            const f32x4 z = mfma(load_frag(frag, kTA1 + mt, lane), xb, zero);
-            const float *b1 = theta + kOffB1 + mt * 16 + 4 * q;
-            h1[mt] = pack4(gelu(z[0] + b1[0]), gelu(z[1] + b1[1]), gelu(z[2] + b1[2]), gelu(z[3] + b1[3]));
-        }
-        // layer 2: Z2^T = W2^T H1^T (weight loads kept per output tile, so
-        // that at most four fragments are in flight)
-        bf16x4 h2[4];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            asm volatile("" ::: "memory");
-            f32x4 acc = zero;
-#pragma unroll
-            for (int kt = 0; kt < 4; ++kt) acc = mfma(load_frag(frag, kTA2 + mt * 4 + kt, lane), h1[kt], acc);
-            const float *b2 = theta + kOffB2 + mt * 16 + 4 * q;
-            h2[mt] = pack4(gelu(acc[0] + b2[0]), gelu(acc[1] + b2[1]), gelu(acc[2] + b2[2]), gelu(acc[3] + b2[3]));
-        }
-        // layer 3: O^T[16 x 16] = W3^T[16 x 64] H2^T (rows 0, 1 valid)
-        f32x4 o = zero;
-#pragma unroll
-        for (int kt = 0; kt < 4; ++kt) o = mfma(load_frag(frag, kTA3 + kt, lane), h2[kt], o);
-        if (q == 0) {
-            out[(st * 16 + r) * ldo + 0] = o[0] + theta[kOffB3];
-            out[(st * 16 + r) * ldo + 1] = o[1] + theta[kOffB3 + 1];
-        }
+    for (int mt = 0; mt < 4; ++mt) {
+        const f32x4 z = mfma(load_frag(frag, kTA1 + mt, lane), xb, zero);
+        const float *b1 = theta + kOffB1 + mt * 16 + 4 * q;
+        h1[mt] = pack4(gelu(z[0] + b1[0]), gelu(z[1] + b1[1]), gelu(z[2] + b1[2]), gelu(z[3] + b1[3]));
     }
+    // layer 2: Z2^T = W2^T H1^T (weight loads kept per output tile, so
+    // that at most four fragments are in flight)
+    bf16x4 h2[4];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+        asm volatile("" ::: "memory");
+        f32x4 acc = zero;
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) acc = mfma(load_frag(frag, kTA2 + mt * 4 + kt, lane), h1[kt], acc);
+        const float *b2 = theta + kOffB2 + mt * 16 + 4 * q;
+        h2[mt] = pack4(gelu(acc[0] + b2[0]), gelu(acc[1] + b2[1]), gelu(acc[2] + b2[2]), gelu(acc[3] + b2[3]));
+    }
+    // layer 3: O^T[16 x 16] = W3^T[16 x 64] H2^T (rows 0, 1 valid)
+    f32x4 o = zero;
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) o = mfma(load_frag(frag, kTA3 + kt, lane), h2[kt], o);
+    return o[0] + theta[kOffB3];
 }
 
 // Fragment of tile t of the packed set for this lane, from the FP32 parameters.

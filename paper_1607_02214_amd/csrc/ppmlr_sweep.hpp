@@ -353,10 +353,9 @@ __device__ inline void wave_hist(unsigned int *s_hist, bool counted, int bin)
 
 // Inputs of the learned guess for one face (see the Riemann block of
 // sweep_tile): sides s = (rho, u, v_t1, v_t2, B_t1, B_t2, P), normalised by
-// the pair means.  Returns whether the face is selected (strong pressure or
-// velocity jump); Pbar and cbar are the mean pressure and sqrt(P/rho).
+// the pair means; Pbar and cbar are the mean pressure and sqrt(P/rho).
 template <typename T>
-__device__ inline bool guess_features(const T *L, const T *R, T gate_p, T gate_u, T *feat, T &Pbar, T &cbar)
+__device__ inline void guess_features(const T *L, const T *R, T *feat, T &Pbar, T &cbar)
 {
     const T rbar = T(0.5) * (L[0] + R[0]);
     Pbar = T(0.5) * (L[6] + R[6]);
@@ -377,7 +376,14 @@ __device__ inline bool guess_features(const T *L, const T *R, T gate_p, T gate_u
         f[5] = x[5] * ibs;
         f[6] = x[6] * iPb;
     }
-    return tabs(R[6] - L[6]) > gate_p * tmin(L[6], R[6]) || tabs(R[1] - L[1]) > gate_u * cbar;
+}
+
+// Whether a face is selected: a strong jump of the pressure or the velocity.
+template <typename T>
+__device__ inline bool guess_selects(T rl, T rr, T ul, T ur, T pl, T pr, T gate_p, T gate_u)
+{
+    const T cbar = Ar<T>::sqrt_(T(0.5) * (pl + pr) * Ar<T>::rcp(T(0.5) * (rl + rr)));
+    return tabs(pr - pl) > gate_p * tmin(pl, pr) || tabs(ur - ul) > gate_u * cbar;
 }
 
 // One tile of a sweep, executed by one workgroup: P pencils, each cut to
@@ -847,58 +853,61 @@ __device__ __forceinline__ void sweep_tile(const ARGS &args, const int tq, const
 
     // ------------------------------------------------------------ R4
     // face i+1/2 between this zone (L) and zone i+1 (R)
-    // Learned guess: faces with a strong jump are compacted per workgroup into
-    // buffer B (free until the fluxes are written) and run through the network
-    // 64 at a time on the matrix cores.  This pass comes before the solver's
-    // right states are loaded, so that they do not occupy registers next to
-    // the network's; they are read again from LDS below.
-    bool lg_gate = false, lg_have = false;   // selected; network output available
+    // Learned guess: faces with a strong jump are compacted per workgroup and run
+    // through the network 16 at a time on the matrix cores, the waves taking
+    // tiles of 16 in turn (tiles of 64 left three of four waves waiting at the
+    // barrier where a workgroup has a few such faces).  The list is in rows 9..15 of
+    // buffer A (the edges, read in R3), seven words of two features each in
+    // lane order, so that there is a place for every lane; the network's answer
+    // takes row 9.  256x192x192 dipole, gates 0.1, one sweep, x / y / z: 997 /
+    // 544 / 586 us as whole-pencil tiles with the list in buffer B, tiles of 64
+    // and the features formed by every wave; 431 / 356 / 359 us as marches.
+    // This pass comes before the solver's right states are
+    // loaded, so that they do not occupy registers next to the network's; they
+    // are read again from LDS below.
+    bool lg_gate = false;                    // selected
     T lg_y = T(0), lg_Pbar = T(1);
     if constexpr (GUESS == kGuessLearned) {
-        constexpr int kCap = ((8 * SM * (int)sizeof(T)) / 40) / 64 * 64;
         const int lane = tid & 63;
-        unsigned short *F = reinterpret_cast<unsigned short *>(sB);
-        float *Yo = reinterpret_cast<float *>(F + kCap * 16);
+        unsigned int *F = reinterpret_cast<unsigned int *>(sA + 9 * S);
+        auto column = [&](int n) -> int {                 // lane n's slot
+            return n + (MARCH ? (AX == 0 ? kCarry * ((int)(((float)n + 0.5f) * a.inv_div) + 1) : kCarry * P) : 0);
+        };
         int slot = 0;
-        {
-            const T Ls[7] = {LrN, Lu, Lv1, Lv2, LT1, LT2, LPt + PdR};
-            T Rs[7];
-            if (face_ok) {
-                Rs[0] = sA[16 * S + sp1]; Rs[1] = sA[1 * S + sp1]; Rs[2] = sA[5 * S + sp1];
-                Rs[3] = sA[6 * S + sp1]; Rs[4] = sA[17 * S + sp1]; Rs[5] = sA[18 * S + sp1];
-                Rs[6] = sA[0 * S + sp1] + PdR;
-            } else {
-#pragma unroll
-                for (int k = 0; k < 7; ++k) Rs[k] = Ls[k];
-            }
-            T feat[14], cbar_;
-            lg_gate = face_ok && guess_features(Ls, Rs, a.gate_p, a.gate_u, feat, lg_Pbar, cbar_);
-            const unsigned long long bal = __ballot(lg_gate);
+        // (few waves have such a face: the others do not form the features)
+        const T PL = LPt + PdR;
+        lg_gate = face_ok && guess_selects(LrN, sA[16 * S + sp1], Lu, sA[1 * S + sp1], PL, sA[0 * S + sp1] + PdR,
+                                           a.gate_p, a.gate_u);
+        const unsigned long long bal = __ballot(lg_gate);
+        if (bal) {
             int base = 0;
-            if (lane == 0 && bal) base = (int)atomicAdd(&s_guess[0], (unsigned int)__popcll(bal));
+            if (lane == 0) base = (int)atomicAdd(&s_guess[0], (unsigned int)__popcll(bal));
             base = __shfl(base, 0);
-            slot = base + __popcll(bal & ((1ull << lane) - 1ull));
-            if (lg_gate && slot < kCap) {
-                unsigned int w[8];
+            slot = column(lg_gate ? base + __popcll(bal & ((1ull << lane) - 1ull)) : 0);
+            if (lg_gate) {
+                const T Ls[7] = {LrN, Lu, Lv1, Lv2, LT1, LT2, PL};
+                const T Rs[7] = {sA[16 * S + sp1], sA[1 * S + sp1],  sA[5 * S + sp1],      sA[6 * S + sp1],
+                                 sA[17 * S + sp1], sA[18 * S + sp1], sA[0 * S + sp1] + PdR};
+                T feat[14], cbar_;
+                guess_features(Ls, Rs, feat, lg_Pbar, cbar_);
 #pragma unroll
-                for (int k = 0; k < 7; ++k)
-                    w[k] = (unsigned int)mlp::f2bf((float)feat[2 * k]) |
-                           ((unsigned int)mlp::f2bf((float)feat[2 * k + 1]) << 16);
-                w[7] = 0u;
-                uint4 *dst = reinterpret_cast<uint4 *>(F + slot * 16);
-                dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
-                dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
+                for (int k = 0; k < 7; ++k) F[k * S + slot] = mlp::pack2(feat[2 * k], feat[2 * k + 1]);
             }
         }
         if (STATS) wave_add(&s_stat[35], lg_gate && g >= own_lo && g < gend);
         __syncthreads();
-        const int nf = min((int)s_guess[0], kCap);
-        for (int b0 = (tid >> 6) * 64; b0 < nf; b0 += (int)(blockDim.x >> 6) * 64)
-            mlp::forward_wave(F + b0 * 16, a.mlp_frag, a.mlp_theta, Yo + b0 * 2, 2);
+        const int nf = (int)s_guess[0], nw = (int)(blockDim.x >> 6);
+#pragma unroll 1
+        for (int b0 = (tid >> 6) * 16; b0 < nf; b0 += nw * 16) {
+            // sample b0 + lane mod 16; features 4 (lane / 16) .. + 3
+            const int n = b0 + (lane & 15), kq = lane >> 4;
+            const int col = column(min(n, Suse - 1));
+            const unsigned int f0 = F[2 * kq * S + col], f1 = kq < 3 ? F[(2 * kq + 1) * S + col] : 0u;
+            const float y = mlp::forward_tile(f0, f1, a.mlp_frag, a.mlp_theta);
+            if (kq == 0 && n < nf) sA[9 * S + col] = (T)y;
+        }
         __syncthreads();
-        lg_have = lg_gate && slot < kCap;
-        if (lg_have) lg_y = (T)Yo[slot * 2];
-        __syncthreads();   // buffer B is written with the fluxes next
+        if (lg_gate) lg_y = sA[9 * S + slot];
     }
     T Pst, ust, v1s, b1s, v2s, b2s;
     const T bns = T(0.5) * (bn + bnp);
@@ -961,12 +970,14 @@ __device__ __forceinline__ void sweep_tile(const ARGS &args, const int tq, const
         if (GUESS == kGuessHarvest) {
             const T Ls[7] = {LrN, Lu, Lv1, Lv2, LT1, LT2, LPt + Pd};
             const T Rs[7] = {sA[16 * S + sp1], Ru, Rv1, Rv2, sA[17 * S + sp1], sA[18 * S + sp1], RPt + Pd};
-            gate = face_ok && g >= own_lo && g < gend && guess_features(Ls, Rs, a.gate_p, a.gate_u, feat, Pbar, cbar);
+            guess_features(Ls, Rs, feat, Pbar, cbar);
+            gate = face_ok && g >= own_lo && g < gend &&
+                   guess_selects(Ls[0], Rs[0], Ls[1], Rs[1], Ls[6], Rs[6], a.gate_p, a.gate_u);
             if (STATS) wave_add(&s_stat[35], gate);
         }
         if (GUESS == kGuessLearned) {
             bool used = false;
-            if (lg_have) {
+            if (lg_gate) {
                 const T Pg = P + lg_Pbar * lg_y;
                 if (__builtin_isfinite(Pg) && Pg > Pfloor) {
                     P = Pg;
@@ -1342,9 +1353,9 @@ constexpr int sweep_waves(int SM, int GUESS, bool TRACE, bool MARCH = false)
 }
 
 // Standalone sweep: one workgroup per tile.  The learned-guess form holds
-// the network pass next to the sweep's registers (~132 VGPRs, 3 waves per
-// SIMD); a budget of 4 waves per SIMD (128 registers, a few bytes spilled
-// in the fused form) makes it ~20 % faster (measured).
+// the network pass next to the sweep's registers; a budget of 4 waves per SIMD
+// (128 registers, up to 15 values spilled in the fused march) was ~20 % faster
+// than 132 registers and 3 waves.
 template <int AX, typename T, bool STATS, bool FUSE_CFL, int SM, int GUESS = kGuessPlain, bool TRACE = false,
           bool MARCH = false>
 __global__ void __launch_bounds__(SM > 0 ? SM : 1024)

@@ -111,7 +111,31 @@ def test_march_of_an_ensemble(dtype, cut):
     us = [torch.from_numpy(kinds[k].U).to("cuda", dtype).contiguous() for k in pick]
     if cut:
         ctxs[36].set_segments(1, 3)
-    ppmlr.ensemble_run(ctxs, us, 3, 0.4)
+    ppmlr.ensemble_run(ctxs, us, 3, 0.4, block=512)     # (0 is what an autotune of the process left)
     for k, c, u in zip(pick, ctxs, us):
         ref, st, t = want[k]
         assert torch.equal(u, ref) and c.time(u) == t and c.stats() == st
+
+
+# The learned guess: its list of faces in the rows of the edges, from a few
+# faces to every lane (gate 0), against segment tiles of another lane order.
+@pytest.mark.parametrize("gate", [0.1, 0.0])
+@pytest.mark.parametrize("kind,n", [("blast", (50, 21, 68)), ("blast", (171, 19, 67)), ("smooth", (43, 69, 93))])
+def test_march_learned(kind, n, gate):
+    from paper_1607_02214_amd import ppmlr
+    case = _case(kind, n, 0)
+    theta = torch.from_numpy(I.mlp_init(2, scale=0.5)).cuda()
+    out = []
+    for segments, tile in ((2, 0), (1, 0), (1, 3)):
+        ctx = case.context()
+        for axis in range(3):
+            ctx.set_segments(axis, segments)
+            ctx.set_tile(axis, tile)
+        ctx.set_guess(ppmlr.GUESS_LEARNED, theta)
+        ctx.set_gate(gate, gate)
+        u = torch.from_numpy(case.U).to("cuda", torch.float32).contiguous()
+        ctx.advance(u, 3, 0.4)
+        out.append((u, ctx.stats(), ctx.time(u)))
+    assert out[0][1]["guess_faces"] > 0 or gate > 0
+    for u, st, t in out[1:]:
+        assert torch.equal(u, out[0][0]) and st == out[0][1] and t == out[0][2]
