@@ -58,6 +58,7 @@ struct ppmlr_ctx {
     int series_n = 0, series_cap = 0;
     double *d_inflow = nullptr;              // the current step's inflow from the series (8 values)
     double *d_partials = nullptr;            // totals partial sums
+    double *h_results = nullptr;             // pinned: results that kernels write for the host (kCflBlocks)
     int partial_blocks = 0;
     long long step = 0;
     int tile[3] = {0, 0, 0};
@@ -172,6 +173,8 @@ void free_tables(ppmlr_ctx *c)
     c->d_dt = nullptr;
     c->d_time = nullptr;
     c->d_partials = nullptr;
+    if (c->h_results) (void)hipHostFree(c->h_results);
+    c->h_results = nullptr;
 }
 
 bool has_background(const ppmlr_ctx *c)
@@ -568,9 +571,29 @@ void set_march(ppmlr::SweepArgs<T> &a, int axis, const March &m)
     a.inv_div = 1.0f / (float)(axis == 0 ? m.M : m.P);
 }
 
+// What a sweep does to the run's time and its signal-speed slots (SweepArgs):
+// advance: the first of a step; step: dt, or the CFL number with slots; clear:
+// the second of a step whose dt came from the slots.
+struct StepTime {
+    bool advance = false, slots = false, clear = false;
+    double step = 0.0;
+};
+
+template <typename T>
+void set_time(const ppmlr_ctx *c, ppmlr::SweepArgs<T> &a, const StepTime &tm)
+{
+    if (tm.advance) {
+        a.t_out = c->d_time;
+        a.step = tm.step;
+        a.dt_out = c->d_dt;
+        if (tm.slots) a.dt_slots = c->d_cflmax;
+    }
+    if (tm.clear) a.clear_slots = c->d_cflmax;
+}
+
 template <typename T>
 ppmlr_status sweep_typed(ppmlr_ctx *c, const T *in, T *u, hipStream_t st, double dt, const double *dt_dev, int axis,
-                         bool fuse)
+                         bool fuse, const StepTime &tm)
 {
     const int nseg = seg_count(c, axis, (int)sizeof(T));
     int P = 0;
@@ -583,6 +606,7 @@ ppmlr_status sweep_typed(ppmlr_ctx *c, const T *in, T *u, hipStream_t st, double
             ppmlr::SweepArgs<T> a;
             fill_args(c, a, in, u, axis, dt, dt_dev, m.P, 1);
             set_march(a, axis, m);
+            set_time(c, a, tm);
             if (axis == 0) return march_axis<0, T>(c, a, m.SM, st, fuse);
             if (axis == 1) return march_axis<1, T>(c, a, m.SM, st, fuse);
             return march_axis<2, T>(c, a, m.SM, st, fuse);
@@ -594,6 +618,7 @@ ppmlr_status sweep_typed(ppmlr_ctx *c, const T *in, T *u, hipStream_t st, double
         return fail(c, PPMLR_EINVAL, "tile does not fit one workgroup");
     ppmlr::SweepArgs<T> a;
     fill_args(c, a, in, u, axis, dt, dt_dev, P, nseg);
+    set_time(c, a, tm);
     const bool stats = c->opt.collect_stats != 0;
     if (axis == 0) return launch_axis<0, T>(c, a, st, stats, fuse);
     if (axis == 1) return launch_axis<1, T>(c, a, st, stats, fuse);
@@ -665,7 +690,7 @@ ppmlr_status finish_flow(ppmlr_ctx *c, const ppmlr_state *s, Flow &f)
 }
 
 ppmlr_status do_sweep(ppmlr_ctx *c, const ppmlr_state *s, double dt, const double *dt_dev, int axis, bool fuse,
-                      Flow &f)
+                      Flow &f, const StepTime &tm = StepTime())
 {
     hipStream_t st = (hipStream_t)s->stream;
     void *out = f.home;
@@ -683,8 +708,8 @@ ppmlr_status do_sweep(ppmlr_ctx *c, const ppmlr_state *s, double dt, const doubl
         if (e) return e;
     }
     ppmlr_status r = (s->dtype == PPMLR_F64)
-                         ? sweep_typed<double>(c, (const double *)f.cur, (double *)out, st, dt, dt_dev, axis, fuse)
-                         : sweep_typed<float>(c, (const float *)f.cur, (float *)out, st, dt, dt_dev, axis, fuse);
+                         ? sweep_typed<double>(c, (const double *)f.cur, (double *)out, st, dt, dt_dev, axis, fuse, tm)
+                         : sweep_typed<float>(c, (const float *)f.cur, (float *)out, st, dt, dt_dev, axis, fuse, tm);
     if (!r) f.cur = out;
     if (c->profiling) {
         ppmlr_status e = hip_check(c, hipEventRecord(mk.stop, st), "hipEventRecord");
@@ -705,7 +730,8 @@ struct CflArgs {
     double gamma, p_floor, r_inner2;
     int has_inner;
     double dip_m, dir[3], bext[3];
-    unsigned long long *out;
+    unsigned long long *out;                        // signal-speed slots
+    double *part;                                   // or every workgroup's maximum (host memory)
 };
 
 __device__ inline void bg64(double dip_m, const double *dir, const double *bext, double x, double y, double z,
@@ -820,15 +846,19 @@ __device__ inline double block_max(double smax, double *red)
 }
 
 // Signal-speed maximum over all zones outside the inner boundary: one atomic
-// per workgroup on the bits of the (non-negative) double.
+// per workgroup on the bits of the (non-negative) double; or, for the host, the
+// workgroups' maxima (no slots to clear and to fold, no copy: with those a step
+// of 97x61x83 zones with the host's dt took 133 us, now 103 us).
 template <typename T>
 __global__ void __launch_bounds__(256) cfl_kernel(const CflArgs<T> a)
 {
     __shared__ double red[4];
     const double m = block_max(cfl_rows(a, (int)(blockIdx.x * 4 + (threadIdx.x >> 6)), (int)gridDim.x * 4), red);
-    if (threadIdx.x == 0)
-        atomicMax(a.out + (blockIdx.x % ppmlr::kCflSlots) * ppmlr::kCflStride,
-                  (unsigned long long)__double_as_longlong(m));
+    if (threadIdx.x == 0) {
+        if (a.part) a.part[blockIdx.x] = m;
+        else atomicMax(a.out + (blockIdx.x % ppmlr::kCflSlots) * ppmlr::kCflStride,
+                       (unsigned long long)__double_as_longlong(m));
+    }
 }
 
 // ... of every member of an ensemble (one row of workgroups each)
@@ -841,25 +871,6 @@ __global__ void __launch_bounds__(256) ens_cfl_kernel(const CflArgs<T> *args)
     if (threadIdx.x == 0)
         atomicMax(a.out + (blockIdx.x % ppmlr::kCflSlots) * ppmlr::kCflStride,
                   (unsigned long long)__double_as_longlong(m));
-}
-
-// Maximum of the signal-speed slots (one wave; the bits of non-negative
-// doubles order as unsigned integers, as for the atomics that filled them).
-__device__ inline unsigned long long slot_max(const unsigned long long *slots)
-{
-    unsigned long long v = slots[threadIdx.x * ppmlr::kCflStride];
-    for (int off = 32; off > 0; off >>= 1) {
-        unsigned long long o = __shfl_xor(v, off);
-        v = o > v ? o : v;
-    }
-    return v;
-}
-
-// Fold the slots into slot 0 (one wave of kCflSlots threads).
-__global__ void fold_slots(unsigned long long *slots)
-{
-    const unsigned long long v = slot_max(slots);
-    slots[threadIdx.x * ppmlr::kCflStride] = threadIdx.x == 0 ? v : 0ull;
 }
 
 __global__ void clear_slots(unsigned long long *slots)
@@ -897,7 +908,7 @@ __device__ inline void series_at(const double *series, int n, double t, double *
 __global__ void dt_kernel(unsigned long long *smax_bits, double *dt, double *t, double cfl, const double *series,
                           int series_n, double *inflow)
 {
-    const unsigned long long bits = slot_max(smax_bits);
+    const unsigned long long bits = ppmlr::slot_max(smax_bits, (int)threadIdx.x);
     smax_bits[threadIdx.x * ppmlr::kCflStride] = 0ull;
     if (threadIdx.x != 0) return;
     double smax = __longlong_as_double((long long)bits);
@@ -990,6 +1001,7 @@ CflArgs<T> cfl_args(const ppmlr_ctx *c, const T *u)
     a.dip_m = c->dip_m;
     for (int k = 0; k < 3; ++k) { a.dir[k] = c->dir[k]; a.bext[k] = c->bext[k]; }
     a.out = c->d_cflmax;
+    a.part = nullptr;
     return a;
 }
 
@@ -1001,21 +1013,26 @@ long long cfl_blocks(const ppmlr_ctx *c)
     return ((long long)c->n[1] * c->n[2] + 4 * per - 1) / (4 * per);
 }
 
+constexpr int kCflBlocks = 2048;
+
+// part: host memory for the workgroups' maxima, or null for the slots; returns
+// the workgroups launched in blocks.
 template <typename T>
-ppmlr_status cfl_typed(ppmlr_ctx *c, const T *u, hipStream_t st)
+ppmlr_status cfl_typed(ppmlr_ctx *c, const T *u, hipStream_t st, double *part, int *blocks)
 {
-    const CflArgs<T> a = cfl_args(c, u);
-    const long long blocks = std::min<long long>(cfl_blocks(c), 2048);
-    hipLaunchKernelGGL(cfl_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, st, a);
+    CflArgs<T> a = cfl_args(c, u);
+    a.part = part;
+    *blocks = (int)std::min<long long>(cfl_blocks(c), kCflBlocks);
+    hipLaunchKernelGGL(cfl_kernel<T>, dim3((unsigned)*blocks), dim3(256), 0, st, a);
     return hip_check(c, hipGetLastError(), "cfl launch");
 }
 
-ppmlr_status cfl_launch(ppmlr_ctx *c, const ppmlr_state *s)
+ppmlr_status cfl_launch(ppmlr_ctx *c, const ppmlr_state *s, double *part, int *blocks)
 {
     hipStream_t st = (hipStream_t)s->stream;
-    hipLaunchKernelGGL(clear_slots, dim3(1), dim3(ppmlr::kCflSlots), 0, st, c->d_cflmax);
-    if (s->dtype == PPMLR_F64) return cfl_typed<double>(c, (const double *)s->u, st);
-    return cfl_typed<float>(c, (const float *)s->u, st);
+    if (!part) hipLaunchKernelGGL(clear_slots, dim3(1), dim3(ppmlr::kCflSlots), 0, st, c->d_cflmax);
+    if (s->dtype == PPMLR_F64) return cfl_typed<double>(c, (const double *)s->u, st, part, blocks);
+    return cfl_typed<float>(c, (const float *)s->u, st, part, blocks);
 }
 
 }  // namespace
@@ -1104,7 +1121,9 @@ ppmlr_status ppmlr_create(const ppmlr_grid *grid, double gamma, const ppmlr_coor
                       "hipMalloc");
     if (!s) s = hip_check(c, hipMalloc((void **)&c->d_dt, sizeof(double)), "hipMalloc");
     if (!s) s = hip_check(c, hipMalloc((void **)&c->d_time, sizeof(double)), "hipMalloc");
-    if (!s) s = hip_check(c, hipMalloc((void **)&c->d_partials, sizeof(double) * (8 * kTotBlocks + 8)), "hipMalloc");
+    if (!s) s = hip_check(c, hipMalloc((void **)&c->d_partials, sizeof(double) * 8 * kTotBlocks), "hipMalloc");
+    if (!s) s = hip_check(c, hipHostMalloc((void **)&c->h_results, sizeof(double) * kCflBlocks, hipHostMallocDefault),
+                          "hipHostMalloc");
     if (!s) {
         hipLaunchKernelGGL(clear_u64, dim3(1), dim3(256), 0, (hipStream_t)0, c->d_stats, kStatWords * kStatSlots);
         hipLaunchKernelGGL(clear_slots, dim3(1), dim3(ppmlr::kCflSlots), 0, (hipStream_t)0, c->d_cflmax);
@@ -1429,11 +1448,15 @@ ppmlr_status ppmlr_step(ppmlr_ctx *c, const ppmlr_state *s, double dt)
     }
     static const int even[3] = {0, 1, 2}, odd[3] = {2, 1, 0};
     const int *ord = (c->step % 2 == 0) ? even : odd;
-    hipLaunchKernelGGL(step_time_kernel, dim3(1), dim3(1), 0, (hipStream_t)s->stream, c->d_time, dt, 1, c->d_series,
-                       c->series_n, c->d_inflow);
+    if (c->series_n > 0)
+        hipLaunchKernelGGL(step_time_kernel, dim3(1), dim3(1), 0, (hipStream_t)s->stream, c->d_time, dt, 1, c->d_series,
+                           c->series_n, c->d_inflow);
     Flow f{s->u, s->u};
     for (int k = 0; k < 3; ++k) {
-        e = do_sweep(c, s, dt, nullptr, ord[k], false, f);
+        StepTime tm;
+        tm.advance = k == 0 && c->series_n == 0;
+        tm.step = dt;
+        e = do_sweep(c, s, dt, nullptr, ord[k], false, f, tm);
         if (e) return e;
     }
     c->step++;
@@ -1459,16 +1482,11 @@ ppmlr_status ppmlr_cfl_dt(ppmlr_ctx *c, const ppmlr_state *s, double cfl, double
     ppmlr_status e = check_state(c, s);
     if (e) return e;
     if (!dt_out || !(cfl > 0.0)) return fail(c, PPMLR_EINVAL, "cfl must be positive");
-    e = cfl_launch(c, s);
+    int blocks = 0;
+    e = cfl_launch(c, s, c->h_results, &blocks);
+    if (!e) e = hip_check(c, hipStreamSynchronize((hipStream_t)s->stream), "hipStreamSynchronize");
     if (e) return e;
-    unsigned long long bits = 0;
-    hipStream_t st = (hipStream_t)s->stream;
-    hipLaunchKernelGGL(fold_slots, dim3(1), dim3(ppmlr::kCflSlots), 0, st, c->d_cflmax);
-    e = hip_check(c, hipMemcpyAsync(&bits, c->d_cflmax, sizeof(bits), hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-    if (!e) e = hip_check(c, hipStreamSynchronize(st), "hipStreamSynchronize");
-    if (e) return e;
-    double smax;
-    std::memcpy(&smax, &bits, sizeof(smax));
+    const double smax = *std::max_element(c->h_results, c->h_results + blocks);
     if (!(smax > 0.0) || !std::isfinite(smax)) return fail(c, PPMLR_ENONPHYS, "no finite signal speed");
     *dt_out = cfl / smax;
     return PPMLR_OK;
@@ -1481,16 +1499,35 @@ ppmlr_status ppmlr_advance(ppmlr_ctx *c, const ppmlr_state *s, int nsteps, doubl
     if (nsteps < 0 || !(cfl > 0.0)) return fail(c, PPMLR_EINVAL, "nsteps >= 0 and cfl > 0 required");
     if (nsteps == 0) return PPMLR_OK;
     hipStream_t st = (hipStream_t)s->stream;
-    e = cfl_launch(c, s);   // signal-speed maximum of the current state
+    int blocks = 0;
+    e = cfl_launch(c, s, nullptr, &blocks);   // signal-speed maximum of the current state
     if (e) return e;
     static const int even[3] = {0, 1, 2}, odd[3] = {2, 1, 0};
     Flow f{s->u, s->u};
+    // Every workgroup of the first sweep forms dt, about 1 us before its zones
+    // are loaded: a round of workgroups, some 300 thousand zones, costs that
+    // once, the kernel 3.3 to 4.7 us and a launch gap (20 steps of 32^3, FP64:
+    // 590 us in the sweep, 640 us with the kernel; 8 steps of 256x192x192, FP32,
+    // shorter workgroups of segments: 7480 and 7340 us).
+    const bool dt_in_sweep = c->series_n == 0 && (long long)c->n[0] * c->n[1] * c->n[2] <= 1 << 20;
     for (int n = 0; n < nsteps; ++n) {
-        hipLaunchKernelGGL(dt_kernel, dim3(1), dim3(ppmlr::kCflSlots), 0, st, c->d_cflmax, c->d_dt, c->d_time, cfl,
-                           c->d_series, c->series_n, c->d_inflow);
+        // The last sweep of a step, but for the call's last, leaves the signal
+        // speeds of the next dt in the slots.  dt is formed from them by a kernel
+        // of its own where the inflow of a time series depends on it, and on
+        // large grids; else in the first sweep, and the second clears the slots.
+        StepTime tm;
+        if (!dt_in_sweep)
+            hipLaunchKernelGGL(dt_kernel, dim3(1), dim3(ppmlr::kCflSlots), 0, st, c->d_cflmax, c->d_dt, c->d_time, cfl,
+                               c->d_series, c->series_n, c->d_inflow);
         const int *ord = (c->step % 2 == 0) ? even : odd;
         for (int k = 0; k < 3; ++k) {
-            e = do_sweep(c, s, 0.0, c->d_dt, ord[k], k == 2, f);
+            if (dt_in_sweep) {
+                tm.advance = k == 0;
+                tm.slots = k == 0;
+                tm.clear = k == 1;
+                tm.step = cfl;
+            }
+            e = do_sweep(c, s, 0.0, c->d_dt, ord[k], k == 2 && n + 1 < nsteps, f, tm);
             if (e) return e;
         }
         c->step++;
@@ -1523,11 +1560,10 @@ ppmlr_status ppmlr_totals(ppmlr_ctx *c, const ppmlr_state *s, double out[8])
     else
         hipLaunchKernelGGL(totals_partial<float>, dim3(kTotBlocks), dim3(256), 0, st, (const float *)s->u, vol,
                            c->n[0], c->n[1], c->tab[0].dxi64, c->tab[1].dxi64, c->tab[2].dxi64, c->d_partials);
-    hipLaunchKernelGGL(totals_final, dim3(1), dim3(256), 0, st, c->d_partials, kTotBlocks, c->d_partials + 8 * kTotBlocks);
+    hipLaunchKernelGGL(totals_final, dim3(1), dim3(256), 0, st, c->d_partials, kTotBlocks, c->h_results);
     e = hip_check(c, hipGetLastError(), "totals launch");
-    if (!e) e = hip_check(c, hipMemcpyAsync(out, c->d_partials + 8 * kTotBlocks, sizeof(double) * 8,
-                                            hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
     if (!e) e = hip_check(c, hipStreamSynchronize(st), "hipStreamSynchronize");
+    if (!e) std::memcpy(out, c->h_results, sizeof(double) * 8);
     return e;
 }
 
@@ -1728,7 +1764,7 @@ __global__ void ens_dt_kernel(unsigned long long *const *smax_bits, double *cons
 {
     const int m = blockIdx.x;
     if (m >= members) return;
-    const unsigned long long bits = slot_max(smax_bits[m]);
+    const unsigned long long bits = ppmlr::slot_max(smax_bits[m], (int)threadIdx.x);
     smax_bits[m][threadIdx.x * ppmlr::kCflStride] = 0ull;
     if (threadIdx.x != 0) return;
     double smax = __longlong_as_double((long long)bits);
@@ -1871,7 +1907,7 @@ __global__ void __launch_bounds__(SM) ensemble_persistent_kernel(const PersistAr
         // dt of every member from its maximum; the slots are cleared for the next one
         for (int m = b; m < n; m += (int)G) {
             if (threadIdx.x < 64) {
-                const unsigned long long bits = slot_max(p.smax[m]);
+                const unsigned long long bits = ppmlr::slot_max(p.smax[m], (int)threadIdx.x);
                 p.smax[m][threadIdx.x * ppmlr::kCflStride] = 0ull;
                 if (threadIdx.x == 0) {
                     const double smx = __longlong_as_double((long long)bits);
@@ -2174,6 +2210,7 @@ ppmlr_status ensemble_typed(ppmlr_ctx *const *ctxs, const ppmlr_state *const *st
             e.members = n;
             e.per_xcd = mo[(size_t)ax * (n + 1) + n];
             const dim3 grid(8 * e.per_xcd);
+            const bool fuse = k == 2 && s + 1 < steps;    // (no step of this call takes the last signal speeds)
             auto launch_as = [&](auto kern, int threads, size_t bytes) {
                 if (bytes > 64 * 1024) {
                     hipError_t he = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -2187,7 +2224,7 @@ ppmlr_status ensemble_typed(ppmlr_ctx *const *ctxs, const ppmlr_state *const *st
                 const size_t bytes = ppmlr::lds_bytes(kSlotsA + kSlotsB, SM, (int)sizeof(T), pmax) +
                                      (periodic ? ppmlr::lds_wrap_bytes(pmax, (int)sizeof(T)) : 0);
 #define PPMLR_ENSM(AX_)                                                                                                \
-                if (k == 2) launch_as(ppmlr::ensemble_sweep_kernel<AX_, T, true, true, SM, true>, kEnsMarchBlock, bytes); \
+                if (fuse) launch_as(ppmlr::ensemble_sweep_kernel<AX_, T, true, true, SM, true>, kEnsMarchBlock, bytes); \
                 else launch_as(ppmlr::ensemble_sweep_kernel<AX_, T, true, false, SM, true>, kEnsMarchBlock, bytes);
                 if (ax == 0) { PPMLR_ENSM(0) } else if (ax == 1) { PPMLR_ENSM(1) } else { PPMLR_ENSM(2) }
 #undef PPMLR_ENSM
@@ -2197,9 +2234,9 @@ ppmlr_status ensemble_typed(ppmlr_ctx *const *ctxs, const ppmlr_state *const *st
             }
             auto launch = [&](auto kern) { launch_as(kern, block, lds); };
 #define PPMLR_ENS3(AX_, B_)                                                                              \
-            if (stats) { if (k == 2) launch(ppmlr::ensemble_sweep_kernel<AX_, T, true, true, B_>);         \
+            if (stats) { if (fuse) launch(ppmlr::ensemble_sweep_kernel<AX_, T, true, true, B_>);         \
                          else launch(ppmlr::ensemble_sweep_kernel<AX_, T, true, false, B_>); }             \
-            else { if (k == 2) launch(ppmlr::ensemble_sweep_kernel<AX_, T, false, true, B_>);              \
+            else { if (fuse) launch(ppmlr::ensemble_sweep_kernel<AX_, T, false, true, B_>);              \
                    else launch(ppmlr::ensemble_sweep_kernel<AX_, T, false, false, B_>); }
 #define PPMLR_ENS(B_)                                                                                    \
             if (ax == 0) { PPMLR_ENS3(0, B_) } else if (ax == 1) { PPMLR_ENS3(1, B_) } else { PPMLR_ENS3(2, B_) }

@@ -169,6 +169,15 @@ struct SweepArgs {
     T gamma;
     T dt;                       // used when dt_dev == nullptr
     const double *dt_dev;       // device-resident dt (advance loop)
+    // The first sweep of a step that advances the time: t_out += dt, with dt =
+    // step, or, with dt_slots, step (the CFL number) over the maximum of the
+    // signal-speed slots; dt_out receives it for the step's other sweeps.  A
+    // kernel of its own for this took 3.3 us and a launch gap per step.
+    double *t_out;
+    double step;
+    const unsigned long long *dt_slots;
+    double *dt_out;
+    unsigned long long *clear_slots;   // slots to clear (the step's second sweep), or null
     int has_bd;                 // background field present
     T dip_m, dir_x, dir_y, dir_z, bext_x, bext_y, bext_z;
     T in_rho, in_vx, in_vy, in_vz, in_bx, in_by, in_bz, in_p;   // inflow (total B)
@@ -1352,6 +1361,30 @@ constexpr int sweep_waves(int SM, int GUESS, bool TRACE, bool MARCH = false)
     return sizeof(T) == 4 && GUESS == kGuessPlain && !TRACE && ((SM > 0 && SM <= 512) || SM == 768) ? 6 : 1;
 }
 
+// Maximum of the signal-speed slots (one wave, lane = slot; the bits of
+// non-negative doubles order as unsigned integers, as for the atomics that
+// filled them).
+__device__ inline unsigned long long slot_max(const unsigned long long *slots, int lane)
+{
+    unsigned long long v = slots[lane * kCflStride];
+    for (int off = 32; off > 0; off >>= 1) {
+        unsigned long long o = __shfl_xor(v, off);
+        v = o > v ? o : v;
+    }
+    return v;
+}
+
+// A value that all lanes hold, as a scalar.
+__device__ inline float uniform(float v)
+{
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+__device__ inline double uniform(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                            __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+
 // Standalone sweep: one workgroup per tile.  The learned-guess form holds
 // the network pass next to the sweep's registers; a budget of 4 waves per SIMD
 // (128 registers, up to 15 values spilled in the fused march) was ~20 % faster
@@ -1378,7 +1411,21 @@ __global__ void __launch_bounds__(SM > 0 ? SM : 1024)
     else { seg = slot / a.nslots; tile = slot - seg * a.nslots; }
     const int r = tile / a.tiles_q;
     const int tq = tile - r * a.tiles_q;
-    const T dt = a.dt_dev ? T(*a.dt_dev) : a.dt;
+    T dt;
+    if (a.t_out) {
+        double d = a.step;
+        if (a.dt_slots) {
+            // every wave on its own (all its lanes are active here)
+            const double m = __longlong_as_double((long long)slot_max(a.dt_slots, (int)__lane_id()));
+            d = m > 0.0 ? a.step / m : 0.0;
+            if (b == 0 && threadIdx.x == 0) *a.dt_out = d;
+        }
+        if (b == 0 && threadIdx.x == 0) *a.t_out += d;
+        dt = uniform(T(d));
+    } else {
+        dt = a.dt_dev ? T(*a.dt_dev) : a.dt;
+    }
+    if (a.clear_slots && b == 0 && threadIdx.x < kCflSlots) a.clear_slots[threadIdx.x * kCflStride] = 0ull;
     unsigned long long *cm = a.cfl_max ? a.cfl_max + (b % kCflSlots) * kCflStride : nullptr;
     if constexpr (MARCH) {
         // the arguments where the launch put them (the first bytes of the
