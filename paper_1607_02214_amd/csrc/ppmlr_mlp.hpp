@@ -86,29 +86,33 @@ __device__ __forceinline__ float gelu_grad(float x)
     return s + x * 2.0f * s * (1.0f - s) * kGc * (1.0f + 3.0f * kGa * x * x);
 }
 
-// Value of fragment element (tile t, lane l, item i) of the packed set.
-__device__ inline float frag_value(const float *th, int t, int l, int i)
+// Value of fragment element (tile t, lane l, item i) of the packed set; t0: t or
+// a smaller tile of the same matrix and direction.  th: theta, or a copy
+// whose W1 and W2 have rows of LD values.
+template <int LD = kH>
+__device__ __forceinline__ float frag_value(const float *th, int t0, int t, int l, int i)
 {
+    constexpr int oW2 = kIn * LD + kH, oW3 = oW2 + kH * LD + kH;
     const int r = l & 15, kk = 4 * (l >> 4) + i;
-    if (t < kTA2) {                        // W1^T: m = hidden, k = input feature
+    if (t0 < kTA2) {                       // W1^T: m = hidden, k = input feature
         const int m = t * 16 + r, k = kk;
-        return k < kIn ? th[kOffW1 + k * kH + m] : 0.0f;
+        return k < kIn ? th[k * LD + m] : 0.0f;
     }
-    if (t < kTA3) {                        // W2^T: m = out hidden, k = in hidden
+    if (t0 < kTA3) {                       // W2^T: m = out hidden, k = in hidden
         const int u = t - kTA2, m = (u >> 2) * 16 + r, k = (u & 3) * 16 + kk;
-        return th[kOffW2 + k * kH + m];
+        return th[oW2 + k * LD + m];
     }
-    if (t < kTB3) {                        // W3^T: m = output, k = hidden
+    if (t0 < kTB3) {                       // W3^T: m = output, k = hidden
         const int m = r, k = (t - kTA3) * 16 + kk;
-        return m < kOut ? th[kOffW3 + k * kOut + m] : 0.0f;
+        return m < kOut ? th[oW3 + k * kOut + m] : 0.0f;
     }
-    if (t < kTB2) {                        // W3: m = hidden, k = output
+    if (t0 < kTB2) {                       // W3: m = hidden, k = output
         const int m = (t - kTB3) * 16 + r, k = kk;
-        return k < kOut ? th[kOffW3 + m * kOut + k] : 0.0f;
+        return k < kOut ? th[oW3 + m * kOut + k] : 0.0f;
     }
     {                                      // W2: m = in hidden, k = out hidden
         const int u = t - kTB2, m = (u >> 2) * 16 + r, k = (u & 3) * 16 + kk;
-        return th[kOffW2 + m * kH + k];
+        return th[oW2 + m * LD + k];
     }
 }
 
@@ -118,7 +122,7 @@ __global__ void pack_kernel(const float *__restrict__ theta, unsigned short *__r
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= tiles * 256) return;
     const int t = idx >> 8, l = (idx >> 2) & 63, i = idx & 3;
-    frag[idx] = f2bf(frag_value(theta, t, l, i));
+    frag[idx] = f2bf(frag_value(theta, t, t, l, i));
 }
 
 __device__ __forceinline__ bf16x4 load_frag(const unsigned short *frag, int t, int lane)
@@ -169,11 +173,27 @@ __device__ __forceinline__ float forward_tile(unsigned int f0, unsigned int f1, 
     return o[0] + theta[kOffB3];
 }
 
-// Fragment of tile t of the packed set for this lane, from the FP32 parameters.
-__device__ __forceinline__ bf16x4 theta_frag(const float *__restrict__ th, int t, int lane)
+// The parameters staged in LDS by a workgroup of 256: coalesced loads, rows of
+// W1 and W2 of 65 values, so that a fragment's column is spread over the banks.
+constexpr int kLdW = kH + 1;
+constexpr int kStage = kNPar + kIn + kH;
+constexpr int kStB1 = kIn * kLdW, kStB2 = kStB1 + kH + kH * kLdW, kStB3 = kStB2 + kH + kH * kOut;
+__device__ __forceinline__ void stage_theta(const float *__restrict__ theta, float *stage)
 {
-    return pack4(frag_value(th, t, lane, 0), frag_value(th, t, lane, 1), frag_value(th, t, lane, 2),
-                 frag_value(th, t, lane, 3));
+#pragma unroll
+    for (int k = 0; k < (kNPar + 255) / 256; ++k) {
+        const int p = k * 256 + (int)threadIdx.x;
+        const int row = p < kOffB1 ? p / kH : (p < kOffW2 ? kIn : (p < kOffB2 ? kIn + (p - kOffW2) / kH : kIn + kH));
+        if (p < kNPar) stage[p + row * (kLdW - kH)] = theta[p];
+    }
+}
+
+// Fragment of tile t of the packed set for this lane, from the staged
+// parameters (t0: see frag_value).
+__device__ __forceinline__ bf16x4 stage_frag(const float *stage, int t0, int t, int lane)
+{
+    return pack4(frag_value<kLdW>(stage, t0, t, lane, 0), frag_value<kLdW>(stage, t0, t, lane, 1),
+                 frag_value<kLdW>(stage, t0, t, lane, 2), frag_value<kLdW>(stage, t0, t, lane, 3));
 }
 
 // Features of sample s for this lane as B operand (k = 4q .. 4q + 3; features
@@ -198,9 +218,9 @@ __device__ __forceinline__ bf16x4 load_x(const float *__restrict__ X, int ldx, l
 }
 
 // Forward over n samples.  A wave keeps the whole network in registers (24
-// fragments and the biases, ~80 registers, built from theta once) and takes
-// tiles of 16 samples in turn, the next tile's features requested ahead; nothing
-// goes through LDS.  What bounds it is the GELU of 128 hidden units a sample
+// fragments and the biases, ~80 registers, built once from theta staged in LDS)
+// and takes tiles of 16 samples in turn, the next tile's features requested
+// ahead; the samples do not go through LDS.  What bounds it is the GELU of 128 hidden units a sample
 // (10 vector instructions, two of them transcendental): the matrix products
 // take a quarter of that and the records 112 MB.  1 M records with rows of 28
 // floats: 170 us as one wave per 64 samples with the weights re-read per tile
@@ -212,24 +232,26 @@ __global__ void __launch_bounds__(256) forward_kernel(const float *__restrict__ 
     const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
     const int tiles = (int)(((long long)n + 15) / 16), nw = (int)gridDim.x * 4;
     int tile = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
-    if (tile >= tiles) return;
+    __shared__ float stage[kStage];
     auto sample = [&](int t) { const long long s = (long long)t * 16 + r; return s < n ? s : (long long)n - 1; };
     bf16x4 xb = load_x<VEC>(X, ldx, sample(tile), q);
     bf16x4 w1[4], w2[16], w3[4];
     f32x4 b1[4], b2[4];
+    stage_theta(theta, stage);
+    __syncthreads();
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        w1[t] = theta_frag(theta, kTA1 + t, lane);
-        w3[t] = theta_frag(theta, kTA3 + t, lane);
+        w1[t] = stage_frag(stage, kTA1, kTA1 + t, lane);
+        w3[t] = stage_frag(stage, kTA3, kTA3 + t, lane);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            b1[t][i] = theta[kOffB1 + t * 16 + 4 * q + i];
-            b2[t][i] = theta[kOffB2 + t * 16 + 4 * q + i];
+            b1[t][i] = stage[kStB1 + t * 16 + 4 * q + i];
+            b2[t][i] = stage[kStB2 + t * 16 + 4 * q + i];
         }
     }
 #pragma unroll
-    for (int t = 0; t < 16; ++t) w2[t] = theta_frag(theta, kTA2 + t, lane);
-    const float b30 = theta[kOffB3], b31 = theta[kOffB3 + 1];
+    for (int t = 0; t < 16; ++t) w2[t] = stage_frag(stage, kTA2, kTA2 + t, lane);
+    const float b30 = stage[kStB3], b31 = stage[kStB3 + 1];
     const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
     for (; tile < tiles; tile += nw) {
         const bf16x4 x0 = xb;
@@ -278,17 +300,23 @@ __device__ __forceinline__ float row_sum(float v)
 // tiles on in registers, the weight gradients as contractions over the
 // tile's samples (operands transposed through the wave's own part of LDS),
 // accumulated in registers over the wave's tiles.  At the end the four waves'
-// gradients are added in LDS in a fixed order and the workgroup writes one
-// partial gradient, in theta order, and its partial loss to part[kNPar].  The
+// gradients are added in a fixed order and the workgroup writes one partial
+// gradient, in theta order, and its partial loss to part[kNPar].  The
 // backward pass uses BF16 operands / FP32 accumulation; the GELU derivatives
 // are rounded to BF16.
-// Tiles of 16 samples a wave put a batch of 4096 on 256 waves (64 samples a
-// wave, whose loops over register arrays were not unrolled either, left 64
-// waves on 64 CUs: 80 us and a launch to pack; now 24 us, a training step on 4096
-// records 98 -> 26 us).
+// Tiles of 16 samples a wave put a batch of 4096 on 256 waves.  A tile itself
+// takes 4 us; the rest is the chain around it, so the parameters come to LDS by
+// coalesced loads (gathered from memory as fragments: 6.5 us), with rows of 65
+// that spread their columns over the banks, and the gradients are added as
+// they lie in the registers, 16 bytes a lane, by all threads (in theta order,
+// one wave at a time, value by value: 8 us).  Batch of 4096: 22 us before,
+// 9.9 us now; a training step 25.6 and 14.3 us.
 constexpr int kGradWave = (16 + 64 * 4 + 16) * 16;                 // BF16 values of a wave's transposed operands
 constexpr size_t kGradLds = (size_t)kTiles * 512 + 4 * (size_t)kGradWave * 2;
-static_assert(kGradLds >= 2 * (size_t)(kNPar + 1) * 4, "the reduction reuses the operands' LDS");
+static_assert(kStage * 4 <= 4 * kGradWave * 2, "the parameters are staged where the operands go");
+constexpr int kSumRegs = 12;                                       // registers (x 4) of a wave added at a time
+constexpr size_t kSumBias = (size_t)4 * kSumRegs * 1024;           // after them: both biases' and the scalars
+static_assert(kSumBias + 4 * (2 * kH + 4) * 4 <= kGradLds, "the reduction reuses the operands' LDS");
 
 template <bool VEC>
 __global__ void __launch_bounds__(256) grad_kernel(const float *__restrict__ X, int ldx, const float *__restrict__ Yt,
@@ -303,18 +331,30 @@ __global__ void __launch_bounds__(256) grad_kernel(const float *__restrict__ X, 
     unsigned short *D2T = H2T + 64 * 16, *D1T = D2T + 64 * 16;      // dZ2^T, dZ1^T
     unsigned short *DOT = D1T + 64 * 16;                            // dO^T, rows >= 2 zero
     const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int t = wave; t < kTiles; t += 4)
-        *reinterpret_cast<bf16x4 *>(frag + (t * 64 + lane) * 4) = theta_frag(theta, t, lane);
+    const int tiles = (n + 15) / 16;
+    int tile = (int)blockIdx.x * 4 + wave;
+    // the first tile's samples
+    auto sample = [&](int t) -> long long { return min((long long)t * 16 + r, (long long)n - 1); };
+    bf16x4 xn = load_x<VEC>(X, ldx, sample(tile), q);
+    float y0 = Yt[sample(tile) * ldy], y1 = Yt[sample(tile) * ldy + 1];
+    float *stage = reinterpret_cast<float *>(frag + kTiles * 256);
+    stage_theta(theta, stage);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kTiles; k += 4) {                           // (four tiles of one matrix)
+        const int t = k + wave;
+        *reinterpret_cast<bf16x4 *>(frag + (t * 64 + lane) * 4) = stage_frag(stage, k, t, lane);
+    }
     f32x4 b1[4], b2[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            b1[t][i] = theta[kOffB1 + t * 16 + 4 * q + i];
-            b2[t][i] = theta[kOffB2 + t * 16 + 4 * q + i];
+            b1[t][i] = stage[kStB1 + t * 16 + 4 * q + i];
+            b2[t][i] = stage[kStB2 + t * 16 + 4 * q + i];
         }
-    const float b30 = theta[kOffB3], b31 = theta[kOffB3 + 1];
-    __syncthreads();
+    const float b30 = stage[kStB3], b31 = stage[kStB3 + 1];
+    __syncthreads();                                                // (the operands go where the stage was)
     auto weights = [&](int t) { return *reinterpret_cast<const bf16x4 *>(frag + (t * 64 + lane) * 4); };
     auto put = [&](unsigned short *M, int row0, const bf16x4 &v) {  // rows row0 + 4q .. + 3 of sample r
 #pragma unroll
@@ -330,12 +370,17 @@ __global__ void __launch_bounds__(256) grad_kernel(const float *__restrict__ X, 
     for (int t = 0; t < 16; ++t) gw2[t] = zero;
     float sq = 0.0f, gb30 = 0.0f, gb31 = 0.0f;
     const float inv_n = 1.0f / (float)n;
-    const int tiles = (n + 15) / 16;
-    for (int tile = (int)blockIdx.x * 4 + wave; tile < tiles; tile += (int)gridDim.x * 4) {
-        const long long s = (long long)tile * 16 + r;
-        const bool in = s < n;
-        bf16x4 x = load_x<VEC>(X, ldx, in ? s : (long long)n - 1, q);
+    for (; tile < tiles; tile += (int)gridDim.x * 4) {
+        const bool in = (long long)tile * 16 + r < n;
+        bf16x4 x = xn;
+        const float t0 = y0, t1 = y1;
         if (!in) x = bf16x4{0, 0, 0, 0};
+        const int next = tile + (int)gridDim.x * 4;
+        if (next < tiles) {
+            xn = load_x<VEC>(X, ldx, sample(next), q);
+            y0 = Yt[sample(next) * ldy];
+            y1 = Yt[sample(next) * ldy + 1];
+        }
         put(XT, 0, x);
         // ---- forward, keeping the activations and the GELU derivatives
         bf16x4 h1[4], h2[4], g1[4], g2[4];
@@ -365,7 +410,7 @@ __global__ void __launch_bounds__(256) grad_kernel(const float *__restrict__ X, 
         // ---- output error dO = (o - y) / n (rows 0, 1 of the output tile), loss
         float d0 = 0.0f, d1 = 0.0f;
         if (q == 0 && in) {
-            const float e0 = o[0] + b30 - Yt[s * ldy], e1 = o[1] + b31 - Yt[s * ldy + 1];
+            const float e0 = o[0] + b30 - t0, e1 = o[1] + b31 - t1;
             sq += e0 * e0;
             sq += e1 * e1;
             d0 = e0 * inv_n;
@@ -415,8 +460,7 @@ __global__ void __launch_bounds__(256) grad_kernel(const float *__restrict__ X, 
         }
         __builtin_amdgcn_wave_barrier();
     }
-    // ---- the waves' gradients, in theta order: waves 2, 3 into LDS, added by
-    // waves 0, 1; wave 1's into LDS, added by wave 0, which writes the partial
+    // ---- the waves' gradients: sums over the lanes where a lane holds a part
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -427,47 +471,54 @@ __global__ void __launch_bounds__(256) grad_kernel(const float *__restrict__ X, 
     gb30 = row_sum(gb30);
     gb31 = row_sum(gb31);
     sq = row_sum(sq);
-    auto each = [&](auto &&f) __attribute__((always_inline)) {                                     // value = f(theta index, value), all this lane holds
+    // every wave's registers into LDS as they are, kSumRegs of the 24 at a time,
+    // then four threads' share each: (wave 0 + wave 2) + (wave 1 + wave 3)
+    float *part = partials + (size_t)blockIdx.x * (kNPar + 1);
+    f32x4 *raw = reinterpret_cast<f32x4 *>(lds);
+    float *small = reinterpret_cast<float *>(lds + kSumBias);       // [wave][b1 64, b2 64, b3 2, loss]
+    auto sum4 = [](auto a, auto b, auto c, auto d) { return (a + c) + (b + d); };
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
+    for (int half = 0; half < 2; ++half) {
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSumRegs; ++k) {
+            const int j = half * kSumRegs + k;                      // gw2 0..15, gw1, gw3
+            raw[(wave * kSumRegs + k) * 64 + lane] = j < 16 ? gw2[j] : (j < 20 ? gw1[j - 16] : gw3[j - 20]);
+        }
+        if (half == 0) {
+            float *sm = small + wave * (2 * kH + 4);
+            if (r == 0) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    *reinterpret_cast<f32x4 *>(sm + t * 16 + 4 * q) = gb1[t];
+                    *reinterpret_cast<f32x4 *>(sm + kH + t * 16 + 4 * q) = gb2[t];
+                }
+            }
+            if (lane == 0) { sm[2 * kH] = gb30; sm[2 * kH + 1] = gb31; sm[2 * kH + 2] = sq; }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSumRegs; k += 4) {
+            const f32x4 *x = raw + (k + wave) * 64 + lane;
+            const f32x4 v = sum4(x[0], x[kSumRegs * 64], x[2 * kSumRegs * 64], x[3 * kSumRegs * 64]);
+            const int j0 = half * kSumRegs + k, j = j0 + wave;      // (four registers of one matrix)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int m = mt * 16 + 4 * q + i;
-                if (4 * q + i < kIn) gw1[mt][i] = f(kOffW1 + (4 * q + i) * kH + mt * 16 + r, gw1[mt][i]);
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt)
-                    gw2[mt * 4 + nt][i] = f(kOffW2 + m * kH + nt * 16 + r, gw2[mt * 4 + nt][i]);
-                if (r < kOut) gw3[mt][i] = f(kOffW3 + m * kOut + r, gw3[mt][i]);
-                if (r == 0) gb1[mt][i] = f(kOffB1 + m, gb1[mt][i]);
-                if (r == 0) gb2[mt][i] = f(kOffB2 + m, gb2[mt][i]);
+                if (j0 < 16) part[kOffW2 + ((j >> 2) * 16 + 4 * q + i) * kH + (j & 3) * 16 + r] = v[i];
+                else if (j0 < 20) { if (4 * q + i < kIn) part[kOffW1 + (4 * q + i) * kH + (j - 16) * 16 + r] = v[i]; }
+                else if (r < kOut) part[kOffW3 + ((j - 20) * 16 + 4 * q + i) * kOut + r] = v[i];
             }
-        if (lane == 0) {
-            gb30 = f(kOffB3, gb30);
-            gb31 = f(kOffB3 + 1, gb31);
-            sq = f(kNPar, sq);
         }
-    };
-    float *buf = reinterpret_cast<float *>(lds);
-    auto put_at = [&](float *b) __attribute__((always_inline)) {
-        each([&](int p, float v) __attribute__((always_inline)) { b[p] = v; return v; });
-    };
-    auto add_from = [&](const float *b) __attribute__((always_inline)) {
-        each([&](int p, float v) __attribute__((always_inline)) { return v + b[p]; });
-    };
-    __syncthreads();
-    if (wave >= 2) put_at(buf + (wave - 2) * (kNPar + 1));
-    __syncthreads();
-    if (wave < 2) add_from(buf + wave * (kNPar + 1));
-    __syncthreads();
-    if (wave == 1) put_at(buf);
-    __syncthreads();
-    if (wave == 0) {
-        add_from(buf);
-        put_at(buf);
+        if (half == 0 && threadIdx.x < 2 * kH + 3) {
+            constexpr int w = 2 * kH + 4;
+            const int k = threadIdx.x;
+            const float v = sum4(small[k], small[w + k], small[2 * w + k], small[3 * w + k]);
+            if (k < kH) part[kOffB1 + k] = v;
+            else if (k < 2 * kH) part[kOffB2 + k - kH] = v;
+            else if (k < 2 * kH + 2) part[kOffB3 + k - 2 * kH] = v;
+            else part[kNPar] = 0.5f * v * inv_n;
+        }
     }
-    __syncthreads();
-    float *part = partials + (size_t)blockIdx.x * (kNPar + 1);
-    for (int p = threadIdx.x; p <= kNPar; p += 256) part[p] = p == kNPar ? 0.5f * buf[p] * inv_n : buf[p];
 }
 
 // Sum the per-workgroup partials in a fixed order: 64 parameters per workgroup,
