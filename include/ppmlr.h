@@ -269,7 +269,13 @@ ppmlr_status ppmlr_set_profiling(ppmlr_ctx *ctx, int enable);
 ppmlr_status ppmlr_kernel_times(ppmlr_ctx *ctx, double ms[3], long long launches[3]);
 
 /* Pencils per workgroup for sweeps along axis (tile shape); 0 = automatic.
- * EINVAL if the tile does not fit one workgroup. */
+ * EINVAL if the tile does not fit one workgroup.  With one segment per pencil
+ * a workgroup takes its pencils whole, in chunks that follow each other (in
+ * place, without a second state), and the automatic choice is the number of
+ * pencils and chunks with the least estimated time; the tile of whole pencils
+ * whose size ppmlr_get_tile returns serves single-chunk shapes, the harvest
+ * mode and counts of pencils that no chunk of 256 lanes holds.  Results do not
+ * depend on any of it, bit for bit. */
 ppmlr_status ppmlr_set_tile(ppmlr_ctx *ctx, int axis, int pencils);
 ppmlr_status ppmlr_get_tile(const ppmlr_ctx *ctx, int axis, int dtype, int *pencils);
 
@@ -302,9 +308,8 @@ ppmlr_status ppmlr_get_segment_order(const ppmlr_ctx *ctx, int axis, int *order)
 ppmlr_status ppmlr_get_segments(const ppmlr_ctx *ctx, int axis, int dtype, int *segments);
 
 /* Tile autotuner: for each axis, times `reps` sweeps of every tile shape
- * (pencils per workgroup, segments per pencil from 1 to 8, both segment
- * orders) that fits one
- * workgroup on a library-owned copy of the state (the caller's state is not
+ * (pencils per workgroup or the automatic choice, segments per pencil from 1
+ * to 8, both segment orders) that fits one workgroup on a library-owned copy of the state (the caller's state is not
  * modified), times the three fastest again with 3 x reps sweeps, keeps the
  * fastest per axis (the shape is set on the context) and returns the pencils
  * per workgroup in tiles[3] (may be NULL).  The sweeps timed use the context's initial-guess mode
@@ -386,7 +391,8 @@ ppmlr_status ppmlr_ensemble_run_noalloc(ppmlr_ctx *const *ctxs, const ppmlr_stat
  * workgroup size (256, 512, 1024) and target segment length (whole pencils,
  * or segments of about 96, 64, 48 or 32 interior zones) on library-owned
  * copies of the states (the callers' states, step counters and times are
- * left unchanged), stores the fastest workgroup size for ensemble calls with
+ * left unchanged; whole pencils are swept in chunks of 256 lanes whatever the
+ * workgroup size, so that they are timed at 512 only where that fits), stores the fastest workgroup size for ensemble calls with
  * block = 0, returns it in *block (may be NULL), and sets every member
  * context's segments per axis to the fastest length's; then, at that
  * workgroup size, tries each other length for one axis at a time (over at
@@ -447,8 +453,8 @@ ppmlr_status ppmlr_set_gate(ppmlr_ctx *ctx, double rel_p, double rel_u);
  * leaves the harvest mode). */
 ppmlr_status ppmlr_set_harvest(ppmlr_ctx *ctx, float *records, long long capacity, unsigned long long *count);
 
-/* Training workspace for batches of up to max_batch samples (device buffers
- * for packed weights and per-workgroup partial gradients). */
+/* Training workspace for batches of up to max_batch samples (a device buffer
+ * for per-workgroup partial gradients). */
 typedef struct ppmlr_mlp ppmlr_mlp;
 ppmlr_status ppmlr_mlp_create(int max_batch, ppmlr_mlp **out);
 void ppmlr_mlp_destroy(ppmlr_mlp *mlp);

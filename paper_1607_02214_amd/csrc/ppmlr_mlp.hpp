@@ -11,8 +11,9 @@
 // accumulator tile of one layer (lane l: column l%16, rows 4*(l/16)+i) has
 // exactly the register layout of the B operand of the next layer (lane l:
 // column l%16, k = 4*(l/16)+i), so activations never leave registers in the
-// forward pass.  Weights are pre-packed into A-operand fragments (64 lanes x
-// 4 BF16 per 16x16 tile, one coalesced 8-byte load per lane).
+// forward pass.  Weights are A-operand fragments (64 lanes x 4 BF16 per 16x16
+// tile, 8 bytes per lane): packed in memory for the sweep, built from the
+// parameters in LDS by the batch kernels.
 //
 // Parameter vector theta (FP32, 5250 values): W1[14][64], b1[64],
 // W2[64][64], b2[64], W3[64][2], b3[2], row-major (input index first).

@@ -6,7 +6,8 @@
 //
 // Execution model: one thread per zone, a workgroup owns one tile of P
 // pencil segments (L interior zones + 7 ghosts per side each; one segment =
-// the whole pencil), and every stencil is served from LDS.  Successive stages
+// the whole pencil) or marches along P whole pencils in chunks, and every
+// stencil is served from LDS.  Successive stages
 // exchange only what a neighbour needs, through two LDS buffers (A, B) with
 // one barrier per exchange:
 //   R1 load + primitives                                  -> A
@@ -17,8 +18,8 @@
 //   R5 Lagrangian zone contents                       B -> A
 //   R6 limited slopes (volume coordinate)             A -> B
 //      remap edge values                           A, B -> A (slots 8..14)
-//   R7 remap parabolas, donor-cell fluxes             A -> A
-//   R8 conservative update, sources, store            A
+//   R7 remap parabolas, donor-cell fluxes             A -> B
+//   R8 conservative update, sources, store            B
 // The pencil axis is a template parameter so that all component indexing is
 // static (no private arrays with dynamic indices).
 #pragma once
@@ -420,7 +421,10 @@ __device__ inline bool guess_selects(T rl, T rr, T ul, T ur, T pl, T pr, T gate_
 // FP32 456 / 515 / 553 us as whole-pencil tiles, 306 / 295 / 291 us as marches;
 // FP64 1394 / 1167 / 1266 us against 745 / 665 / 700 us.  Requesting the next
 // chunk's zones ahead was measured and is not done (315 / 302 / 299 us): with
-// 20 waves on a CU the loads are covered, and the registers are not there.
+// 20 waves on a CU the loads are covered, and the registers are not there; nor
+// by a load or two per lane that only bring its rows into the L2 (6 % slower,
+// 15 % at 512x384x384; loads return in order, and the later ones of the chunk
+// would wait behind them).
 // GUESS: initial guess of the normal-pair Newton iteration: the plain linear
 // guess, the learned (MLP) guess on selected faces, or the plain guess with
 // the selected faces' states and solutions recorded for training.  s_guess:
