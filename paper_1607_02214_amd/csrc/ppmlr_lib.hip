@@ -489,8 +489,11 @@ March march_search(const ppmlr_ctx *c, int axis, int elem, int P_req)
     double best_t = 1e300;
     for (int P = P_req > 0 ? P_req : 1; P <= (P_req > 0 ? P_req : 8); ++P) {
         for (int C = 1; C <= 64 && (C == 1 || (N + kG) / C >= kG); ++C) {
-            const March m = march_shape(N, P, C, 320);
+            March m = march_shape(N, P, C, 320);
             if (m.P == 0) continue;
+            // (FP64: four workgroups per CU with rows of 208 slots, three with 256:
+            // x sweep of 256x192x192, two pencils of 95 zones, 680 and 769 us)
+            if (elem == 8 && !trace && m.SM == 256 && P * (m.M + ppmlr::kCarry) <= 208) m.SM = 208;
             const int waves = block_threads(P, m.M) / 64;
             const size_t lds = (march_lds(c, axis, P, m.SM, elem) + 1279) / 1280 * 1280;
             const double per_cu = std::min((int)(160 * 1024 / lds), 4 * wps / waves);
@@ -538,6 +541,9 @@ ppmlr_status launch_march(ppmlr_ctx *c, const ppmlr::SweepArgs<T> &a, int SM, hi
     switch (SM) {
     case 128: return launch_march_sm<AX, T, FUSE, 128, TRACE, GUESS>(c, a, st);
     case 192: return launch_march_sm<AX, T, FUSE, 192, TRACE, GUESS>(c, a, st);
+    case 208:
+        if constexpr (sizeof(T) == 8 && !TRACE) return launch_march_sm<AX, T, FUSE, 208, TRACE, GUESS>(c, a, st);
+        else return fail(c, PPMLR_EINVAL, "no march of this stride");
     case 256: return launch_march_sm<AX, T, FUSE, 256, TRACE, GUESS>(c, a, st);
     case 320: return launch_march_sm<AX, T, FUSE, 320, TRACE, GUESS>(c, a, st);
     default: return fail(c, PPMLR_EINVAL, "no march of this stride");

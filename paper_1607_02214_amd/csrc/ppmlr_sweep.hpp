@@ -419,7 +419,7 @@ __device__ inline bool guess_selects(T rl, T rr, T ul, T ur, T pl, T pr, T gate_
 // one workgroup on a CU; chunks of 25 zones of 8 pencils are 4 waves, five
 // workgroups a CU, rows of 32 B in y and z.  256x192x192, one sweep, x / y / z:
 // FP32 456 / 515 / 553 us as whole-pencil tiles, 306 / 295 / 291 us as marches;
-// FP64 1394 / 1167 / 1266 us against 745 / 665 / 700 us.  Requesting the next
+// FP64 1394 / 1167 / 1266 us against 680 / 665 / 700 us.  Requesting the next
 // chunk's zones ahead was measured and is not done (315 / 302 / 299 us): with
 // 20 waves on a CU the loads are covered, and the registers are not there; nor
 // by a load or two per lane that only bring its rows into the L2 (6 % slower,

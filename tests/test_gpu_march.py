@@ -139,3 +139,13 @@ def test_march_learned(kind, n, gate):
     assert out[0][1]["guess_faces"] > 0 or gate > 0
     for u, st, t in out[1:]:
         assert torch.equal(u, out[0][0]) and st == out[0][1] and t == out[0][2]
+
+
+# FP64 rows of 208 slots: the fewest and the most that two pencils fill, and one
+# zone more
+@pytest.mark.parametrize("kind,nx", [("smooth", 169), ("blast", 171), ("smooth", 175), ("smooth", 177)])
+def test_march_rows_of_208(kind, nx):
+    case = _case(kind, (nx, 9, 11), 0)
+    ref, st, t = _run(case, torch.float64, 2)
+    got, st2, t2 = _run(case, torch.float64, 1, 2)
+    assert torch.equal(got, ref) and st2 == st and t2 == t
