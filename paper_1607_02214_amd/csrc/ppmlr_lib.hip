@@ -491,10 +491,11 @@ March march_search(const ppmlr_ctx *c, int axis, int elem, int P_req)
         for (int C = 1; C <= 64 && (C == 1 || (N + kG) / C >= kG); ++C) {
             March m = march_shape(N, P, C, 320);
             if (m.P == 0) continue;
-            // (FP64: four workgroups per CU with rows of 208 slots, three with 256:
-            // x sweep of 256x192x192, two pencils of 95 zones, 680 and 769 us)
-            if (elem == 8 && !trace && m.SM == 256 && P * (m.M + ppmlr::kCarry) <= 208) m.SM = 208;
             const int waves = block_threads(P, m.M) / 64;
+            // (FP64, three waves: four workgroups per CU with rows of 208 slots,
+            // three with 256: x sweep of 256x192x192, two pencils of 95 zones, 680
+            // and 769 us; four waves are more lanes than that kernel is built for)
+            if (elem == 8 && !trace && waves <= 3 && m.SM == 256 && P * (m.M + ppmlr::kCarry) <= 208) m.SM = 208;
             const size_t lds = (march_lds(c, axis, P, m.SM, elem) + 1279) / 1280 * 1280;
             const double per_cu = std::min((int)(160 * 1024 / lds), 4 * wps / waves);
             const double wgs = (double)((nq + P - 1) / P) * nr, rounds = wgs / (256.0 * per_cu);
@@ -525,6 +526,7 @@ template <int AX, typename T, bool FUSE, int SM, bool TRACE, int GUESS>
 ppmlr_status launch_march_sm(ppmlr_ctx *c, const ppmlr::SweepArgs<T> &a, hipStream_t st)
 {
     // (counters are always collected in the kernel, and not stored without a buffer)
+    if (block_threads(a.P, a.M) > SM) return fail(c, PPMLR_EINVAL, "march exceeds its workgroup");
     const size_t lds = march_lds(c, AX, a.P, SM, (int)sizeof(T));
     auto kern = ppmlr::sweep_kernel<AX, T, true, FUSE, SM, GUESS, TRACE, true>;
     if (lds > 64 * 1024) {

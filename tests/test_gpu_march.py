@@ -141,8 +141,8 @@ def test_march_learned(kind, n, gate):
         assert torch.equal(u, out[0][0]) and st == out[0][1] and t == out[0][2]
 
 
-# FP64 rows of 208 slots: the fewest and the most that two pencils fill, and one
-# zone more
+# FP64 rows of 208 slots: two pencils of 95 and 96 zones, and two whose lanes or
+# slots are more than those workgroups take
 @pytest.mark.parametrize("kind,nx", [("smooth", 169), ("blast", 171), ("smooth", 175), ("smooth", 177)])
 def test_march_rows_of_208(kind, nx):
     case = _case(kind, (nx, 9, 11), 0)
