@@ -77,6 +77,13 @@ def load_traffic(dtype: str):
     return d, d.get("source_hash")
 
 
+def pencils(ctx, axis, *dtype):
+    """Pencils per workgroup to give another context for the same sweeps: an
+    axis without segments keeps the automatic choice (0), whose shape is not the
+    whole-pencil tile that get_tile returns."""
+    return 0 if ctx.get_segments(axis, *dtype) == 1 else ctx.get_tile(axis, *dtype)
+
+
 def shape_record(prof, axis, shape):
     """The record of a committed counter summary taken with the tile shape
     `shape` = (pencils per workgroup, segments, segment order) on `axis`: the
@@ -178,7 +185,7 @@ def series_leg(args, setup, make_ctx, shape_ctx):
     for a in range(3):
         ctx.set_tile(a, 1)
         ctx.set_segments(a, shape_ctx.get_segments(a))
-        ctx.set_tile(a, shape_ctx.get_tile(a))
+        ctx.set_tile(a, pencils(shape_ctx, a))
         ctx.set_segment_order(a, shape_ctx.get_segment_order(a))
     u = torch.from_numpy(setup.U).to(device="cuda", dtype=torch.float32).contiguous()
     t_end = 1.2 * (args.warmup + args.steps) * ctx.cfl_dt(u, args.cfl)
@@ -213,7 +220,7 @@ def ionosphere_leg(args, setup, make_ctx, shape_ctx, u_dev):
     for a in range(3):
         ctx.set_tile(a, 1)
         ctx.set_segments(a, shape_ctx.get_segments(a))
-        ctx.set_tile(a, shape_ctx.get_tile(a))
+        ctx.set_tile(a, pencils(shape_ctx, a))
         ctx.set_segment_order(a, shape_ctx.get_segment_order(a))
     u = u_dev.clone()
     prm = ppmlr.iono_default_params()
@@ -363,7 +370,7 @@ def learned_leg(args, setup, make_ctx, u_plain, st_plain, value_plain, ref64=Non
         for ax in range(3):
             c.set_segments(ax, ctx.get_segments(ax))
             c.set_segment_order(ax, ctx.get_segment_order(ax))
-            c.set_tile(ax, ctx.get_tile(ax, ppmlr.F32))
+            c.set_tile(ax, pencils(ctx, ax, ppmlr.F32))
 
     def timed(c):
         w = torch.from_numpy(setup.U).to(device="cuda", dtype=torch.float32).contiguous()
@@ -663,11 +670,12 @@ def main():
         context of its own, in `rounds` passes over the candidates (each
         candidate's time is its fastest pass), and keep the fastest."""
         pdt = ppmlr.F64 if dtype == torch.float64 else ppmlr.F32
-        base = [ctx.get_tile(a, pdt) for a in range(3)]
+        base = [pencils(ctx, a, pdt) for a in range(3)]
         segs = [ctx.get_segments(a, pdt) for a in range(3)]
         order = [ctx.get_segment_order(a) for a in range(3)]
         times = {}
-        cands = [(py, pz) for py in sorted({base[1], 4, 8}) for pz in sorted({base[2], 4, 8})]
+        cands = [(py, pz) for py in sorted({base[1], 4, 8} if base[1] else {0})
+                 for pz in sorted({base[2], 4, 8} if base[2] else {0})]
         for _ in range(rounds):
             for py, pz in cands:
                 trial = make_ctx()
