@@ -54,9 +54,13 @@ def kernel_source_hash() -> str:
     The tile shape the counters were taken with is recorded beside them."""
     import re
     h = hashlib.sha256()
-    for rel in ("paper_1607_02214_amd/csrc/ppmlr_sweep.hpp", "paper_1607_02214_amd/csrc/ppmlr_mlp.hpp",
+    for rel in ("paper_1607_02214_amd/csrc/ppmlr_sweep.hpp", "paper_1607_02214_amd/csrc/ppmlr_march.hpp",
+                "paper_1607_02214_amd/csrc/ppmlr_mlp.hpp",
                 "paper_1607_02214_amd/csrc/ppmlr_char.hpp"):
-        with open(os.path.join(ROOT, rel), encoding="utf-8") as f:
+        path = os.path.join(ROOT, rel)
+        if not os.path.exists(path):                 # (a copy of some of the sources)
+            continue
+        with open(path, encoding="utf-8") as f:
             src = f.read()
         src = re.sub(r"/\*.*?\*/", " ", src, flags=re.S)
         src = re.sub(r"//[^\n]*", " ", src)

@@ -17,11 +17,15 @@
 #include "ppmlr_iono.hpp"
 #include "ppmlr_sweep.hpp"
 
+using ppmlr::block_threads;
 using ppmlr::kG;
 using ppmlr::kSlotsA;
 using ppmlr::kSlotsB;
 using ppmlr::kStatWords;
 using ppmlr::kStatSlots;
+using ppmlr::March;
+using ppmlr::march_shape;
+using ppmlr::march_stride;
 
 struct AxisTables {
     // FP64 and FP32 copies: extended widths [M], centres [M], faces [M+1];
@@ -30,12 +34,6 @@ struct AxisTables {
     double *rdx64 = nullptr, *rdc64 = nullptr;
     float *dx32 = nullptr, *xc32 = nullptr, *xf32 = nullptr, *xci32 = nullptr;
     float *rdx32 = nullptr, *rdc32 = nullptr;
-};
-
-// Shape of a march (whole pencils in chunks, see sweep_tile): P pencils per
-// workgroup, C chunks of L zones, M = L + 7 zones per chunk, LDS stride SM.
-struct March {
-    int P = 0, C = 0, L = 0, M = 0, SM = 0;
 };
 
 struct ppmlr_ctx {
@@ -181,9 +179,6 @@ bool has_background(const ppmlr_ctx *c)
 {
     return c->dip_m != 0.0 || c->bext[0] != 0.0 || c->bext[1] != 0.0 || c->bext[2] != 0.0;
 }
-
-// Threads needed for a tile of P pencils, rounded to whole waves.
-int block_threads(int P, int M) { return ((P * M + 63) / 64) * 64; }
 
 // Segments of a pencil of N zones cut into `nseg`: interior length of all but
 // the last (which is shorter or equal, and not empty); 0 if nseg is invalid.
@@ -437,23 +432,6 @@ size_t march_lds(const ppmlr_ctx *c, int axis, int P, int SM, int elem)
            (c->bc_hi[axis] == PPMLR_PERIODIC ? ppmlr::lds_wrap_bytes(P, elem) : 0);
 }
 
-// The march of P pencils of N zones in C chunks; P = 0 where the last chunk would
-// be empty, a chunk shorter than 14 zones (but for a single one), or its zones
-// and carries more than 4 waves or max_slots LDS slots per row.
-March march_shape(int N, int P, int C, int max_slots)
-{
-    March m;
-    m.L = (N + kG + C - 1) / C;
-    if ((C > 1 && m.L < 2 * kG) || (C - 1) * m.L >= N + kG) return m;
-    m.M = m.L + kG;
-    const int slots = P * (m.M + ppmlr::kCarry);
-    m.SM = slots <= 128 ? 128 : (slots + 63) / 64 * 64;
-    if (block_threads(P, m.M) > 256 || m.SM > max_slots) return m;
-    m.C = C;
-    m.P = P;
-    return m;
-}
-
 // How much a y or z sweep is slowed by rows of w 4-byte words (see march_search).
 double row_cost(int axis, int w, bool cached)
 {
@@ -492,10 +470,7 @@ March march_search(const ppmlr_ctx *c, int axis, int elem, int P_req)
             March m = march_shape(N, P, C, 320);
             if (m.P == 0) continue;
             const int waves = block_threads(P, m.M) / 64;
-            // (FP64, three waves: four workgroups per CU with rows of 208 slots,
-            // three with 256: x sweep of 256x192x192, two pencils of 95 zones, 680
-            // and 769 us; four waves are more lanes than that kernel is built for)
-            if (elem == 8 && !trace && waves <= 3 && m.SM == 256 && P * (m.M + ppmlr::kCarry) <= 208) m.SM = 208;
+            m.SM = march_stride(m, elem, trace);
             const size_t lds = (march_lds(c, axis, P, m.SM, elem) + 1279) / 1280 * 1280;
             const double per_cu = std::min((int)(160 * 1024 / lds), 4 * wps / waves);
             const double wgs = (double)((nq + P - 1) / P) * nr, rounds = wgs / (256.0 * per_cu);

@@ -24,50 +24,20 @@
 // static (no private arrays with dynamic indices).
 #pragma once
 #include "ppmlr_char.hpp"
+#include "ppmlr_march.hpp"
 #include "ppmlr_mlp.hpp"
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace ppmlr {
 
-constexpr int kG = 7;           // ghost zones per side
-constexpr int kSlotsA = 16;     // values per zone in LDS buffer A
-constexpr int kSlotsAGuess = 19;  // buffer A of the learned / harvest sweeps (3 more face values)
-constexpr int kSlotsB = 8;       // values per zone in LDS buffer B
 // The signal-speed maximum is accumulated in kCflSlots words kCflStride
 // words apart (workgroup b uses slot b mod kCflSlots), so that the
 // workgroups' atomics do not all queue on one address; readers take the
 // maximum of the slots.
 constexpr int kCflSlots = 64;
 constexpr int kCflStride = 32;
-constexpr int kStatWords = 37;  // iteration histogram [32], floors, nonconverged, nonphys,
-                                // learned-guess faces, learned-guess fallbacks
 constexpr int kStatSlots = 64;  // copies of the counters (workgroup b adds to copy b % 64)
-
-// Dynamic LDS of a sweep workgroup: the workgroup's scalars (16 doubles of
-// per-wave signal-speed maxima, the kStatWords counters, the learned guess's
-// face count or a persistent launch's barrier flag, and a persistent launch's
-// tile claim), then the tile buffers A and B (slots values per zone, stride
-// S).  A zone reads its neighbours' slots up to two zones away without a
-// bounds test: what a zone at the end of a tile reads beyond it (another
-// value's slot, the scalars in front, the guard of two zones behind) reaches
-// ghost zones only, as the tile's 7 ghost zones are the radius of the whole
-// sweep.  P: pencils per workgroup (the zones of y and z tiles are P slots
-// apart).
-constexpr int kLdsScalars = 16 * 8 + (kStatWords + 2) * 4;
-__host__ __device__ constexpr size_t lds_guard(int P, int elem) { return ((size_t)2 * P * elem + 15) / 16 * 16; }
-__host__ __device__ constexpr size_t lds_front(int P, int elem)
-{
-    constexpr size_t head = (kLdsScalars + 15) / 16 * 16;
-    return lds_guard(P, elem) > head ? lds_guard(P, elem) : head;
-}
-__host__ __device__ constexpr size_t lds_bytes(int slots, int S, int elem, int P)
-{
-    return lds_front(P, elem) + ((size_t)slots * (size_t)S * (size_t)elem + 15) / 16 * 16 + lds_guard(P, elem);
-}
-// A march keeps the old first kG zones of a periodic axis behind the rows.
-__host__ __device__ constexpr size_t lds_wrap_bytes(int P, int elem) { return (size_t)8 * kG * P * elem; }
-constexpr int kCarry = 6;       // slots of every row that a march keeps for each pencil
 
 enum { kPeriodic = 0, kOutflow = 1, kInflow = 2 };
 
@@ -469,13 +439,14 @@ __device__ __forceinline__ void sweep_tile(const ARGS &args, const int tq, const
     const int q0 = tq * a.P;
     const int Suse = a.S, M = a.M, N = a.N, P = a.P;
     const bool slot_ok = tid < Suse;
+    const int zn = MARCH ? march_lane(tid, Suse) : tid;   // this lane's zone of the tile or chunk
     int p, i;
-    // tid / divisor as floor((tid + 1/2) * (1/divisor)): exact for tid < 2^12
+    // zn / divisor as floor((zn + 1/2) * (1/divisor)): exact for zn < 2^12
     // and divisors up to 2^11 (the distance to the next integer, >= 1/(2 div),
-    // exceeds the rounding error, < tid * 2^-23 / div)
-    const int qd = (int)(((float)tid + 0.5f) * a.inv_div);
-    if (AX == 0) { p = qd; i = tid - p * M; }             // zones of a pencil adjacent
-    else { i = qd; p = tid - i * P; }                     // pencils adjacent (coalesced)
+    // exceeds the rounding error, < zn * 2^-23 / div)
+    const int qd = (int)(((float)zn + 0.5f) * a.inv_div);
+    if (AX == 0) { p = qd; i = zn - p * M; }              // zones of a pencil adjacent
+    else { i = qd; p = zn - i * P; }                      // pencils adjacent (coalesced)
     // slot offset of zone i+1 (kept from the compiler for x, which would fold
     // it into address arithmetic per slot)
     int d = (AX == 0) ? 1 : P;
@@ -486,7 +457,7 @@ __device__ __forceinline__ void sweep_tile(const ARGS &args, const int tq, const
     // for the ends of a tile).  A march keeps kCarry slots of every row before
     // each pencil's zones, what a chunk's last zone leaves to the next chunk: three
     // sets, two of each in turn.
-    const int t = tid + (MARCH ? (AX == 0 ? kCarry * (p + 1) : kCarry * P) : 0);
+    const int t = MARCH ? march_slot(AX == 0, zn, p, P) : tid;
     const int sp1 = t + d, sp2 = sp1 + d;
     T *sP = sB + kSlotsB * S;                             // march on a periodic axis: old zones 0 .. 6
     const bool wrap = MARCH && a.bc_hi == kPeriodic;
@@ -884,7 +855,7 @@ __device__ __forceinline__ void sweep_tile(const ARGS &args, const int tq, const
         const int lane = tid & 63;
         unsigned int *F = reinterpret_cast<unsigned int *>(sA + 9 * S);
         auto column = [&](int n) -> int {                 // lane n's slot
-            return n + (MARCH ? (AX == 0 ? kCarry * ((int)(((float)n + 0.5f) * a.inv_div) + 1) : kCarry * P) : 0);
+            return MARCH ? march_slot(AX == 0, n, (int)(((float)n + 0.5f) * a.inv_div), P) : n;
         };
         int slot = 0;
         // (few waves have such a face: the others do not form the features)
