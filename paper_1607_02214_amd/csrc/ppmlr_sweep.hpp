@@ -70,11 +70,13 @@ template <> struct Ar<double> {
     __device__ static inline double rcp(double x) { return rcp64(x); }
     __device__ static inline double div(double a, double b) { return a * rcp64(b); }
     __device__ static inline double sqrt_(double x) { return __builtin_sqrt(x); }
-    // square root of a positive, finite value: x rsqrt(x) with one correction
+    // square root: x rsqrt(x) with one correction; zero and +infinity (class
+    // bits 5, 6 and 9) are their own roots, where that form has no value
     __device__ static inline double sqrtp(double x)
     {
         const double y = rsqrt64(x), r = x * y;
-        return __builtin_fma(__builtin_fma(-r, r, x), 0.5 * y, r);
+        const double s = __builtin_fma(__builtin_fma(-r, r, x), 0.5 * y, r);
+        return __builtin_amdgcn_class(x, 0x260) ? x : s;
     }
     __device__ static inline double rsqrt(double x) { return rsqrt64(x); }
 };
