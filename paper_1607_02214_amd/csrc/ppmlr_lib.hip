@@ -15,6 +15,7 @@
 
 #include "ppmlr.h"
 #include "ppmlr_iono.hpp"
+#include "ppmlr_rows.hpp"
 #include "ppmlr_sweep.hpp"
 
 using ppmlr::block_threads;
@@ -749,25 +750,26 @@ __device__ inline float wave_max(float v)
 // c_f,a <= sqrt(a^2 + b^2): a wave whose lanes' bounds all lie at or below a
 // value that it has reached skips the three fast speeds (six FP64 square
 // roots).  The maximum is the same.  Rows are addressed without divisions per
-// zone; grids narrower than a wave put several rows on one.  256x192x192 FP32:
+// zone (see RowSplit for grids of few or short rows).  256x192x192 FP32:
 // 149 us with a grid-stride loop over zones and every speed, 84 us now (a copy of
 // the same bytes takes 62 us).
 template <typename T>
 __device__ inline double cfl_rows(const CflArgs<T> &a, int wave, int nw)
 {
     const int lane = (int)__lane_id();
-    int shift = 6;                                       // lanes per row: 64, or the power of two that holds nx
-    while (shift > 0 && (1 << (shift - 1)) >= a.nx) --shift;
-    const int sub = lane >> shift, i0 = lane & ((1 << shift) - 1), per = 64 >> shift, step = 1 << shift;
     const int rows = a.ny * a.nz;
+    const ppmlr::RowSplit w(a.nx, rows, nw);
+    const int i0 = lane & (w.lanes - 1), sub = lane >> w.shift;
     double smax = 0.0;
     float reached = -1.0f;                               // a lower bound of the wave's maximum so far
-    for (int row0 = wave * per; row0 < rows; row0 += nw * per) {
-        const int row = min(row0 + sub, rows - 1);
+    for (long long n = wave; n < w.units(); n += nw) {
+        const int group = w.parts == 1 ? (int)n : (int)n / w.parts, part = w.parts == 1 ? 0 : (int)n - group * w.parts;
+        const int row = min(group * w.per + sub, rows - 1);
         const int k = row / a.ny, j = row - k * a.ny;
         const double y = a.yc[j], z = a.zc[k], iy = a.rdy[j], iz = a.rdz[k];
-        for (int ii = 0; ii < a.nx; ii += step) {
-            const int i = min(ii + i0, a.nx - 1);
+        const int end = min((part + 1) * w.width, w.cols);
+        for (int col = part * w.width; col < end; ++col) {
+            const int i = min(col * w.lanes + i0, a.nx - 1);
             const double x = a.xc[i], ix = a.rdx[i];
             const T *u = a.u + ((long long)row * a.nx + i);
             const double r = (double)u[0];
@@ -988,15 +990,14 @@ CflArgs<T> cfl_args(const ppmlr_ctx *c, const T *u)
     return a;
 }
 
-// Workgroups of four waves that take every row of zones (or rows, where several
-// fit a wave) once.
-long long cfl_blocks(const ppmlr_ctx *c)
-{
-    const int per = c->n[0] > 32 ? 1 : (c->n[0] > 16 ? 2 : 4);
-    return ((long long)c->n[1] * c->n[2] + 4 * per - 1) / (4 * per);
-}
-
 constexpr int kCflBlocks = 2048;
+
+// Workgroups of four waves for the signal speeds of a grid.
+int cfl_blocks(const ppmlr_ctx *c)
+{
+    const ppmlr::RowSplit w(c->n[0], (long long)c->n[1] * c->n[2], 4 * kCflBlocks);
+    return (int)std::min<long long>((w.units() + 3) / 4, kCflBlocks);
+}
 
 // part: host memory for the workgroups' maxima, or null for the slots; returns
 // the workgroups launched in blocks.
@@ -1005,7 +1006,7 @@ ppmlr_status cfl_typed(ppmlr_ctx *c, const T *u, hipStream_t st, double *part, i
 {
     CflArgs<T> a = cfl_args(c, u);
     a.part = part;
-    *blocks = (int)std::min<long long>(cfl_blocks(c), kCflBlocks);
+    *blocks = cfl_blocks(c);
     hipLaunchKernelGGL(cfl_kernel<T>, dim3((unsigned)*blocks), dim3(256), 0, st, a);
     return hip_check(c, hipGetLastError(), "cfl launch");
 }
@@ -2171,9 +2172,9 @@ ppmlr_status ensemble_typed(ppmlr_ctx *const *ctxs, const ppmlr_state *const *st
     // one launch per sweep: the start-of-call maximum of all members, then per
     // step the dt kernel and three sweep kernels
     if (!persistent && !err) {
-        long long rows = 1;
+        int rows = 1;
         for (int m = 0; m < n; ++m) rows = std::max(rows, cfl_blocks(ctxs[m]));
-        const unsigned gx = (unsigned)std::min<long long>(rows, std::max(64, 2048 / n));
+        const unsigned gx = (unsigned)std::min(rows, std::max(64, 2048 / n));
         hipLaunchKernelGGL(ens_clear_kernel, dim3(n), dim3(ppmlr::kCflSlots), 0, st, (unsigned long long *const *)d_ptr);
         for (int m0 = 0; m0 < n; m0 += 65535)
             hipLaunchKernelGGL(ens_cfl_kernel<T>, dim3(gx, (unsigned)std::min(n - m0, 65535)), dim3(256), 0, st,
