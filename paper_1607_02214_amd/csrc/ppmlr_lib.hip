@@ -26,7 +26,10 @@ using ppmlr::kStatWords;
 using ppmlr::kStatSlots;
 using ppmlr::March;
 using ppmlr::march_shape;
-using ppmlr::march_stride;
+using ppmlr::row_cost;
+using ppmlr::stride_for;
+using ppmlr::Sweep;
+using ppmlr::sweep_shape;
 
 struct AxisTables {
     // FP64 and FP32 copies: extended widths [M], centres [M], faces [M+1];
@@ -192,8 +195,6 @@ int seg_len(int N, int nseg)
 
 constexpr int kMaxSegments = 8;           // autotuner's search range
 
-int stride_for(int threads, int elem);
-
 // Segments per pencil: the context's setting, or (0 = automatic) the fewest
 // whose tile of one pencil segment fits a workgroup and the LDS (one for
 // any FP32 pencil up to 1010 zones).
@@ -223,22 +224,6 @@ int seg_fast_for(const ppmlr_ctx *c, int axis)
 
 // Zones of one tile's pencil segment (interior + ghosts).
 int tile_M(const ppmlr_ctx *c, int axis, int elem) { return seg_len(c->n[axis], seg_count(c, axis, elem)) + 2 * kG; }
-
-// LDS stride of a sweep launch with `threads` lanes: the smallest of the
-// compile-time strides 256, 384, ..., 1024 (steps of 128) that holds them and
-// whose two buffers fit the 160 KB LDS; 0 = the exact runtime stride (an
-// FP64 tile of 832 lanes, whose rounded stride would not fit); -1 = does not
-// fit.  A stride close to the workgroup size leaves LDS for more resident
-// workgroups per CU.
-int stride_for(int threads, int elem)
-{
-    if (threads > 1024) return -1;
-    const int sm = threads <= 256 ? 256 : (threads + 127) / 128 * 128;
-    const int P = threads / (2 * kG + 1) + 1;   // at most: a tile's pencils have 15 zones or more
-    if (ppmlr::lds_bytes(kSlotsA + kSlotsB, sm, elem, P) <= 160 * 1024) return sm;
-    if (ppmlr::lds_bytes(kSlotsA + kSlotsB, threads, elem, P) <= 160 * 1024 && elem == 8) return 0;
-    return -1;
-}
 
 // Automatic tile: the number of pencil segments per workgroup that wastes the
 // fewest lanes (padding to whole waves plus ghost zones), within the thread
@@ -427,72 +412,21 @@ bool learned_f32(const ppmlr_ctx *c, int elem)
     return elem == 4 && c->guess == PPMLR_GUESS_LEARNED && c->opt.tracing == PPMLR_TRACE_TWO_FAMILY;
 }
 
-size_t march_lds(const ppmlr_ctx *c, int axis, int P, int SM, int elem)
+Sweep sweep_of(const ppmlr_ctx *c, int axis, int elem)
 {
-    return ppmlr::lds_bytes((learned_f32(c, elem) ? ppmlr::kSlotsAGuess : kSlotsA) + kSlotsB, SM, elem, P) +
-           (c->bc_hi[axis] == PPMLR_PERIODIC ? ppmlr::lds_wrap_bytes(P, elem) : 0);
+    return {{c->n[0], c->n[1], c->n[2]}, axis, elem, c->opt.tracing == PPMLR_TRACE_CHARACTERISTIC, learned_f32(c, elem),
+            c->bc_hi[axis] == PPMLR_PERIODIC};
 }
 
-// How much a y or z sweep is slowed by rows of w 4-byte words (see march_search).
-double row_cost(int axis, int w, bool cached)
-{
-    if (axis == 0) return 1.0;
-    if (cached) return w >= 4 ? 1.0 : (w == 3 ? 1.1 : (w == 2 ? 1.15 : 1.7));
-    return w >= 8 ? 1.0 : (w == 4 ? (axis == 1 ? 1.03 : 1.25) : (w > 4 ? 1.12 : (w == 3 ? 1.2 : (w == 2 ? 1.35 : 1.8))));
-}
-
-// The march for whole pencils along axis, with P pencils per workgroup (0:
-// chosen), or none (P = 0): the learned and harvest modes keep whole-pencil
-// tiles, and so does an explicit P that no chunk of four waves holds.
-//
-// Workgroups are held to 4 waves: one per SIMD, so that a CU fills evenly (with
-// 5 or 7 waves, two of a workgroup meet on a SIMD, and half as many workgroups
-// were resident: y sweep 431 and 409 us against 304 us with 4).  Among the
-// shapes the estimated time decides: chunks one after the other, times the
-// rounds of workgroups that the chip holds at once, times the time of a chunk,
-// which grows with the waves that share a CU (FP32, us: 4.5 + 0.155 per wave,
-// from 256x192x192 sweeps at 8, 12, 16 and 20 waves per CU: 560, 413, 336, 295
-// us).  In y and z, rows narrower than 32 B cost more (y, z sweep: 16 B 1.03,
-// 1.30; 8 B 1.35; widths other than powers of two 1.1 to 1.2); less so where
-// the state stays in the last-level cache (128x96x96: 16 B 1.0, 8 B 1.15).
-March march_search(const ppmlr_ctx *c, int axis, int elem, int P_req)
-{
-    March best;
-    const bool trace = c->opt.tracing == PPMLR_TRACE_CHARACTERISTIC;
-    const int N = c->n[axis], nq = axis == 0 ? c->n[1] : c->n[0];
-    const double nr = axis == 2 ? c->n[1] : c->n[2];
-    const int wps = elem == 4 ? (trace || learned_f32(c, elem) ? 4 : 5) : (trace ? 2 : 3);     // waves per SIMD (registers)
-    const double t0 = elem == 4 ? (trace ? 5.0 : 4.5) : 4.2;           // us of a chunk alone, and per wave on its CU
-    const double t1 = elem == 4 ? (trace ? 0.22 : 0.155) : (trace ? 0.78 : 0.52);
-    const bool cached = 8.0 * c->n[0] * c->n[1] * c->n[2] * elem < 128e6;
-    double best_t = 1e300;
-    for (int P = P_req > 0 ? P_req : 1; P <= (P_req > 0 ? P_req : 8); ++P) {
-        for (int C = 1; C <= 64 && (C == 1 || (N + kG) / C >= kG); ++C) {
-            March m = march_shape(N, P, C, 320);
-            if (m.P == 0) continue;
-            const int waves = block_threads(P, m.M) / 64;
-            m.SM = march_stride(m, elem, trace);
-            const size_t lds = (march_lds(c, axis, P, m.SM, elem) + 1279) / 1280 * 1280;
-            const double per_cu = std::min((int)(160 * 1024 / lds), 4 * wps / waves);
-            const double wgs = (double)((nq + P - 1) / P) * nr, rounds = wgs / (256.0 * per_cu);
-            const double row = row_cost(axis, P * elem / 4, cached);
-            // (a last round that is not full takes a round's time; with many
-            // rounds workgroups follow each other and it is less)
-            const double t = rounds <= 1.0 ? C * row * (t0 + t1 * waves * std::ceil(wgs / 256.0))
-                                           : C * row * (t0 + t1 * waves * per_cu) * (rounds + 0.2);
-            if (t < best_t - 1e-9) { best_t = t; best = m; }
-        }
-    }
-    return best;
-}
-
+// The shape of a sweep of whole pencils with the context's setting, or none (P
+// = 0): the harvest mode keeps its tiles.
 const March &march_plan(ppmlr_ctx *c, int axis, int elem)
 {
     static const March none;
     if (c->opt.tracing == PPMLR_TRACE_TWO_FAMILY && elem == 4 && c->guess == PPMLR_GUESS_HARVEST) return none;
     const int f = elem == 8 ? 1 : (learned_f32(c, elem) ? 2 : 0);
     if (c->march_req[axis][f] != c->tile[axis]) {
-        c->march[axis][f] = march_search(c, axis, elem, c->tile[axis]);
+        c->march[axis][f] = sweep_shape(sweep_of(c, axis, elem), c->tile[axis]);
         c->march_req[axis][f] = c->tile[axis];
     }
     return c->march[axis][f];
@@ -503,7 +437,7 @@ ppmlr_status launch_march_sm(ppmlr_ctx *c, const ppmlr::SweepArgs<T> &a, hipStre
 {
     // (counters are always collected in the kernel, and not stored without a buffer)
     if (block_threads(a.P, a.M) > SM) return fail(c, PPMLR_EINVAL, "march exceeds its workgroup");
-    const size_t lds = march_lds(c, AX, a.P, SM, (int)sizeof(T));
+    const size_t lds = ppmlr::march_lds(sweep_of(c, AX, (int)sizeof(T)), a.P, SM);
     auto kern = ppmlr::sweep_kernel<AX, T, true, FUSE, SM, GUESS, TRACE, true>;
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -762,7 +696,7 @@ __device__ inline double cfl_rows(const CflArgs<T> &a, int wave, int nw)
     const int i0 = lane & (w.lanes - 1), sub = lane >> w.shift;
     double smax = 0.0;
     float reached = -1.0f;                               // a lower bound of the wave's maximum so far
-    for (long long n = wave; n < w.units(); n += nw) {
+    for (unsigned n = (unsigned)wave; n < w.units(); n += (unsigned)nw) {
         const int group = w.parts == 1 ? (int)n : (int)n / w.parts, part = w.parts == 1 ? 0 : (int)n - group * w.parts;
         const int row = min(group * w.per + sub, rows - 1);
         const int k = row / a.ny, j = row - k * a.ny;
@@ -996,7 +930,7 @@ constexpr int kCflBlocks = 2048;
 int cfl_blocks(const ppmlr_ctx *c)
 {
     const ppmlr::RowSplit w(c->n[0], (long long)c->n[1] * c->n[2], 4 * kCflBlocks);
-    return (int)std::min<long long>((w.units() + 3) / 4, kCflBlocks);
+    return (int)std::min(w.units() / 4 + 1, (unsigned)kCflBlocks);
 }
 
 // part: host memory for the workgroups' maxima, or null for the slots; returns

@@ -16,7 +16,7 @@ namespace ppmlr {
 // column); with more waves than groups every group goes to `parts` waves,
 // `width` columns each.  (A wave per group and all its columns was 60 us for
 // 4000 x 1 x 1 zones, one wave over 63 columns in turn; with the columns dealt
-// out 18 us.)
+// out 19 us.)
 struct RowSplit {
     int shift, lanes, per, cols, groups, parts, width;      // lanes = 2^shift
     PPMLR_HD RowSplit(int nx, long long rows, int waves)
@@ -27,11 +27,13 @@ struct RowSplit {
         per = 64 >> shift;
         cols = ((nx - 1) >> shift) + 1;
         groups = (int)((rows - 1) >> (6 - shift)) + 1;
+        parts = width = 1;
+        if (cols == 1) return;                               // (no divisions on the way to a short row)
         parts = waves / groups < cols ? waves / groups : cols;
         if (parts < 1) parts = 1;
         width = (cols - 1) / parts + 1;
     }
-    PPMLR_HD long long units() const { return (long long)groups * parts; }
+    PPMLR_HD unsigned units() const { return (unsigned)groups * (unsigned)parts; }   // at most the waves or groups
 };
 
 }  // namespace ppmlr
