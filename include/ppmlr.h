@@ -391,8 +391,9 @@ ppmlr_status ppmlr_ensemble_run_noalloc(ppmlr_ctx *const *ctxs, const ppmlr_stat
  * workgroup size (256, 512, 1024) and target segment length (whole pencils,
  * or segments of about 96, 64, 48 or 32 interior zones) on library-owned
  * copies of the states (the callers' states, step counters and times are
- * left unchanged; whole pencils are swept in chunks of 256 lanes whatever the
- * workgroup size, so that they are timed at 512 only where that fits), stores the fastest workgroup size for ensemble calls with
+ * left unchanged; where whole pencils are swept in chunks of 256 lanes along
+ * every axis, whatever the workgroup size, they are timed at 512 only if that
+ * fits), stores the fastest workgroup size for ensemble calls with
  * block = 0, returns it in *block (may be NULL), and sets every member
  * context's segments per axis to the fastest length's; then, at that
  * workgroup size, tries each other length for one axis at a time (over at

@@ -1912,6 +1912,25 @@ March ens_march(const ppmlr_ctx *c, int axis, int elem)
     return best;
 }
 
+// Whether a call with one launch per sweep marches along axis: no member cuts it
+// into segments, and, in FP32, some member's pencils take more than one chunk.
+// Members of one chunk each are better off as tiles that fill the block (four
+// steps, FP32, before the marches / marching / as tiles: 256 members of 32^3 9.7
+// / 10.9 / 8.6 ms, 64 of 64^3 9.5 / 9.2 / 8.8 ms, 16 of 200x200x4 2.4 / 3.6 / 2.2
+// ms; in FP64, where fewer waves fit a CU, 256 of 32^3 20.0 / 17.1 / 18.3 ms).
+// plan: the members' marches.
+bool ens_marches(ppmlr_ctx *const *ctxs, int n, int axis, int elem, March *plan)
+{
+    bool chunks = elem == 8;
+    for (int m = 0; m < n; ++m) {
+        if (seg_count(ctxs[m], axis, elem) != 1) return false;
+        plan[m] = ens_march(ctxs[m], axis, elem);
+        if (plan[m].P == 0) return false;
+        chunks = chunks || plan[m].C > 1;
+    }
+    return chunks;
+}
+
 template <typename T>
 struct EnsTables {
     static constexpr size_t up256(size_t b) { return (b + 255) / 256 * 256; }
@@ -1962,21 +1981,18 @@ ppmlr_status ensemble_typed(ppmlr_ctx *const *ctxs, const ppmlr_state *const *st
     std::vector<ppmlr::SweepArgs<T>> desc((size_t)6 * n);
     std::vector<int> mo((size_t)3 * (n + 1));
     bool stats = false;
-    // Axes that no member cuts into segments are swept by marches (whole pencils
-    // in chunks, in place), whatever the block size: one launch of 256 lanes
-    // (32 members of 96^3 to 160^3, FP32, four steps: 43.6 ms as whole-pencil
-    // tiles of 512 lanes, 36.9 ms; 43.4 ms with the tiles of all members dealt
-    // out to the XCDs as one list).  The persistent launch has no registers for
-    // them and keeps tiles.
+    // Marches (whole pencils in chunks, in place) are one launch of 256 lanes,
+    // whatever the block size (32 members of 96^3 to 160^3, FP32, four steps: 43.6
+    // ms as whole-pencil tiles of 512 lanes, 36.9 ms; 43.4 ms with the tiles of all
+    // members dealt out to the XCDs as one list).  The persistent launch has no
+    // registers for them and keeps tiles.
     bool march[3];
     int pmax = 1;
     bool periodic = false;
     std::vector<March> plan((size_t)3 * n);
     for (int ax = 0; ax < 3; ++ax) {
-        march[ax] = !persistent;
+        march[ax] = !persistent && ens_marches(ctxs, n, ax, (int)sizeof(T), &plan[(size_t)ax * n]);
         for (int m = 0; m < n && march[ax]; ++m) {
-            plan[(size_t)ax * n + m] = ens_march(ctxs[m], ax, (int)sizeof(T));
-            march[ax] = seg_count(ctxs[m], ax, (int)sizeof(T)) == 1 && plan[(size_t)ax * n + m].P > 0;
             pmax = std::max(pmax, plan[(size_t)ax * n + m].P);
             periodic = periodic || ctxs[m]->bc_hi[ax] == PPMLR_PERIODIC;
         }
@@ -2367,12 +2383,19 @@ ppmlr_status ppmlr_ensemble_autotune(ppmlr_ctx *const *ctxs, const ppmlr_state *
     hipEvent_t t0 = nullptr, t1 = nullptr;
     if (!e) e = hip_check(ctxs[0], hipEventCreate(&t0), "hipEventCreate");
     if (!e) e = hip_check(ctxs[0], hipEventCreate(&t1), "hipEventCreate");
+    auto all_march = [&]() {
+        std::vector<March> plan(n);
+        const int elem = states[0]->dtype == PPMLR_F64 ? 8 : 4;
+        return ens_marches(ctxs, n, 0, elem, plan.data()) && ens_marches(ctxs, n, 1, elem, plan.data()) &&
+               ens_marches(ctxs, n, 2, elem, plan.data());
+    };
     for (int cand = 0; cand < 15 && !e; ++cand) {
         const int B = cands[cand / 5], len = lens[cand % 5];
         set_lengths(len);
         if (ensemble_check(ctxs, tptr.data(), n, reps, cfl, B) != PPMLR_OK) continue;
-        // (whole pencils march, whatever the block: the usual one is tried if it may be)
-        if (len == 0 && B != 512 && g_ensemble_launch == PPMLR_ENSEMBLE_PER_SWEEP &&
+        // (marches do not depend on the block: where all axes march the usual one
+        // is tried, if it may be)
+        if (len == 0 && B != 512 && g_ensemble_launch == PPMLR_ENSEMBLE_PER_SWEEP && all_march() &&
             ensemble_check(ctxs, tptr.data(), n, reps, cfl, 512) == PPMLR_OK)
             continue;
         e = hip_check(ctxs[0], hipEventRecord(t0, st), "hipEventRecord");

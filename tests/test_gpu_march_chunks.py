@@ -124,3 +124,27 @@ def test_march_of_many_chunks_in_a_graph():
             ctx.sweep(ref, dt, axis)
         torch.cuda.synchronize()
         assert torch.equal(u, ref)
+
+
+# an ensemble's axes: tiles where every member is one chunk (FP32), marches
+# where one is not, next to members of one chunk
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [F32, F64])
+def test_ensemble_axes_of_one_chunk_and_of_many(dtype):
+    from paper_1607_02214_amd import ppmlr
+    cases = [GC.smooth_case(shape=(17, 33, 300), seed=1), GC.blast_case(n=(40, 33, 30)), GC.c1_case(32)]
+    for block in (256, 512):
+        if block == 256 and max(len(f) for c in cases for f in c.faces) + 13 > block:
+            use = cases[1:]
+        else:
+            use = cases
+        ctxs = [c.context() for c in use]
+        us = [torch.from_numpy(c.U).to("cuda", dtype).contiguous() for c in use]
+        ppmlr.ensemble_run(ctxs, us, 3, 0.4, block=block)
+        for c, ctx, u in zip(use, ctxs, us):
+            solo = c.context()
+            for a in range(3):
+                solo.set_segments(a, 2)
+            w = torch.from_numpy(c.U).to("cuda", dtype).contiguous()
+            solo.advance(w, 3, 0.4)
+            assert torch.equal(u, w) and ctx.time(u) == solo.time(w)
