@@ -82,9 +82,9 @@ def load_traffic(dtype: str):
 
 
 def pencils(ctx, axis, *dtype):
-    """Pencils per workgroup to give another context for the same sweeps: an
-    axis without segments keeps the automatic choice (0), whose shape is not the
-    whole-pencil tile that get_tile returns."""
+    """Pencils per workgroup to give a context of another mode, or a search
+    among segments: an axis without segments keeps the automatic choice (0),
+    which is each mode's own."""
     return 0 if ctx.get_segments(axis, *dtype) == 1 else ctx.get_tile(axis, *dtype)
 
 
@@ -189,7 +189,7 @@ def series_leg(args, setup, make_ctx, shape_ctx):
     for a in range(3):
         ctx.set_tile(a, 1)
         ctx.set_segments(a, shape_ctx.get_segments(a))
-        ctx.set_tile(a, pencils(shape_ctx, a))
+        ctx.set_tile(a, shape_ctx.get_tile(a))
         ctx.set_segment_order(a, shape_ctx.get_segment_order(a))
     u = torch.from_numpy(setup.U).to(device="cuda", dtype=torch.float32).contiguous()
     t_end = 1.2 * (args.warmup + args.steps) * ctx.cfl_dt(u, args.cfl)
@@ -224,7 +224,7 @@ def ionosphere_leg(args, setup, make_ctx, shape_ctx, u_dev):
     for a in range(3):
         ctx.set_tile(a, 1)
         ctx.set_segments(a, shape_ctx.get_segments(a))
-        ctx.set_tile(a, pencils(shape_ctx, a))
+        ctx.set_tile(a, shape_ctx.get_tile(a))
         ctx.set_segment_order(a, shape_ctx.get_segment_order(a))
     u = u_dev.clone()
     prm = ppmlr.iono_default_params()

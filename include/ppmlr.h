@@ -270,12 +270,14 @@ ppmlr_status ppmlr_kernel_times(ppmlr_ctx *ctx, double ms[3], long long launches
 
 /* Pencils per workgroup for sweeps along axis (tile shape); 0 = automatic.
  * EINVAL if the tile does not fit one workgroup.  With one segment per pencil
- * a workgroup takes its pencils whole, in chunks that follow each other (in
- * place, without a second state), and the automatic choice is the number of
- * pencils and chunks with the least estimated time; the tile of whole pencils
- * whose size ppmlr_get_tile returns serves single-chunk shapes, the harvest
- * mode and counts of pencils that no chunk of 256 lanes holds.  Results do not
- * depend on any of it, bit for bit. */
+ * a workgroup takes its pencils whole, as one tile or in chunks that follow
+ * each other (in place, without a second state), whichever has the least
+ * estimated time, and the automatic choice is that of the pencils too (the
+ * harvest mode takes tiles).  Results do not depend on any of it, bit for bit.
+ * ppmlr_get_tile returns the pencils per workgroup that a sweep of a state of
+ * that dtype is launched with in the context's present mode; given back to
+ * ppmlr_set_tile, with the same segments, they lead to the same launches (also
+ * where they march and a tile of as many pencils would not fit). */
 ppmlr_status ppmlr_set_tile(ppmlr_ctx *ctx, int axis, int pencils);
 ppmlr_status ppmlr_get_tile(const ppmlr_ctx *ctx, int axis, int dtype, int *pencils);
 
@@ -309,10 +311,11 @@ ppmlr_status ppmlr_get_segments(const ppmlr_ctx *ctx, int axis, int dtype, int *
 
 /* Tile autotuner: for each axis, times `reps` sweeps of every tile shape
  * (pencils per workgroup or the automatic choice, segments per pencil from 1
- * to 8, both segment orders) that fits one workgroup on a library-owned copy of the state (the caller's state is not
- * modified), times the three fastest again with 3 x reps sweeps, keeps the
- * fastest per axis (the shape is set on the context) and returns the pencils
- * per workgroup in tiles[3] (may be NULL).  The sweeps timed use the context's initial-guess mode
+ * to 8, both segment orders) that fits one workgroup on a library-owned copy of
+ * the state (the caller's state is not modified), times the three fastest again
+ * with 3 x reps sweeps, keeps the fastest per axis (the shape is set on the
+ * context) and returns the pencils per workgroup, as ppmlr_get_tile does, in
+ * tiles[3] (may be NULL).  The sweeps timed use the context's initial-guess mode
  * (the harvest mode is timed as the plain one and records nothing); they add
  * to the counters.  Synchronises; allocates and frees one state-sized buffer. */
 ppmlr_status ppmlr_autotune(ppmlr_ctx *ctx, const ppmlr_state *state, int reps, int tiles[3]);

@@ -246,9 +246,12 @@ int auto_tile(const ppmlr_ctx *c, int axis, int elem)
     return best;
 }
 
+// Pencils per workgroup of a tile (a setting that only a march holds, see
+// ppmlr_set_tile, leaves the tiles of other modes to the automatic choice).
 int pick_tile(const ppmlr_ctx *c, int axis, int elem)
 {
-    return c->tile[axis] > 0 ? c->tile[axis] : auto_tile(c, axis, elem);
+    const bool set = c->tile[axis] > 0 && block_threads(c->tile[axis], tile_M(c, axis, 4)) <= 1024;
+    return set ? c->tile[axis] : auto_tile(c, axis, elem);
 }
 
 template <typename T>
@@ -418,18 +421,43 @@ Sweep sweep_of(const ppmlr_ctx *c, int axis, int elem)
             c->bc_hi[axis] == PPMLR_PERIODIC};
 }
 
-// The shape of a sweep of whole pencils with the context's setting, or none (P
-// = 0): the harvest mode keeps its tiles.
+// Whether sweeps keep tiles although no axis is cut: the harvest mode.
+bool keeps_tiles(const ppmlr_ctx *c, int elem)
+{
+    return c->opt.tracing == PPMLR_TRACE_TWO_FAMILY && elem == 4 && c->guess == PPMLR_GUESS_HARVEST;
+}
+
+// The shape of a sweep of whole pencils with the context's setting, or none (P = 0).
 const March &march_plan(ppmlr_ctx *c, int axis, int elem)
 {
     static const March none;
-    if (c->opt.tracing == PPMLR_TRACE_TWO_FAMILY && elem == 4 && c->guess == PPMLR_GUESS_HARVEST) return none;
+    if (keeps_tiles(c, elem)) return none;
     const int f = elem == 8 ? 1 : (learned_f32(c, elem) ? 2 : 0);
     if (c->march_req[axis][f] != c->tile[axis]) {
         c->march[axis][f] = sweep_shape(sweep_of(c, axis, elem), c->tile[axis]);
         c->march_req[axis][f] = c->tile[axis];
     }
     return c->march[axis][f];
+}
+
+// Pencils per workgroup of the sweeps along axis as they are launched.
+int launched_pencils(const ppmlr_ctx *c, int axis, int elem)
+{
+    const int P = seg_count(c, axis, elem) == 1 && !keeps_tiles(c, elem)
+                      ? sweep_shape(sweep_of(c, axis, elem), c->tile[axis]).P : 0;
+    return P > 0 ? P : pick_tile(c, axis, elem);
+}
+
+// Whether P pencils are the automatic choice along axis, in one of the
+// precisions and modes that the context may be used in.
+bool chosen_pencils(const ppmlr_ctx *c, int axis, int P)
+{
+    for (int kind = 0; kind < 3; ++kind) {
+        Sweep s = sweep_of(c, axis, kind == 1 ? 8 : 4);
+        s.learned = kind == 2 && !s.trace;
+        if (seg_count(c, axis, s.elem) == 1 && sweep_shape(s, 0).P == P) return true;
+    }
+    return false;
 }
 
 template <int AX, typename T, bool FUSE, int SM, bool TRACE, int GUESS>
@@ -1528,8 +1556,9 @@ ppmlr_status ppmlr_set_tile(ppmlr_ctx *c, int axis, int pencils)
     if (!c || axis < 0 || axis > 2 || pencils < 0) return PPMLR_EINVAL;
     if (pencils > 0) {
         int M = tile_M(c, axis, 4);
-        if (block_threads(pencils, M) > 1024) return fail(c, PPMLR_EINVAL, "tile exceeds 1024 threads");
-        if (ppmlr::lds_bytes(kSlotsA + kSlotsB, pencils * M, 4, pencils) > 160 * 1024)
+        if (block_threads(pencils, M) > 1024) {
+            if (!chosen_pencils(c, axis, pencils)) return fail(c, PPMLR_EINVAL, "tile exceeds 1024 threads");
+        } else if (ppmlr::lds_bytes(kSlotsA + kSlotsB, pencils * M, 4, pencils) > 160 * 1024)
             return fail(c, PPMLR_EINVAL, "tile exceeds the LDS budget");
     }
     c->tile[axis] = pencils;
@@ -1546,7 +1575,8 @@ ppmlr_status ppmlr_set_segments(ppmlr_ctx *c, int axis, int segments)
     const char *why = nullptr;
     if (L == 0) why = "segment count leaves a segment empty";
     else if (k > 1 && L < kG) why = "segments shorter than the ghost width";
-    else if (c->tile[axis] > 0 && block_threads(c->tile[axis], L + 2 * kG) > 1024) why = "tile exceeds 1024 threads";
+    else if (c->tile[axis] > 0 && block_threads(c->tile[axis], L + 2 * kG) > 1024 &&
+             !(k == 1 && chosen_pencils(c, axis, c->tile[axis]))) why = "tile exceeds 1024 threads";
     if (why) {
         c->seg[axis] = old;
         return fail(c, PPMLR_EINVAL, why);
@@ -1652,7 +1682,7 @@ ppmlr_status ppmlr_autotune(ppmlr_ctx *c, const ppmlr_state *s, int reps, int ti
         c->tile[axis] = best.P;
         c->seg[axis] = best.nseg;
         c->seg_order[axis] = best.order;
-        if (tiles) tiles[axis] = pick_tile(c, axis, (int)elem);
+        if (tiles) tiles[axis] = launched_pencils(c, axis, (int)elem);
     }
     c->profiling = prof;
     c->guess = guess;
@@ -2466,7 +2496,7 @@ ppmlr_status ppmlr_ensemble_autotune(ppmlr_ctx *const *ctxs, const ppmlr_state *
 ppmlr_status ppmlr_get_tile(const ppmlr_ctx *c, int axis, int dtype, int *pencils)
 {
     if (!c || axis < 0 || axis > 2 || !pencils) return PPMLR_EINVAL;
-    *pencils = pick_tile(c, axis, dtype == PPMLR_F64 ? 8 : 4);
+    *pencils = launched_pencils(c, axis, dtype == PPMLR_F64 ? 8 : 4);
     return PPMLR_OK;
 }
 
