@@ -1451,11 +1451,13 @@ ppmlr_status ppmlr_advance(ppmlr_ctx *c, const ppmlr_state *s, int nsteps, doubl
     static const int even[3] = {0, 1, 2}, odd[3] = {2, 1, 0};
     Flow f{s->u, s->u};
     // Every workgroup of the first sweep forms dt, about 1 us before its zones
-    // are loaded: a round of workgroups, some 300 thousand zones, costs that
-    // once, the kernel 3.3 to 4.7 us and a launch gap (20 steps of 32^3, FP64:
-    // 590 us in the sweep, 640 us with the kernel; 8 steps of 256x192x192, FP32,
-    // shorter workgroups of segments: 7480 and 7340 us).
-    const bool dt_in_sweep = c->series_n == 0 && (long long)c->n[0] * c->n[1] * c->n[2] <= 1 << 20;
+    // are loaded: a round of workgroups costs that once, the kernel 3.3 to 4.7 us
+    // and a launch gap.  20 steps, in the sweep and with the kernel: FP32 32^3 495
+    // and 524 us, 64^3 871 and 894, 101^3 2398 and 2407, 128^3 4518 and 4526, 160^3
+    // 7307 and 7249; FP64 32^3 596 and 625 us, 64^3 1775 and 1802, 80^3 2995 and
+    // 2974, 101^3 4823 and 4736.
+    const long long zones = (long long)c->n[0] * c->n[1] * c->n[2];
+    const bool dt_in_sweep = c->series_n == 0 && zones * (s->dtype == PPMLR_F64 ? 8 : 4) <= 4 << 20;
     for (int n = 0; n < nsteps; ++n) {
         // The last sweep of a step, but for the call's last, leaves the signal
         // speeds of the next dt in the slots.  dt is formed from them by a kernel
