@@ -38,8 +38,9 @@ FP32_UNPACKED_TFLOPS = 78.6       # the same without packed instructions: 256 CU
 FLOPS_PER_ZONE_SWEEP = 1875.8
 FLOPS_SOURCE = "oracle instrumented count (oracle/flop_count.py, 64 pencils per axis of the start state)"
 # What the kernels execute: FP32 operations per lane (ADD + MUL + TRANS + 2 FMA)
-# of the y sweep from its VALU counters (committed counter summary).
-KERNEL_FP32_OPS_PER_LANE = 1119.0
+# of the y sweep, a lane being one zone of one chunk, from its VALU counters
+# (committed counter summary).
+KERNEL_FP32_OPS_PER_LANE = 929.0
 PROFILES = os.path.join(ROOT, "profiles")
 # Vector-instruction issue: one wave64 VALU instruction per CU per cycle
 # (256 CUs at 2.4 GHz); FP32 transcendentals (rcp, sqrt, rsq) issue at half

@@ -21,7 +21,10 @@
 //   R7 remap parabolas, donor-cell fluxes             A -> B
 //   R8 conservative update, sources, store            B
 // The pencil axis is a template parameter so that all component indexing is
-// static (no private arrays with dynamic indices).
+// static.  Private arrays are in registers, but for the wave structure of the
+// characteristic mode (Waves7, 68 B a lane in FP32, 136 B in FP64): a choice
+// between two of its members by a sign is compiled to a store at a computed
+// address.
 #pragma once
 #include "ppmlr_char.hpp"
 #include "ppmlr_march.hpp"
@@ -372,8 +375,10 @@ __device__ inline bool guess_selects(T rl, T rr, T ul, T ur, T pl, T pr, T gate_
 // segment `seg` (interior zones seg*L .. seg*L + L - 1 with G zones on either
 // side; one segment = the whole pencil).  A zone's result depends on the
 // zones within G of it only, so segments give the whole-pencil result
-// bit for bit; neighbour reads are clamped at the ends of the pencil's
-// extended range, as for a whole pencil.  tq, r: tile position (q tiles of P
+// bit for bit.  Neighbours are read without a bounds test (see the LDS layout):
+// what a zone at an end of the tile reads beyond it has no meaning, and reaches
+// no further than the G ghosts there, the radius of all stages together; a stage
+// that reads further needs more ghosts.  tq, r: tile position (q tiles of P
 // pencils, r the slow transverse index).  The state is read through a.vin
 // and written through a.var: the same buffer for whole pencils, different
 // buffers for segments (a segment's ghost zones are other segments' interior
