@@ -169,16 +169,19 @@ inline double march_time(const Sweep &s, int P, int C, const Load &l)
 }
 
 // Estimated us of tiles (C = 1) and of a march, for the choice between them: as
-// above, with what tells in few rounds.  On 27 grids from 28^3 to 160^3 and
-// 60x400x100, in every mode and precision, the shape chosen is within 6 % of the
-// fastest count of pencils on all but 19 of 333 sweeps measured.
+// above, with what tells in few rounds.  On 362 sweeps of 150 random grids (24 to
+// 420 zones an axis, every mode and precision) whose shape is not the one of
+// march_time over tiles and marches alike: 0.87 of its time in the mean, 17 of
+// them 3 to 13 % slower.  On 27 other grids the shape chosen was within 6 % of
+// the fastest count of pencils on all but 20 of 330 sweeps.
 inline double sweep_time(const Sweep &s, int P, int C, const Load &l)
 {
-    // (rows of the whole grid that are as narrow are one piece for all workgroups;
-    // 100x100x100, y and z: tiles with rows of 8 B 1.3)
+    // (rows of the whole grid that are as narrow are one piece for all workgroups.
+    // Tiles suffer more from narrow ones than marches do: 100x100x100, y and z,
+    // rows of 8 B 1.3; 36x123x241, z, rows of 4 B 2.7, 33x167x189, y, 2.3)
     const int w = P * s.elem / 4;
     const double row = l.cached && l.nq * s.elem <= 32 ? 1.0
-                       : l.cached && w == 2 && s.axis > 0 ? 1.3 : row_cost(s.axis, w, l.cached);
+                       : l.cached && w <= 2 && s.axis > 0 ? (w == 2 ? (s.elem == 8 ? 1.3 : 1.4) : 2.4) : row_cost(s.axis, w, l.cached);
     const double full = row * (l.t0 + l.t1 * l.waves * l.per_cu);
     // a round that leaves room (where narrow rows cost what the waves of a CU wait
     // for each other): so many workgroups on the fullest CU
@@ -189,8 +192,9 @@ inline double sweep_time(const Sweep &s, int P, int C, const Load &l)
     const double n = C == 1 ? 1.0 : C * ((s.trace || s.learned ? 1.0 : 1.075) + 0.01 * (C - 2));
     // (the chip's loads come all at once as it fills)
     if (l.rounds <= 1.0) return n * part(l.wgs) * (1.0 + 0.2 * l.rounds);
-    const double whole = std::floor(l.rounds);
-    if (l.rounds <= 4.0) return n * (full * whole + part(l.wgs - 256.0 * l.per_cu * whole));
+    // (the second round; a few workgroups of it find room as the first ones end)
+    const double more = l.wgs - 256.0 * l.per_cu;
+    if (l.rounds <= 2.0) return n * (full + part(more) * std::min(1.0, 25.0 * (l.rounds - 1.0)));
     return n * full * (l.rounds + 0.2);
 }
 
@@ -232,13 +236,18 @@ inline March sweep_shape(const Sweep &s, int P_req)
         const int stride = s.learned ? (threads <= 256 ? 256 : (threads <= 512 ? 512 : 1024)) : stride_for(threads, s.elem);
         const bool wide = threads > 256;
         if (threads > 1024 || stride < 0 || (wide && P > 8 && P_req == 0)) continue;
+        // (FP64 tiles of more than 12 waves, 8 with characteristic tracing, spill a
+        // third of their registers: 189x26x36, x, four pencils 35 us, one 22 us)
+        const bool spills = s.elem == 8 && threads > (s.trace ? 512 : 768);
         // (FP32 tiles have the registers for 6 waves per SIMD, of which the sixth is
         // room and no gain: z sweep of 100x100x100, 4 waves, 45 us, and 38 us as two
         // chunks at 5 per SIMD)
         const int tile_wps = wide && wps == 5 ? 6 : wps;
         const Load l(s, P, threads / 64, lds_bytes((s.learned ? kSlotsAGuess : kSlotsA) + kSlotsB,
                                                    stride > 0 ? stride : threads, s.elem, P), tile_wps);
-        if (wide && l.rounds > (P == 1 && tile_wps == 6 ? 2.0 : 1.0) && (P_req == 0 || march.P > 0)) continue;
+        if ((spills || (wide && l.rounds > (P == 1 && tile_wps == 6 ? 2.0 : 1.0))) &&
+            (P_req == 0 || march.P > 0))
+            continue;
         const double t = sweep_time(s, P, 1, l);
         if (t < tile_t - 1e-9) {
             tile_t = t;

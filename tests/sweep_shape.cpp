@@ -34,7 +34,7 @@ static bool launchable(const Sweep &s, int P_req, const March &m)
 int main()
 {
     long long n = 0, marches = 0;
-    const int sizes[] = {1, 2, 3, 8, 14, 28, 32, 61, 97, 192, 300, 512, 1000, 1011, 4000};
+    const int sizes[] = {1, 2, 3, 8, 14, 28, 32, 61, 97, 189, 192, 239, 300, 512, 1000, 1011, 4000};
     for (int nx : sizes)
         for (int ny : sizes)
             for (int nz : sizes)
@@ -47,6 +47,15 @@ int main()
                         if (!launchable(s, 0, m)) return 1;
                         for (int P : {1, 3, 8, 11, 40})
                             if (!launchable(s, P, sweep_shape(s, P))) return 1;
+                        // tiles of one pencil read 4 B of every line they touch: not on a
+                        // grid that fills the chip several times over
+                        if (kind == 0 && axis > 0 && nx > 8 && m.C == 1 && m.P == 1 &&
+                            (double)nx * ny * nz / s.n[axis] > 4000)
+                            return bad(s, 0, m, "narrow rows on a full chip"), 1;
+                        // FP64 tiles that spill are for grids that no march holds
+                        if (m.C == 1 && s.elem == 8 && block_threads(m.P, m.M) > (s.trace ? 512 : 768) &&
+                            march_shape(s.n[axis], m.P, 8, 320).P > 0)
+                            return bad(s, 0, m, "a tile that spills"), 1;
                         // asked for the pencils that were chosen, the shape is the same
                         const March r = sweep_shape(s, m.P);
                         if (r.P != m.P || r.C != m.C || r.L != m.L || r.SM != m.SM) return bad(s, m.P, r, "not the shape chosen"), 1;
