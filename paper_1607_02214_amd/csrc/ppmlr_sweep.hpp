@@ -446,7 +446,10 @@ __device__ __forceinline__ void sweep_tile(const ARGS &args, const int tq, const
     const int q0 = tq * a.P;
     const int Suse = a.S, M = a.M, N = a.N, P = a.P;
     const bool slot_ok = tid < Suse;
-    const int zn = MARCH ? march_lane(tid, Suse) : tid;   // this lane's zone of the tile or chunk
+    // this lane's zone of the tile or chunk (the lanes that pad a workgroup to
+    // whole waves load the last one's line and no lines of their own: y sweep of
+    // 192x160x160 in tiles of one pencil, 94 zones in 128 lanes, 454 and 403 us)
+    const int zn = march_lane(tid, Suse);
     int p, i;
     // zn / divisor as floor((zn + 1/2) * (1/divisor)): exact for zn < 2^12
     // and divisors up to 2^11 (the distance to the next integer, >= 1/(2 div),
