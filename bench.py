@@ -40,7 +40,7 @@ FLOPS_SOURCE = "oracle instrumented count (oracle/flop_count.py, 64 pencils per 
 # What the kernels execute: FP32 operations per lane (ADD + MUL + TRANS + 2 FMA)
 # of the y sweep, a lane being one zone of one chunk, from its VALU counters
 # (committed counter summary).
-KERNEL_FP32_OPS_PER_LANE = 929.0
+KERNEL_FP32_OPS_PER_LANE = 928.0
 PROFILES = os.path.join(ROOT, "profiles")
 # Vector-instruction issue: one wave64 VALU instruction per CU per cycle
 # (256 CUs at 2.4 GHz); FP32 transcendentals (rcp, sqrt, rsq) issue at half
