@@ -171,7 +171,7 @@ inline double march_time(const Sweep &s, int P, int C, const Load &l)
 // Estimated us of tiles (C = 1) and of a march, for the choice between them: as
 // above, with what tells in few rounds.  On 362 sweeps of 150 random grids (24 to
 // 420 zones an axis, every mode and precision) whose shape is not the one of
-// march_time over tiles and marches alike: 0.87 of its time in the mean, 17 of
+// march_time over tiles and marches alike: 0.88 of its time in the mean, 12 of
 // them 3 to 13 % slower.  On 27 other grids the shape chosen was within 6 % of
 // the fastest count of pencils on all but 20 of 330 sweeps.
 inline double sweep_time(const Sweep &s, int P, int C, const Load &l)
@@ -192,9 +192,10 @@ inline double sweep_time(const Sweep &s, int P, int C, const Load &l)
     const double n = C == 1 ? 1.0 : C * ((s.trace || s.learned ? 1.0 : 1.075) + 0.01 * (C - 2));
     // (the chip's loads come all at once as it fills)
     if (l.rounds <= 1.0) return n * part(l.wgs) * (1.0 + 0.2 * l.rounds);
-    // (the second round; a few workgroups of it find room as the first ones end)
+    // (the second round, in step with those before and after it: 1.2 and 2.2 whole
+    // rounds; a few workgroups of it find room as the first ones end)
     const double more = l.wgs - 256.0 * l.per_cu;
-    if (l.rounds <= 2.0) return n * (full + part(more) * std::min(1.0, 25.0 * (l.rounds - 1.0)));
+    if (l.rounds <= 2.0) return n * (1.2 * full + part(more) * std::min(1.0, 25.0 * (l.rounds - 1.0)));
     return n * full * (l.rounds + 0.2);
 }
 
